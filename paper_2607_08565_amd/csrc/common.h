@@ -278,6 +278,7 @@ struct ProbeHdr {
   unsigned long long tot[NREG];     // blocks per region
   unsigned long long n_skip;        // blocks the lookup did not probe (past their request's bound)
   unsigned long long n_search;      // probes the bound's search made
+  unsigned long long n_rec;         // direct form: requests whose counts the lookup left in records (0: above)
 };
 struct ProbeView {
   ProbeHdr *hdr;
@@ -321,6 +322,46 @@ inline uint64_t probe_layout(int64_t n_blocks, ProbeView *v, void *base) {
   return off;
 }
 
+// Direct form of a probe state, for batches of at most DIRECT_MAX blocks: no region order.
+// The hash (or one pass over the keys) writes part_key and part_req in block order, the
+// lookup desc_p in block order; inv, part_blk, skip and the region counts stay unused.
+// Such a batch touches at most DIRECT_MAX lines of the table, which the translation caches
+// hold in any order, and its time is launches and round trips: ordering it took 4 of 5
+// launches and two thirds of the time.  64 requests of 64 to 170 blocks: 118 us of kernels in
+// 23 launches per batch -> 48 in 9.  The line: up to 2^18 blocks both forms of batches of
+// 10^5 blocks take the same time or the direct one less; with the line at 2^20 a replay of
+// 4,096 sessions in batches of 1 to 5 M blocks (its first ones then direct) takes 5.62
+// against 5.52 ms, at 2^22 6.08, and 1,024 long sessions 8.84 against 7.35 ms.
+// With at most DIRECT_REQ requests every request has a flag word (in `hist`: 0 = valid)
+// that its own workgroup writes, and a record of the lookup's counts (in `base`), so nothing has
+// to be cleared by a launch of its own; with more, errors and counts go to the header.
+constexpr uint64_t DIRECT_MAX = uint64_t(1) << 18;
+constexpr int32_t DIRECT_REQ = 16384;
+static_assert(uint64_t(DIRECT_REQ) <= uint64_t(NREG) * PART_WG, "a flag word and a record per request");
+inline bool direct_batch(uint64_t n_blocks) { return n_blocks <= DIRECT_MAX; }
+__device__ __forceinline__ bool request_tiles(const int64_t *blk_off, int32_t r, int32_t n_req, int64_t n_blocks,
+                                              int64_t &b0, int64_t &nb) {
+  b0 = blk_off[r];
+  const int64_t b1 = blk_off[r + 1];
+  nb = b1 - b0;
+  return b0 >= 0 && b0 <= b1 && b1 <= n_blocks && (r > 0 || b0 == 0) && (r + 1 < n_req || b1 == n_blocks);
+}
+// One thread per request: its validity (and, on request 0, the header).
+__device__ __forceinline__ void direct_flag(const ProbeView &pv, int32_t r, int32_t n_req, int64_t n_blocks, bool ok) {
+  if (n_req <= DIRECT_REQ) {
+    pv.hist[r] = ok ? 0u : 1u;
+    if (r == 0) {
+      pv.hdr->err = 0;
+      pv.hdr->n = uint64_t(n_blocks);
+      pv.hdr->n_skip = pv.hdr->n_search = 0;
+      pv.hdr->n_rec = 0;
+    }
+  } else {  // the header was cleared by a launch before
+    if (!ok) atomicCAS(&pv.hdr->err, 0, SMETRIC_EINVAL);
+    if (r == 0) pv.hdr->n = uint64_t(n_blocks);
+  }
+}
+
 // Region partition of a probe state, shared by smetric_probe_partition and the hash call
 // that counts the regions itself (defined with the probe).  partition_head clears the
 // state (and the [chunk][region] counts when the hash is to add into them) in one launch;
@@ -331,6 +372,9 @@ int probe_state_args(const smetric_index *idx, const uint64_t *keys, const int64
 void partition_head(ProbeView &pv, bool clear_hist, hipStream_t stream);
 int partition_tail(const DevIndex &ix, ProbeView &pv, const uint64_t *keys, const int64_t *blk_off, int32_t n_req,
                    uint64_t n, bool counted, hipStream_t stream);
+// Direct form: what precedes the kernel that writes the state (the clear, when more than
+// DIRECT_REQ requests share the header's words, or none write it).
+inline bool direct_needs_clear(int32_t n_req) { return n_req == 0 || n_req > DIRECT_REQ; }
 inline uint64_t partition_chunk(uint64_t n) { return n ? (n + PART_WG - 1) / PART_WG : 1; }
 
 // Sizing shared by host code.

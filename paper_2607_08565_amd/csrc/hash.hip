@@ -121,15 +121,15 @@ __device__ __forceinline__ uint64_t affine_scan64(uint64_t v, const ChainConsts 
 }
 
 // Given lane l's block digest for block j = j0 + l (valid when l < n_valid), finish the
-// tile: salt, chain scan from `carry`, finalise, store.  Returns the chain state after
+// tile: salt, chain scan from `carry`, finalise into `key`.  Returns the chain state after
 // the tile's last block (meaningful when the tile is full).
 __device__ __forceinline__ uint64_t finish_tile(uint64_t d, int64_t j0, int n_valid, uint64_t carry,
-                                                const ChainConsts &cc, uint64_t *out) {
+                                                const ChainConsts &cc, uint64_t &key) {
   const int lane = threadIdx.x & 63;
   const int64_t j = j0 + lane;
   const uint64_t v = affine_scan64(lane < n_valid ? finalise(d + uint64_t(j)) : 0, cc);
   const uint64_t s = cc.Mlane * carry + v;  // s_j = M^(l+1) carry + sum_k M^(l-k) e_k
-  if (lane < n_valid) out[lane] = remap(finalise(s));
+  key = remap(finalise(s));
   return uint64_t(__shfl(int64_t(s), 63, 64));
 }
 
@@ -169,11 +169,14 @@ __device__ __forceinline__ void load_tile16(const int32_t *x, int64_t tile, int6
   }
 }
 
-// COUNT: also the region partition's count pass -- every key adds one to its (partition
+// MODE H_COUNT: also the region partition's count pass -- every key adds one to its (partition
 // chunk, table region) cell of `hist` (chunks of clen blocks, as the partition cuts them);
 // a request's blocks meet at most two chunks unless it is longer than a chunk, so they are
 // counted in LDS and added with one atomic per nonzero cell (the rare rest directly).
-template <int NW, bool COUNT>
+// MODE H_DIRECT: also the direct form of the probe state -- each key and its request in
+// block order, and the request's validity.
+enum HashMode { H_KEYS = 0, H_COUNT = 1, H_DIRECT = 2 };
+template <int NW, int MODE>
 __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restrict__ tokens,
                                                          int64_t n_tokens,
                                                          const int64_t *__restrict__ tok_off,
@@ -183,14 +186,21 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
                                                          uint64_t *__restrict__ keys,
                                                          int32_t *status,
                                                          uint32_t *__restrict__ hist, uint64_t n_buckets,
-                                                         uint64_t nb_inv, uint64_t clen, int *probe_err) {
+                                                         uint64_t nb_inv, uint64_t clen, int *probe_err,
+                                                         ProbeView pv) {
+  constexpr bool COUNT = MODE == H_COUNT;
   __shared__ uint64_t dig[NW][64];
   __shared__ uint64_t agg[NW];
   __shared__ unsigned int lh[COUNT ? 2 * NREG : 1];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = blockIdx.x;
   int64_t t0, b0, nb;
-  if (!request_ok(tok_off, blk_off, r, n_tokens, n_blocks, 16, t0, b0, nb)) {
+  const bool ok = request_ok(tok_off, blk_off, r, n_tokens, n_blocks, 16, t0, b0, nb);
+  if (MODE == H_DIRECT && threadIdx.x == 0) {
+    int64_t tb, tn;
+    direct_flag(pv, r, n_req, n_blocks, request_tiles(blk_off, r, n_req, n_blocks, tb, tn) && ok);
+  }
+  if (!ok) {
     if (threadIdx.x == 0 && status) atomicCAS(status, 0, SMETRIC_EINVAL);
     // counting: this request's blocks are neither written nor counted, so the partition
     // must not run on the counts (it would place more blocks than it reserved)
@@ -265,6 +275,10 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
     if (lane < n_valid) {
       const uint64_t key = remap(finalise(cc.Mlane * c + v));
       keys[b0 + j0 + lane] = key;
+      if (MODE == H_DIRECT) {
+        pv.part_key[b0 + j0 + lane] = key;
+        pv.part_req[b0 + j0 + lane] = uint32_t(r);
+      }
       if (COUNT) {
         const uint64_t b = uint64_t(b0 + j0 + lane);
         const uint32_t g = region_of(key, n_buckets, nb_inv);
@@ -282,20 +296,33 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
   }
 }
 
-// Any even B in [2, 256].
+// Any even B in [2, 256].  DIRECT: as hash16_kernel's H_DIRECT, but a request's token range
+// does not make the probe state invalid (its keys are then the caller's earlier ones).
+template <bool DIRECT>
 __global__ __launch_bounds__(64 * WAVES) void hash_generic_kernel(
     const int32_t *__restrict__ tokens, int64_t n_tokens, const int64_t *__restrict__ tok_off,
     const int64_t *__restrict__ blk_off, int32_t n_req, int64_t n_blocks, int B, uint64_t seed,
-    uint64_t *__restrict__ keys, int32_t *status) {
+    uint64_t *__restrict__ keys, int32_t *status, ProbeView pv) {
   __shared__ uint32_t K[256];
   for (int t = threadIdx.x; t < B; t += blockDim.x) K[t] = uint32_t(splitmix_out(seed, t));
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = blockIdx.x * WAVES + wave;
   if (r >= n_req) return;
+  bool tiles = false;
+  if (DIRECT) {
+    int64_t tb, tn;
+    tiles = request_tiles(blk_off, r, n_req, n_blocks, tb, tn);
+    if (lane == 0) direct_flag(pv, r, n_req, n_blocks, tiles);
+  }
   int64_t t0, b0, nb;
   if (!request_ok(tok_off, blk_off, r, n_tokens, n_blocks, B, t0, b0, nb)) {
     if (lane == 0 && status) atomicCAS(status, 0, SMETRIC_EINVAL);
+    if (DIRECT && tiles)
+      for (int64_t j = lane; j < nb; j += 64) {
+        pv.part_key[b0 + j] = keys[b0 + j];
+        pv.part_req[b0 + j] = uint32_t(r);
+      }
     return;
   }
   const ChainConsts cc = chain_consts(seed, B);
@@ -309,7 +336,15 @@ __global__ __launch_bounds__(64 * WAVES) void hash_generic_kernel(
       for (int k = 0; k < B / 2; ++k)
         d += uint64_t(uint32_t(b[2 * k]) + K[2 * k]) * uint64_t(uint32_t(b[2 * k + 1]) + K[2 * k + 1]);
     }
-    carry = finish_tile(d, j0, n_valid, carry, cc, keys + b0 + j0);
+    uint64_t key;
+    carry = finish_tile(d, j0, n_valid, carry, cc, key);
+    if (lane < n_valid) {
+      keys[b0 + j0 + lane] = key;
+      if (DIRECT) {
+        pv.part_key[b0 + j0 + lane] = key;
+        pv.part_req[b0 + j0 + lane] = uint32_t(r);
+      }
+    }
   }
 }
 
@@ -330,12 +365,12 @@ extern "C" int smetric_hash_blocks(const int32_t *tokens, int64_t n_tokens, cons
     return SMETRIC_EINVAL;
   const dim3 grid((n_req + WAVES - 1) / WAVES), block(64 * WAVES);
   if (block_size == 16)
-    hipLaunchKernelGGL((hash16_kernel<HASH_NW, false>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens, tok_off, blk_off,
-                       n_req, n_blocks, seed, keys, status, static_cast<uint32_t *>(nullptr), uint64_t(0), uint64_t(0),
-                       uint64_t(1), static_cast<int *>(nullptr));
+    hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_KEYS>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens, tok_off,
+                       blk_off, n_req, n_blocks, seed, keys, status, static_cast<uint32_t *>(nullptr), uint64_t(0),
+                       uint64_t(0), uint64_t(1), static_cast<int *>(nullptr), ProbeView{});
   else
-    hipLaunchKernelGGL(hash_generic_kernel, grid, block, 0, stream, tokens, n_tokens, tok_off,
-                       blk_off, n_req, n_blocks, int(block_size), seed, keys, status);
+    hipLaunchKernelGGL(hash_generic_kernel<false>, grid, block, 0, stream, tokens, n_tokens, tok_off,
+                       blk_off, n_req, n_blocks, int(block_size), seed, keys, status, ProbeView{});
   return hip_rc(hipGetLastError());
 }
 
@@ -349,16 +384,28 @@ extern "C" int smetric_hash_partition(const int32_t *tokens, int64_t n_tokens, c
   if (int rc = probe_state_args(idx, keys, blk_off, n_req, n_blocks, probe, probe_bytes)) return rc;
   ProbeView pv;
   probe_layout(n_blocks, &pv, probe);
+  if (direct_batch(uint64_t(n_blocks))) {
+    if (direct_needs_clear(n_req)) partition_head(pv, false, stream);
+    if (n_req > 0 && block_size == 16)
+      hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_DIRECT>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens,
+                         tok_off, blk_off, n_req, n_blocks, seed, keys, status, static_cast<uint32_t *>(nullptr),
+                         uint64_t(0), uint64_t(0), uint64_t(1), static_cast<int *>(nullptr), pv);
+    else if (n_req > 0)
+      hipLaunchKernelGGL(hash_generic_kernel<true>, dim3((n_req + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, stream,
+                         tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, int(block_size), seed, keys, status, pv);
+    return hip_rc(hipGetLastError());
+  }
   const DevIndex ix = dev_view(idx);  // geometry only
   const bool counted = block_size == 16 && n_req > 0;
   partition_head(pv, counted, stream);
   if (counted)
-    hipLaunchKernelGGL((hash16_kernel<HASH_NW, true>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens,
+    hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_COUNT>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens,
                        tok_off, blk_off, n_req, n_blocks, seed, keys, status, pv.hist, ix.n_buckets, ix.nb_inv,
-                       partition_chunk(uint64_t(n_blocks)), &pv.hdr->err);
+                       partition_chunk(uint64_t(n_blocks)), &pv.hdr->err, ProbeView{});
   else if (n_req > 0)
-    hipLaunchKernelGGL(hash_generic_kernel, dim3((n_req + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, stream, tokens,
-                       n_tokens, tok_off, blk_off, n_req, n_blocks, int(block_size), seed, keys, status);
+    hipLaunchKernelGGL(hash_generic_kernel<false>, dim3((n_req + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, stream,
+                       tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, int(block_size), seed, keys, status,
+                       ProbeView{});
   return partition_tail(ix, pv, keys, blk_off, n_req, uint64_t(n_blocks), counted, stream);
 }
 

@@ -25,15 +25,16 @@
 //
 // Insert pipeline (no sort, no host synchronisation):
 //   clear      scratch dedupe table
-//   probe      per pair (r, j): validate; find (key, target) -> refresh position, or
+//   find       per pair (r, j): validate; find (key, target) -> refresh position, or
 //              enter the pair in the dedupe table keyed by (key, instance), keeping the
-//              lowest request index (atomic min), and list each distinct new pair once
-//   check      one thread: first error -> EINVAL/EFULL, nothing changes; else count
-//   refresh    epoch = max(old, epoch) for existing entries
-//   place      each distinct new pair claims a slot; the thread whose slot becomes the
-//              key's (T+1)-th plain slot -- unique, since claims fill a chain in order --
-//              queues the key for conversion
+//              lowest request index (atomic min); the first to enter a pair places it.  The
+//              last workgroup checks: first error -> EINVAL/EFULL, nothing changes; else count
+//   apply      epoch = max(old, epoch) for existing entries; each distinct new pair claims a
+//              slot, and the thread whose slot becomes the key's (T+1)-th plain slot --
+//              unique, since claims fill a chain in order -- queues the key for conversion
 //   spill      queued keys get a bitmap record, member slots, a header and tombstones
+// Batches of at most SI_MAX blocks take one launch (ins_small_kernel); a probed batch past
+// the direct form's size takes the region-ordered passes.
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "common.h"
@@ -155,6 +156,13 @@ __device__ Found find_member(const DevIndex &ix, uint64_t key, uint32_t inst) {
   return Found{-1, 0};
 }
 
+// The entry (key, inst) of a key with bitmap record rec.
+__device__ __forceinline__ Found find_holder(const DevIndex &ix, uint64_t rec, uint64_t key, uint32_t inst) {
+  const uint64_t bw = ix.pool[rec * uint64_t(ix.words) + (inst >> 6)];
+  if (!((bw >> (inst & 63)) & 1)) return Found{-1, 0};
+  return find_member(ix, key, inst);
+}
+
 __device__ Found find_entry(const DevIndex &ix, uint64_t key, uint32_t inst) {
   ChainWalk w = chain_start(home_bucket(key, ix.n_buckets), key_cls(key));
   bool had_empty;
@@ -169,11 +177,7 @@ __device__ Found find_entry(const DevIndex &ix, uint64_t key, uint32_t inst) {
       const uint64_t v = bk[SLOTS + s];
       const uint32_t kind = val_kind(v);
       if (kind == PLAIN && val_inst(v) == inst) return Found{int64_t(b * SLOTS + s), v};
-      if (kind == HEADER) {
-        const uint64_t bw = ix.pool[val_rec(v) * uint64_t(ix.words) + (inst >> 6)];
-        if (!((bw >> (inst & 63)) & 1)) return Found{-1, 0};
-        return find_member(ix, key, inst);
-      }
+      if (kind == HEADER) return find_holder(ix, val_rec(v), key, inst);
     }
     had_empty = sc.empty != 0;
   } while (chain_next(ix, w, had_empty));
@@ -366,7 +370,8 @@ struct WsHdr {
   unsigned long long n_over;   // region-ordered insert: candidates in bins too large for LDS
   int req_bad;                 // region-ordered insert: some request's target or session is invalid
   int inl;                     // region-ordered insert: refreshes done by the classify pass
-  unsigned long long pad[21];
+  unsigned long long turns;    // find pass: new pairs, workgroups that have ended, errors (ins_check_last)
+  unsigned long long pad[20];
 };
 static_assert(sizeof(WsHdr) == 256, "ws header size");
 
@@ -419,11 +424,13 @@ constexpr int BIN_CAP = 3072;               // larger bins use the fallback pair
 static_assert(INS_WG % KCH == 0 && SEG_PER_CH <= 64, "chunk = whole classify segments");
 static_assert(BIN_CAP + WG_THREADS < DT, "an LDS pair table never fills");
 
+// Workgroups of the find and apply passes: at most 2 FIND_WG.
+constexpr int FIND_WG = 256;
+
 struct InsWs {
   WsHdr *hdr;
-  uint64_t *pos;    // per block: slot + 1 of an entry to refresh, 0 = none
+  uint64_t *pos;    // per block: slot + 1 of an entry to refresh, a new pair (POS_NEW), 0 = none
   DSlot *dd;        // dedupe table (region-ordered insert: fallback pair table)
-  uint64_t *list;   // dedupe slots of distinct new pairs
   uint64_t *trig;   // keys queued for conversion
   uint64_t *def;    // list positions of deferred new pairs
   Cand *cand;       // region-ordered insert: absent pairs, one segment per workgroup,
@@ -439,7 +446,7 @@ struct InsWs {
   Cand *bcand;      // candidates in bin order
   NewPair *np;      // bin order: distinct new pairs
   uint64_t n_dedupe;
-  uint64_t list_cap;  // entries in list and trig
+  uint64_t list_cap;  // entries in trig and def
   uint64_t seg;       // segment length of the region-ordered insert
 };
 
@@ -463,7 +470,6 @@ uint64_t insert_ws_layout(int64_t n_blocks, InsWs *ws, void *base) {
   const uint64_t o_hdr = take(sizeof(WsHdr));
   const uint64_t o_pos = take(8 * n);
   const uint64_t o_dd = take(16 * nd);
-  const uint64_t o_list = take(8 * nl);
   const uint64_t o_trig = take(8 * nl);
   const uint64_t o_def = take(8 * nl);
   const uint64_t o_cand = take(sizeof(Cand) * seg_n);
@@ -482,7 +488,6 @@ uint64_t insert_ws_layout(int64_t n_blocks, InsWs *ws, void *base) {
     ws->hdr = reinterpret_cast<WsHdr *>(b + o_hdr);
     ws->pos = reinterpret_cast<uint64_t *>(b + o_pos);
     ws->dd = reinterpret_cast<DSlot *>(b + o_dd);
-    ws->list = reinterpret_cast<uint64_t *>(b + o_list);
     ws->trig = reinterpret_cast<uint64_t *>(b + o_trig);
     ws->def = reinterpret_cast<uint64_t *>(b + o_def);
     ws->cand = reinterpret_cast<Cand *>(b + o_cand);
@@ -506,16 +511,19 @@ uint64_t insert_ws_layout(int64_t n_blocks, InsWs *ws, void *base) {
 __device__ __forceinline__ void ws_error(WsHdr *h, int e) { atomicCAS(&h->err, 0, e); }
 
 // Returns the dedupe slot when this call created the entry (first sighting of the
-// pair), else -1; the caller lists created slots with one atomic per wavefront.
+// pair), -1 when it was there, -2 on an error (recorded).  TRY: compare-and-swap without a look first -- two round trips for a new
+// pair instead of four, for batches that are bound by them; where many pairs meet on a
+// slot the look keeps most of them off the atomics.
+template <bool TRY>
 __device__ int64_t dedupe_pair(const InsWs &ws, uint64_t nd, uint64_t key, uint64_t mine) {
   uint64_t h = mix64(key ^ ((mine >> 32) * 0xC2B2AE3D27D4EB4Full)) & (nd - 1);
   for (uint64_t step = 0; step < nd; ++step, h = (h + 1) & (nd - 1)) {
     DSlot *d = ws.dd + h;
-    uint64_t k = __hip_atomic_load(&d->key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t k = TRY ? KEY_EMPTY : __hip_atomic_load(&d->key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (k == KEY_EMPTY) k = atomicCAS(reinterpret_cast<unsigned long long *>(&d->key), KEY_EMPTY, key);
     if (k != KEY_EMPTY && k != key) continue;
     // this slot's key is `key`; its owner instance is decided by the second word
-    uint64_t w = __hip_atomic_load(&d->w2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t w = TRY ? 0 : __hip_atomic_load(&d->w2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     while (true) {
       if (w == 0) {
         const uint64_t prev = atomicCAS(reinterpret_cast<unsigned long long *>(&d->w2), 0ull, mine);
@@ -531,30 +539,7 @@ __device__ int64_t dedupe_pair(const InsWs &ws, uint64_t nd, uint64_t key, uint6
     }
   }
   ws_error(ws.hdr, SMETRIC_EINTERNAL);
-  return -1;
-}
-
-// Append base + j for every bit j of each lane's mask: one atomicAdd per wavefront.
-__device__ __forceinline__ void append_wave_mask(unsigned long long *counter, uint64_t *list, uint64_t cap,
-                                                 uint32_t mask, uint64_t base) {
-  const uint32_t c = __popc(mask);
-  if (!__ballot(c != 0)) return;
-  const int lane = threadIdx.x & 63;
-  uint32_t x = c;  // inclusive prefix over the wavefront
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
-  unsigned long long at = 0;
-  if (lane == 63) at = atomicAdd(counter, (unsigned long long)x);
-  at = __shfl(at, 63, 64) + (x - c);
-  while (mask) {
-    const int j = __builtin_ctz(mask);
-    mask &= mask - 1;
-    if (at < cap) list[at] = base + uint64_t(j);  // callers size the list to hold every entry
-    ++at;
-  }
+  return -2;
 }
 
 // Append `h` (when >= 0) to the list: one atomicAdd per wavefront for all its lanes.
@@ -572,8 +557,6 @@ __device__ __forceinline__ void append_wave(unsigned long long *counter, uint64_
   }
 }
 
-constexpr int IW = 1;  // waves per workgroup in per-request kernels
-
 __device__ __forceinline__ bool range_of(const int64_t *blk_off, int r, int64_t n_blocks, int64_t &b0,
                                          int64_t &nb) {
   b0 = blk_off[r];
@@ -582,115 +565,229 @@ __device__ __forceinline__ bool range_of(const int64_t *blk_off, int r, int64_t 
   return b0 >= 0 && b0 <= b1 && b1 <= n_blocks;
 }
 
-__global__ __launch_bounds__(64 * IW) void ins_probe_kernel(DevIndex ix, InsWs ws, const uint64_t *keys,
-                                                            const int64_t *blk_off, int32_t n_req,
-                                                            int64_t n_blocks, const int32_t *instance,
-                                                            const uint32_t *session, uint32_t epoch) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = blockIdx.x * IW + wave;
-  if (r >= n_req) return;
-  int64_t b0, nb;
-  if (!range_of(blk_off, r, n_blocks, b0, nb)) {
-    if (lane == 0) ws_error(ws.hdr, SMETRIC_EINVAL);
-    return;
-  }
-  if (nb == 0) return;
-  if (lane == 0) atomicAdd(&ws.hdr->n_pairs, (unsigned long long)nb);
-  const int32_t inst = instance[r];
-  const uint32_t sess = session[r];
-  if (inst < 0 || inst >= ix.n_inst || sess >= SESSION_LIMIT) {
-    if (lane == 0) ws_error(ws.hdr, SMETRIC_EINVAL);
-    return;
-  }
-  for (int64_t j0 = 0; j0 < nb; j0 += 64) {
-    const int64_t j = j0 + lane;
-    int64_t fresh = -1;
-    if (j < nb) {
-      const uint64_t key = keys[b0 + j];
-      if (key == KEY_EMPTY || key == KEY_TOMB) {
-        ws_error(ws.hdr, SMETRIC_EINVAL);
-        ws.pos[b0 + j] = 0;
-      } else {
-        const Found f = find_entry(ix, key, uint32_t(inst));
-        if (f.slot >= 0) {
-          ws.pos[b0 + j] = val_epoch(f.val) < epoch ? uint64_t(f.slot) + 1 : 0;
-        } else {
-          ws.pos[b0 + j] = 0;
-          fresh = dedupe_pair(ws, ws.n_dedupe, key, ((uint64_t(inst) + 1) << 32) | uint32_t(r));
-        }
-      }
-    }
-    append_wave(&ws.hdr->n_new, ws.list, ws.list_cap, fresh);
-  }
+// One launch clears the workspace's header and the pair table.
+__global__ __launch_bounds__(TB) void ins_clear_kernel(InsWs ws) {
+  const uint64_t stride = uint64_t(gridDim.x) * TB, t = uint64_t(blockIdx.x) * TB + threadIdx.x;
+  if (t < sizeof(WsHdr) / 8) reinterpret_cast<uint64_t *>(ws.hdr)[t] = 0;
+  for (uint64_t h = t; h < ws.n_dedupe; h += stride) ws.dd[h] = DSlot{0, 0};
 }
 
-__global__ void ins_check_kernel(DevIndex ix, InsWs ws, int64_t n_blocks) {
+// What the find pass leaves per block in pos: nothing, the slot + 1 of an entry to refresh,
+// or POS_NEW | the pair-table slot of a new pair that this block entered first.
+constexpr uint64_t POS_NEW = uint64_t(1) << 63;
+
+// Grid of the find and apply passes: one atomic per workgroup on the pass's counter (12 ns
+// each when they meet on one word), so few and large workgroups where there are many blocks.
+inline int find_threads(uint64_t threads) { return threads <= uint64_t(FIND_WG) * TB ? TB : 4 * TB; }
+inline int find_grid(uint64_t threads) {
+  const uint64_t nt = find_threads(threads), g = (threads + nt - 1) / nt;
+  return int(g < 1 ? 1 : (g > 2 * FIND_WG ? 2 * FIND_WG : g));
+}
+
+// Waits until this wavefront's memory operations have completed.
+__device__ __forceinline__ void memory_done() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+}
+
+// End of a find pass.  The last workgroup to get here makes the all-or-nothing check -- the
+// first input error, or EFULL, leaves the index unchanged -- so the check costs no launch of
+// its own: every workgroup adds, in one atomic, its turn, whether it met an error, and its
+// new pairs, and the one whose turn is the last has the totals in the returned word.  The
+// words that pass between workgroups are all accessed by atomics, and a workgroup's are
+// complete before its turn, so no cache is written back.  n_entries: as read when the kernel
+// began (nothing else changes it meanwhile).
+constexpr int TURN_SHIFT = 40, ERR_SHIFT = 52;  // 2^40 new pairs, 2^12 workgroups
+static_assert(2 * FIND_WG < (1 << 12), "turns and errors fit their fields");
+template <bool PAIRS>
+__device__ void ins_check_last(const DevIndex &ix, const InsWs &ws, int64_t n_blocks, unsigned long long n_entries,
+                               uint32_t n_new, uint64_t n_pairs, bool bad) {
+  __shared__ unsigned long long s_new, s_pairs;
+  __shared__ bool s_bad;
+  if (threadIdx.x == 0) {
+    s_new = s_pairs = 0;
+    s_bad = false;
+  }
+  memory_done();  // every wavefront's error code has reached the device's coherence point
+  __syncthreads();
+  if (n_new) atomicAdd(&s_new, (unsigned long long)n_new);
+  if (PAIRS && n_pairs) atomicAdd(&s_pairs, (unsigned long long)n_pairs);
+  if (bad) s_bad = true;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   WsHdr *h = ws.hdr;
-  int e = h->err;
-  if (e == 0 && h->n_pairs > (unsigned long long)n_blocks) e = SMETRIC_EINVAL;
-  if (e == 0 && ix.hdr->n_entries + h->n_new > ix.capacity) e = SMETRIC_EFULL;
+  if (PAIRS && s_pairs) {
+    atomicAdd(&h->n_pairs, s_pairs);
+    memory_done();
+  }
+  const unsigned long long mine = s_new + (1ull << TURN_SHIFT) + (s_bad ? 1ull << ERR_SHIFT : 0ull);
+  const unsigned long long all = atomicAdd(&h->turns, mine) + mine;
+  if (((all >> TURN_SHIFT) & ((1u << (ERR_SHIFT - TURN_SHIFT)) - 1)) != gridDim.x) return;
+  const unsigned long long total = all & ((1ull << TURN_SHIFT) - 1);
+  int e = 0;
+  if (all >> ERR_SHIFT) e = __hip_atomic_load(&h->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else if (PAIRS && __hip_atomic_load(&h->n_pairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >
+                        (unsigned long long)n_blocks)
+    e = SMETRIC_EINVAL;
+  if (e == 0 && n_entries + total > ix.capacity) e = SMETRIC_EFULL;
   if (e != 0) {
     h->abort = 1;
     set_status(ix.hdr, e);
   } else {
-    ix.hdr->n_entries += h->n_new;
+    ix.hdr->n_entries = n_entries + total;
   }
 }
 
-__global__ __launch_bounds__(64 * IW) void ins_refresh_kernel(DevIndex ix, InsWs ws, const int64_t *blk_off,
-                                                              int32_t n_req, int64_t n_blocks,
-                                                              uint32_t epoch) {
-  if (ws.hdr->abort) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = blockIdx.x * IW + wave;
-  if (r >= n_req) return;
-  int64_t b0, nb;
-  if (!range_of(blk_off, r, n_blocks, b0, nb)) return;
-  for (int64_t j = lane; j < nb; j += 64) {
-    const uint64_t p = ws.pos[b0 + j];
-    if (!p) continue;
-    uint64_t *vp = val_ptr(ix, int64_t(p - 1));
-    const uint64_t v = *vp;
-    if (val_epoch(v) < epoch) *vp = val_raise_epoch(v, epoch);
-  }
-}
-
-__global__ void ins_place_kernel(DevIndex ix, InsWs ws, const uint32_t *session, uint32_t epoch) {
-  if (ws.hdr->abort) return;
-  const uint64_t n = ws.hdr->n_new;
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  const uint64_t first = uint64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63u);
-  for (uint64_t i0 = first; i0 < n; i0 += stride) {  // whole wavefronts iterate together
-    const uint64_t i = i0 + (threadIdx.x & 63);
-    int64_t tk = -1, df = -1;
-    bool rf = false;
-    if (i < n) {
-      const DSlot d = ws.dd[ws.list[i]];
-      bool trig;
-      const int pl = place_new(ix, d.key, dd_inst(d.w2), epoch, session[dd_req(d.w2)], trig, true);
-      if (pl == FAILED) set_status(ix.hdr, SMETRIC_EINTERNAL);
-      else if (pl == DEFERRED) df = int64_t(i);
-      else if (pl == REFRESHED) rf = true;
-      else if (trig) tk = int64_t(i);
+// Find and dedupe, self-contained: groups of `per` threads (a wavefront or TB threads) take
+// requests, their threads blocks.
+template <int NT>
+__global__ __launch_bounds__(NT) void ins_probe_kernel(DevIndex ix, InsWs ws, const uint64_t *keys,
+                                                       const int64_t *blk_off, int32_t n_req, int64_t n_blocks,
+                                                       const int32_t *instance, const uint32_t *session,
+                                                       uint32_t epoch, int per) {
+  const int gt = threadIdx.x % per, groups = NT / per;
+  const unsigned long long n_entries = ix.hdr->n_entries;
+  uint64_t pairs = 0;
+  uint32_t n_new = 0;
+  bool bad = false;
+  for (int64_t r = int64_t(blockIdx.x) * groups + threadIdx.x / per; r < n_req; r += int64_t(gridDim.x) * groups) {
+    int64_t b0, nb;
+    if (!range_of(blk_off, int(r), n_blocks, b0, nb)) {
+      bad = true;
+      continue;
     }
-    uncount_refreshed(ix, rf);
-    append_wave(&ws.hdr->n_trig, ws.trig, ws.list_cap, tk);  // queue by list index
-    append_wave(&ws.hdr->n_def, ws.def, ws.list_cap, df);
+    if (nb == 0) continue;
+    if (gt == 0) pairs += uint64_t(nb);
+    const int32_t inst = instance[r];
+    const uint32_t sess = session[r];
+    if (inst < 0 || inst >= ix.n_inst || sess >= SESSION_LIMIT) {
+      bad = true;
+      continue;
+    }
+    for (int64_t j = gt; j < nb; j += per) {
+      const uint64_t key = keys[b0 + j];
+      uint64_t at = 0;
+      if (key == KEY_EMPTY || key == KEY_TOMB) {
+        bad = true;
+      } else {
+        const Found f = find_entry(ix, key, uint32_t(inst));
+        if (f.slot >= 0) {
+          at = val_epoch(f.val) < epoch ? uint64_t(f.slot) + 1 : 0;
+        } else {
+          const int64_t h = dedupe_pair<false>(ws, ws.n_dedupe, key, ((uint64_t(inst) + 1) << 32) | uint32_t(r));
+          at = h >= 0 ? POS_NEW | uint64_t(h) : 0;
+          n_new += h >= 0;
+          bad |= h == -2;
+        }
+      }
+      ws.pos[b0 + j] = at;
+    }
+  }
+  if (bad) ws_error(ws.hdr, SMETRIC_EINVAL);
+  ins_check_last<true>(ix, ws, n_blocks, n_entries, n_new, pairs, bad);
+}
+
+// The same from the direct form of a probe state: threads take blocks, and the descriptor
+// answers for blocks of no or one holder.
+template <int NT>
+__global__ __launch_bounds__(NT) void insd_find_kernel(DevIndex ix, ProbeView pv, InsWs ws, int64_t n_blocks,
+                                                       const int32_t *instance, const uint32_t *session,
+                                                       uint32_t epoch) {
+  const unsigned long long n_entries = ix.hdr->n_entries;
+  bool bad = pv.hdr->err != 0;
+  const int64_t n = bad ? 0 : n_blocks;
+  uint32_t n_new = 0;
+  for (int64_t p = int64_t(blockIdx.x) * NT + threadIdx.x; p < n; p += int64_t(gridDim.x) * NT) {
+    const uint64_t key = pv.part_key[p], d = pv.desc_p[p];
+    const uint32_t r = pv.part_req[p];
+    const int32_t inst = instance[r];
+    uint64_t at = 0;
+    if (inst < 0 || inst >= ix.n_inst || session[r] >= SESSION_LIMIT || key == KEY_EMPTY || key == KEY_TOMB) {
+      bad = true;
+    } else {
+      const uint32_t kind = desc_kind(d);
+      int64_t slot = -1;
+      bool raise = true;
+      if (kind == D_ONE) {
+        if (desc_inst(d) == uint32_t(inst)) slot = int64_t(desc_x(d));
+      } else if (kind == D_HOT || kind == D_MANY) {
+        const Found f = kind == D_HOT ? find_holder(ix, desc_x(d), key, uint32_t(inst)) : find_entry(ix, key, uint32_t(inst));
+        slot = f.slot;
+        raise = val_epoch(f.val) < epoch;
+      }
+      if (slot >= 0) {
+        at = raise ? uint64_t(slot) + 1 : 0;
+      } else {
+        const int64_t h = dedupe_pair<true>(ws, ws.n_dedupe, key, ((uint64_t(inst) + 1) << 32) | r);
+        at = h >= 0 ? POS_NEW | uint64_t(h) : 0;
+        n_new += h >= 0;
+        bad |= h == -2;
+      }
+    }
+    ws.pos[p] = at;
+  }
+  if (bad) ws_error(ws.hdr, SMETRIC_EINVAL);
+  ins_check_last<false>(ix, ws, n_blocks, n_entries, n_new, 0, bad);
+}
+
+// What the find pass left for one block.  A refreshed entry's value is read first, so an
+// entry that many requests share is raised by few of them; new pairs claim EMPTY slots
+// only, so the two never touch one value except an entry that both raise to one epoch.
+__device__ __forceinline__ void apply_pos(const DevIndex &ix, const InsWs &ws, uint64_t at, const uint32_t *session,
+                                          uint32_t epoch) {
+  int64_t tk = -1, df = -1;
+  bool rf = false;
+  if (at & POS_NEW) {
+    const int64_t h = int64_t(at & ~POS_NEW);
+    const DSlot d = ws.dd[h];
+    bool trig;
+    const int pl = place_new(ix, d.key, dd_inst(d.w2), epoch, session[dd_req(d.w2)], trig, true);
+    if (pl == FAILED) set_status(ix.hdr, SMETRIC_EINTERNAL);
+    else if (pl == DEFERRED) df = h;
+    else if (pl == REFRESHED) rf = true;  // a block past its probe bound that was an entry
+    else if (trig) tk = h;
+  } else if (at) {
+    uint64_t *vp = val_ptr(ix, int64_t(at - 1));
+    const uint64_t v = *vp;
+    if (val_epoch(v) < epoch) raise_epoch_at(vp, val_kind(v), val_inst(v), epoch);
+  }
+  uncount_refreshed(ix, rf);
+  append_wave(&ws.hdr->n_trig, ws.trig, ws.list_cap, tk);  // by pair-table slot
+  append_wave(&ws.hdr->n_def, ws.def, ws.list_cap, df);
+}
+
+// Apply; blk_off null: the blocks of a direct probe state, else those of every request.
+template <int NT>
+__global__ __launch_bounds__(NT) void ins_apply_kernel(DevIndex ix, InsWs ws, const int64_t *blk_off, int32_t n_req,
+                                                       int64_t n_blocks, const uint32_t *session, uint32_t epoch,
+                                                       int per) {
+  if (ws.hdr->abort) return;
+  const int lane = threadIdx.x & 63;
+  if (blk_off) {
+    const int groups = NT / per;
+    for (int64_t r = int64_t(blockIdx.x) * groups + threadIdx.x / per; r < n_req; r += int64_t(gridDim.x) * groups) {
+      int64_t b0, nb;
+      if (!range_of(blk_off, int(r), n_blocks, b0, nb)) continue;
+      for (int64_t j0 = (threadIdx.x % per) & ~63; j0 < nb; j0 += per)  // whole wavefronts iterate together
+        apply_pos(ix, ws, j0 + lane < nb ? ws.pos[b0 + j0 + lane] : 0, session, epoch);
+    }
+  } else {
+    for (int64_t p0 = int64_t(blockIdx.x) * NT + (threadIdx.x & ~63); p0 < n_blocks; p0 += int64_t(gridDim.x) * NT)
+      apply_pos(ix, ws, p0 + lane < n_blocks ? ws.pos[p0 + lane] : 0, session, epoch);
   }
 }
 
 // Convert the queued keys.  trig holds indexes: key = np[idx].key when `np` is given
-// (region-ordered insert: new-pair positions), dd[via[idx]].key when `dd` is (insert:
-// positions in the dedupe list), else keys[idx] (rebuild).
+// (region-ordered insert: new-pair positions), dd[idx].key when `dd` is (insert: pair-table
+// slots), else keys[idx] (rebuild).
 __global__ void spill_kernel(DevIndex ix, const uint64_t *trig, const unsigned long long *n_trig,
-                             const int *abort_flag, const uint64_t *keys, const DSlot *dd, const uint64_t *via,
-                             const NewPair *np) {
+                             const int *abort_flag, const uint64_t *keys, const DSlot *dd, const NewPair *np) {
   if (abort_flag && *abort_flag) return;
   const uint64_t n = *n_trig;
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
     const uint64_t t = trig[i];
-    const uint64_t key = np ? np[t].key : (dd ? dd[via[t]].key : keys[t]);
+    const uint64_t key = np ? np[t].key : (dd ? dd[t].key : keys[t]);
     if (!spill_key(ix, key)) set_status(ix.hdr, SMETRIC_EINTERNAL);
   }
 }
@@ -1056,12 +1153,6 @@ __global__ void insp_size2_kernel(InsWs ws) {
   for (uint64_t h = t0; h < nd; h += stride) ws.dd[h] = DSlot{0, 0};
 }
 
-__global__ void dd_clear_kernel(DSlot *dd, uint64_t n, const unsigned long long *n_dev) {
-  const uint64_t nd = n_dev ? *n_dev : n;
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t h = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; h < nd; h += stride) dd[h] = DSlot{0, 0};
-}
-
 // Scatter pass: workgroup (g, c) moves its chunk into bin order one tile at a time (LDS
 // ranks per bin, the tile regrouped by bin in LDS, each bin's part written as one run
 // after the previous tile's).
@@ -1202,7 +1293,7 @@ __global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(InsWs ws) {
       uint32_t mine = 0;
       for (uint32_t k = lo + t; k < hi; k += DD_T) {
         const Cand e = ws.bcand[k];
-        const int64_t h = dedupe_pair(ws, nd2, e.key, e.w2);
+        const int64_t h = dedupe_pair<false>(ws, nd2, e.key, e.w2);
         ws.np[k] = h >= 0 ? NewPair{e.key, NP_FALLBACK | uint64_t(h)} : NewPair{KEY_EMPTY, 0};
         mine += h >= 0;
       }
@@ -1314,6 +1405,242 @@ __global__ __launch_bounds__(TB) void insp_place_kernel(DevIndex ix, ProbeView p
     append_wave(&ws.hdr->n_def, ws.def, ws.list_cap, df);
   }
   if (!ws.hdr->inl) refresh_pass(ix, pv, ws, epoch);
+}
+
+// ---------------------------------------------------------------------------------
+// Insert of a small batch: one launch, one workgroup
+// ---------------------------------------------------------------------------------
+// A batch of at most SI_MAX blocks is bound by launches and by one round trip to memory
+// after another, not by bandwidth: the stages of the general insert (8 launches, 13 from a
+// probe state) each find a few thousand pairs at most.  Here one workgroup takes them
+// all, SI_U pairs per thread, with barriers between the stages: find every pair (from the
+// descriptor where the batch was probed), dedupe the absent ones in an LDS table of pair
+// numbers, check, then refresh and place.  Pairs are numbered in request order (plain) or
+// carry their request (probed), so a repeated pair keeps its lowest request.  A thread
+// converts the keys whose (T+1)-th plain slot it claimed and enters the pairs it had to
+// defer, after a barrier each.
+// One agent's requests (64 to 350 blocks each): 26 us of kernels in 8 launches -> 9.3 us in
+// one.  At 4,096 new pairs it takes 29 us, what the five launches of the next size up take.
+constexpr int SI_T = 1024;
+constexpr int SI_U = 4;
+constexpr int SI_MAX = SI_T * SI_U;
+constexpr int SI_TAB = 2 * SI_MAX;  // never more than half full
+constexpr uint32_t SI_FREE = 0xFFFFFFFFu;
+
+template <bool PROBED>
+__global__ __launch_bounds__(SI_T) void ins_small_kernel(DevIndex ix, ProbeView pv, const uint64_t *keys,
+                                                         const int64_t *blk_off, int32_t n_req, int64_t n_blocks,
+                                                         const int32_t *instance, const uint32_t *session,
+                                                         uint32_t epoch) {
+  __shared__ uint64_t skey[SI_MAX];
+  __shared__ uint32_t tab[SI_TAB];  // pair numbers
+  __shared__ uint32_t sreq[SI_MAX];
+  __shared__ uint16_t sinst[SI_MAX];
+  __shared__ uint32_t pre[PROBED ? 1 : SI_T + 1];
+  __shared__ uint32_t wt[SI_T / 64];
+  __shared__ int bad_range, err;
+  __shared__ unsigned int n_new, n_trig, n_def;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t == 0) {
+    bad_range = err = 0;
+    n_new = n_trig = n_def = 0;
+  }
+  for (int h = t; h < SI_TAB; h += SI_T) tab[h] = SI_FREE;
+  __syncthreads();
+  uint32_t n;
+  if constexpr (PROBED) {
+    n = uint32_t(pv.hdr->n < uint64_t(n_blocks) ? pv.hdr->n : uint64_t(n_blocks));
+    if (t == 0 && pv.hdr->err) bad_range = 1;
+  } else {
+    // the pairs of request r are numbered from pre[r]
+    int64_t b0 = 0, nb = 0;
+    if (t < n_req && !range_of(blk_off, t, n_blocks, b0, nb)) {
+      bad_range = 1;
+      nb = 0;
+    }
+    uint32_t x = uint32_t(nb);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(x, d, 64);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) wt[wave] = x;
+    __syncthreads();
+    uint32_t before = 0;
+    n = 0;
+#pragma unroll
+    for (int w = 0; w < SI_T / 64; ++w) {
+      before += w < wave ? wt[w] : 0;
+      n += wt[w];  // at most SI_T ranges of at most SI_MAX blocks
+    }
+    pre[t + 1] = before + x;
+    if (t == 0) {
+      pre[0] = 0;
+      if (n > uint64_t(n_blocks)) bad_range = 1;
+    }
+  }
+  __syncthreads();
+  if (bad_range) {
+    if (t == 0) set_status(ix.hdr, SMETRIC_EINVAL);
+    return;
+  }
+  uint64_t key[SI_U], d[SI_U];
+  uint32_t r[SI_U], sess[SI_U];
+  int32_t inst[SI_U];
+#pragma unroll
+  for (int u = 0; u < SI_U; ++u) {
+    const uint32_t p = u * SI_T + t;
+    key[u] = KEY_EMPTY;
+    d[u] = 0;
+    r[u] = 0;
+    if (p < n) {
+      if constexpr (PROBED) {
+        key[u] = pv.part_key[p];
+        r[u] = pv.part_req[p];
+        d[u] = pv.desc_p[p];
+      } else {
+        uint32_t lo = 0, hi = uint32_t(n_req);  // pre[lo] <= p < pre[hi]
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (pre[mid] <= p) lo = mid;
+          else hi = mid;
+        }
+        r[u] = lo;
+        key[u] = keys[blk_off[lo] + (p - pre[lo])];
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < SI_U; ++u) {
+    const bool in = uint32_t(u * SI_T + t) < n;
+    inst[u] = in ? instance[r[u]] : 0;
+    sess[u] = in ? session[r[u]] : 0;
+  }
+  // find: the slot of an existing pair, and whether its epoch is known to need no raise
+  int64_t slot[SI_U];
+  uint32_t kind[SI_U];
+  bool absent[SI_U], fresh[SI_U];
+#pragma unroll
+  for (int u = 0; u < SI_U; ++u) {
+    const uint32_t p = u * SI_T + t;
+    slot[u] = -1;
+    kind[u] = PLAIN;
+    absent[u] = fresh[u] = false;
+    if (p >= n) continue;
+    skey[p] = key[u];
+    sreq[p] = r[u];
+    sinst[p] = uint16_t(inst[u]);
+    if (inst[u] < 0 || inst[u] >= ix.n_inst || sess[u] >= SESSION_LIMIT || key[u] == KEY_EMPTY || key[u] == KEY_TOMB) {
+      err = SMETRIC_EINVAL;
+      continue;
+    }
+    const uint32_t dk = PROBED ? desc_kind(d[u]) : uint32_t(D_MANY);
+    if (dk == D_ONE) {
+      if (desc_inst(d[u]) == uint32_t(inst[u])) slot[u] = int64_t(desc_x(d[u]));
+    } else if (dk == D_HOT || dk == D_MANY) {
+      const Found f = dk == D_HOT ? find_holder(ix, desc_x(d[u]), key[u], uint32_t(inst[u]))
+                                  : find_entry(ix, key[u], uint32_t(inst[u]));
+      slot[u] = f.slot;
+      if (f.slot >= 0) {
+        kind[u] = val_kind(f.val);
+        fresh[u] = val_epoch(f.val) >= epoch;
+      }
+    }
+    absent[u] = slot[u] < 0;
+  }
+  __syncthreads();
+  if (err) {
+    if (t == 0) set_status(ix.hdr, err);
+    return;
+  }
+  // dedupe: a slot of the table ends with the number of its pair that has the lowest request
+  uint32_t own[SI_U];
+#pragma unroll
+  for (int u = 0; u < SI_U; ++u) {
+    const uint32_t p = u * SI_T + t;
+    own[u] = 0;
+    if (!absent[u]) continue;
+    uint32_t h = uint32_t(mix64(key[u] ^ ((uint64_t(inst[u]) + 1) * 0xC2B2AE3D27D4EB4Full))) & (SI_TAB - 1);
+    while (true) {
+      uint32_t cur = atomicCAS(&tab[h], SI_FREE, p);
+      if (cur == SI_FREE) break;
+      if (skey[cur] == key[u] && sinst[cur] == uint16_t(inst[u])) {
+        // the same pair (whichever of its numbers the slot holds by now): the lower request stays
+        while (sreq[cur] > r[u] || (sreq[cur] == r[u] && cur > p)) {
+          const uint32_t was = atomicCAS(&tab[h], cur, p);
+          if (was == cur) break;
+          cur = was;
+        }
+        break;
+      }
+      h = (h + 1) & (SI_TAB - 1);
+    }
+    own[u] = h;
+  }
+  __syncthreads();
+  uint32_t mine = 0;
+#pragma unroll
+  for (int u = 0; u < SI_U; ++u) {
+    absent[u] = absent[u] && tab[own[u]] == uint32_t(u * SI_T + t);
+    mine += absent[u];
+  }
+  if (mine) atomicAdd(&n_new, mine);
+  __syncthreads();
+  if (t == 0) {
+    if (ix.hdr->n_entries + n_new > ix.capacity) {
+      err = SMETRIC_EFULL;
+      set_status(ix.hdr, SMETRIC_EFULL);
+    } else if (n_new) {
+      atomicAdd(&ix.hdr->n_entries, (unsigned long long)n_new);
+    }
+  }
+  __syncthreads();
+  if (err) return;
+  uint32_t trig = 0, def = 0;  // bit u: pair u converts its key, was deferred
+#pragma unroll
+  for (int u = 0; u < SI_U; ++u) {
+    bool rf = false;
+    if (slot[u] >= 0) {
+      if (!fresh[u]) raise_epoch_at(val_ptr(ix, slot[u]), kind[u], uint32_t(inst[u]), epoch);
+    } else if (absent[u]) {
+      bool tr;
+      const int pl = place_new(ix, key[u], uint32_t(inst[u]), epoch, sess[u], tr, true);
+      if (pl == FAILED) set_status(ix.hdr, SMETRIC_EINTERNAL);
+      else if (pl == DEFERRED) def |= 1u << u;
+      else if (pl == REFRESHED) rf = true;  // a block past its probe bound that was an entry
+      else if (tr) trig |= 1u << u;
+    }
+    uncount_refreshed(ix, rf);
+  }
+  if (trig) n_trig = 1;
+  if (def) n_def = 1;
+  __syncthreads();
+  if (n_trig) {  // every claim and value above is visible before a conversion reads the chain
+    __threadfence();
+    while (trig) {
+      const int u = __builtin_ctz(trig);
+      trig &= trig - 1;
+      if (!spill_key(ix, skey[u * SI_T + t])) set_status(ix.hdr, SMETRIC_EINTERNAL);
+    }
+    __threadfence();
+    __syncthreads();
+  }
+  if (n_def) {
+    __threadfence();
+    while (__ballot(def != 0)) {
+      bool rf = false;
+      if (def) {
+        const int u = __builtin_ctz(def);
+        def &= def - 1;
+        const uint32_t p = u * SI_T + t;
+        bool tr;
+        const int pl = place_new(ix, skey[p], sinst[p], epoch, session[sreq[p]], tr, false);
+        rf = pl == REFRESHED;
+        if (pl != PLACED && pl != REFRESHED) set_status(ix.hdr, SMETRIC_EINTERNAL);
+      }
+      uncount_refreshed(ix, rf);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -1661,9 +1988,8 @@ __global__ __launch_bounds__(TB) void rebuild_tile_kernel(DevIndex ix, const uin
 // as further plain slots).  Items index `keys` (and `vals`) directly, or through
 // `via` into the dedupe table `dd` (insert: session of the lowest request).
 __global__ void deferred_kernel(DevIndex ix, const uint64_t *items, const unsigned long long *n_items,
-                                const int *abort_flag, const uint64_t *via, const DSlot *dd,
-                                const uint32_t *session, uint32_t epoch, const uint64_t *keys,
-                                const uint64_t *vals, const NewPair *np) {
+                                const int *abort_flag, const DSlot *dd, const uint32_t *session, uint32_t epoch,
+                                const uint64_t *keys, const uint64_t *vals, const NewPair *np) {
   if (abort_flag && *abort_flag) return;
   const uint64_t n = *n_items;
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
@@ -1675,14 +2001,14 @@ __global__ void deferred_kernel(DevIndex ix, const uint64_t *items, const unsign
       const NewPair e = np[t];
       const uint64_t w2 = np_w2(e, dd);
       pl = place_new(ix, e.key, dd_inst(w2), epoch, session[dd_req(w2)], trig, false);
-    } else if (via) {
-      const DSlot d = dd[via[t]];
+    } else if (dd) {
+      const DSlot d = dd[t];
       pl = place_new(ix, d.key, dd_inst(d.w2), epoch, session[dd_req(d.w2)], trig, false);
     } else {
       const uint64_t v = vals[t];
       pl = place_new(ix, keys[t], dump_inst(v), dump_epoch(v), dump_session(v), trig, false);
     }
-    if (pl == REFRESHED && !np && !via) pl = FAILED;  // rebuild survivors are distinct
+    if (pl == REFRESHED && !np && !dd) pl = FAILED;  // rebuild survivors are distinct
     if (pl != PLACED && pl != REFRESHED) set_status(ix.hdr, SMETRIC_EINTERNAL);
     uncount_refreshed(ix, pl == REFRESHED);
   }
@@ -1808,6 +2134,16 @@ int read_hdr(const smetric_index *idx, IndexHdr *out, hipStream_t s) {
   return hip_rc(hipStreamSynchronize(s));
 }
 
+// The last two passes of an insert that lists its new pairs in the pair table: conversions,
+// then the pairs deferred until theirs.
+int ins_convert(const DevIndex &ix, const InsWs &ws, const uint32_t *session, uint32_t epoch, hipStream_t stream) {
+  hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, ws.trig, &ws.hdr->n_trig, &ws.hdr->abort,
+                     nullptr, ws.dd, nullptr);
+  hipLaunchKernelGGL(deferred_kernel, dim3(64), dim3(TB), 0, stream, ix, ws.def, &ws.hdr->n_def, &ws.hdr->abort,
+                     ws.dd, session, epoch, nullptr, nullptr, nullptr);
+  return hip_rc(hipGetLastError());
+}
+
 // Gather all entries and sort them by (key, instance) for the dump.  Stable LSD radix
 // passes, each over the full 64-bit sort word (restricting a pass to a bit range gave
 // wrong orders for some inputs with the installed rocPRIM):
@@ -1905,21 +2241,21 @@ extern "C" int smetric_index_insert(smetric_index *idx, const uint64_t *keys, co
   InsWs ws;
   insert_ws_layout(n_blocks, &ws, workspace);
   const DevIndex ix = dev_view(idx);
-  int rc;
-  if ((rc = fill(ws.hdr, sizeof(WsHdr), 0, stream))) return rc;
-  hipLaunchKernelGGL(dd_clear_kernel, dim3(grid_for(ws.n_dedupe)), dim3(TB), 0, stream, ws.dd, ws.n_dedupe,
-                     nullptr);
-  const dim3 rgrid((n_req + IW - 1) / IW), rblock(64 * IW);
-  hipLaunchKernelGGL(ins_probe_kernel, rgrid, rblock, 0, stream, ix, ws, keys, blk_off, n_req, n_blocks, instance,
-                     session, epoch);
-  hipLaunchKernelGGL(ins_check_kernel, dim3(1), dim3(1), 0, stream, ix, ws, n_blocks);
-  hipLaunchKernelGGL(ins_refresh_kernel, rgrid, rblock, 0, stream, ix, ws, blk_off, n_req, n_blocks, epoch);
-  hipLaunchKernelGGL(ins_place_kernel, dim3(grid_for(uint64_t(n_blocks))), dim3(TB), 0, stream, ix, ws, session, epoch);
-  hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, ws.trig, &ws.hdr->n_trig, &ws.hdr->abort,
-                     nullptr, ws.dd, ws.list, nullptr);
-  hipLaunchKernelGGL(deferred_kernel, dim3(64), dim3(TB), 0, stream, ix, ws.def, &ws.hdr->n_def, &ws.hdr->abort,
-                     ws.list, ws.dd, session, epoch, nullptr, nullptr, nullptr);
-  return hip_rc(hipGetLastError());
+  if (n_blocks <= SI_MAX && n_req <= SI_T) {
+    hipLaunchKernelGGL(ins_small_kernel<false>, dim3(1), dim3(SI_T), 0, stream, ix, ProbeView{}, keys, blk_off, n_req,
+                       n_blocks, instance, session, epoch);
+    return hip_rc(hipGetLastError());
+  }
+  hipLaunchKernelGGL(ins_clear_kernel, dim3(grid_for(ws.n_dedupe)), dim3(TB), 0, stream, ws);
+  const int per = n_blocks / n_req > 64 ? TB : 64;
+  const uint64_t threads = uint64_t(n_req) * per;
+  const int nt = find_threads(threads);
+  const dim3 grid(find_grid(threads)), blk(nt);
+  hipLaunchKernelGGL((nt == TB ? ins_probe_kernel<TB> : ins_probe_kernel<4 * TB>), grid, blk, 0, stream, ix, ws, keys,
+                     blk_off, n_req, n_blocks, instance, session, epoch, per);
+  hipLaunchKernelGGL((nt == TB ? ins_apply_kernel<TB> : ins_apply_kernel<4 * TB>), grid, blk, 0, stream, ix, ws, blk_off,
+                     n_req, n_blocks, session, epoch, per);
+  return ins_convert(ix, ws, session, epoch, stream);
 }
 
 extern "C" int smetric_index_evict_ws_bytes(const smetric_index *idx, uint64_t *ws_bytes) {
@@ -2046,11 +2382,10 @@ extern "C" int smetric_index_evict(smetric_index *idx, uint32_t frac_num, uint32
   unsigned long long *n_def = ws.count + 2;
   hipLaunchKernelGGL(rebuild_claim_kernel, dim3(n_tiles < MAX_GRID ? n_tiles : MAX_GRID), dim3(TB), 0, stream, ix,
                      keys, vals, left_list, ws.toff, n_tiles, trig, n_trig, def, n_def, idx->capacity);
-  hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, trig, n_trig, nullptr, keys, nullptr, nullptr,
-                     nullptr);
+  hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, trig, n_trig, nullptr, keys, nullptr, nullptr);
   // every member of a key with a bitmap record is deferred here (millions): the full grid
   hipLaunchKernelGGL(deferred_kernel, dim3(MAX_GRID), dim3(TB), 0, stream, ix, def, n_def, nullptr, nullptr, nullptr,
-                     nullptr, 0u, keys, vals, nullptr);
+                     0u, keys, vals, nullptr);
   if ((rc = hip_rc(hipGetLastError()))) return rc;
   return hip_rc(hipStreamSynchronize(stream));
 }
@@ -2098,6 +2433,21 @@ extern "C" int smetric_index_insert_probed(smetric_index *idx, const void *probe
   InsWs ws;
   insert_ws_layout(n_blocks, &ws, workspace);
   const DevIndex ix = dev_view(idx);
+  if (n_blocks <= SI_MAX) {
+    hipLaunchKernelGGL(ins_small_kernel<true>, dim3(1), dim3(SI_T), 0, stream, ix, pv, nullptr, nullptr, n_req, n_blocks,
+                       instance, session, epoch);
+    return hip_rc(hipGetLastError());
+  }
+  if (direct_batch(uint64_t(n_blocks))) {
+    hipLaunchKernelGGL(ins_clear_kernel, dim3(grid_for(ws.n_dedupe)), dim3(TB), 0, stream, ws);
+    const int nt = find_threads(uint64_t(n_blocks));
+    const dim3 grid(find_grid(uint64_t(n_blocks))), blk(nt);
+    hipLaunchKernelGGL((nt == TB ? insd_find_kernel<TB> : insd_find_kernel<4 * TB>), grid, blk, 0, stream, ix, pv, ws,
+                       n_blocks, instance, session, epoch);
+    hipLaunchKernelGGL((nt == TB ? ins_apply_kernel<TB> : ins_apply_kernel<4 * TB>), grid, blk, 0, stream, ix, ws, nullptr,
+                       n_req, n_blocks, session, epoch, TB);
+    return ins_convert(ix, ws, session, epoch, stream);
+  }
   int rc;
   if ((rc = fill(ws.hdr, sizeof(WsHdr), 0, stream))) return rc;
   const dim3 flat(FLAT_WG), blk(TB);
@@ -2114,8 +2464,8 @@ extern "C" int smetric_index_insert_probed(smetric_index *idx, const void *probe
   hipLaunchKernelGGL(insp_check_kernel, dim3(1), blk, 0, stream, ix, ws);
   hipLaunchKernelGGL(insp_place_kernel, dim3(PLACE_WG), blk, 0, stream, ix, pv, ws, session, epoch);
   hipLaunchKernelGGL(spill_kernel, dim3(64), blk, 0, stream, ix, ws.trig, &ws.hdr->n_trig, &ws.hdr->abort,
-                     nullptr, nullptr, nullptr, ws.np);
+                     nullptr, nullptr, ws.np);
   hipLaunchKernelGGL(deferred_kernel, dim3(64), blk, 0, stream, ix, ws.def, &ws.hdr->n_def, &ws.hdr->abort,
-                     nullptr, ws.dd, session, epoch, nullptr, nullptr, ws.np);
+                     ws.dd, session, epoch, nullptr, nullptr, ws.np);
   return hip_rc(hipGetLastError());
 }

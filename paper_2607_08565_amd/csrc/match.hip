@@ -216,9 +216,11 @@ __device__ __forceinline__ Holders decode(const DevIndex &ix, uint64_t d, uint64
   return H;
 }
 
-// DESC = false: probe each block's chain here (early exit after the first all-miss
-// chunk).  DESC = true: read the descriptors written by the region-ordered probe.
-template <int WPL, bool DESC>
+// S_WALK: probe each block's chain here (early exit after the first all-miss chunk).
+// S_REGION: read the descriptors written by the region-ordered probe, through the blocks'
+// positions; S_DIRECT: those of the direct form, in block order.
+enum MatchSrc { S_WALK = 0, S_REGION = 1, S_DIRECT = 2 };
+template <int WPL, int SRC>
 __global__ __launch_bounds__(64 * MW) void match_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
                                                         const int64_t *__restrict__ blk_off,
                                                         int32_t n_req, int64_t n_blocks,
@@ -226,6 +228,7 @@ __global__ __launch_bounds__(64 * MW) void match_kernel(DevIndex ix, const uint6
                                                         const uint64_t *__restrict__ desc,
                                                         const uint32_t *__restrict__ inv,
                                                         const ProbeHdr *__restrict__ ph) {
+  constexpr bool DESC = SRC != S_WALK;
   __shared__ int32_t nlist[MW][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = blockIdx.x * MW + wave;
@@ -267,9 +270,12 @@ __global__ __launch_bounds__(64 * MW) void match_kernel(DevIndex ix, const uint6
     if (DESC && left == 0) {
       // indexes clamped to the request's last block, so that the loads need no branches
       // (a branch around a load makes the compiler wait for it on the spot)
-      uint32_t at[PF];
+      uint64_t at[PF];
 #pragma unroll
-      for (int k = 0; k < PF; ++k) at[k] = inv[b0 + (j + 64 * k < nb ? j + 64 * k : nb - 1)];
+      for (int k = 0; k < PF; ++k) {
+        at[k] = uint64_t(b0 + (j + 64 * k < nb ? j + 64 * k : nb - 1));
+        if (SRC == S_REGION) at[k] = inv[at[k]];
+      }
 #pragma unroll
       for (int k = 0; k < PF; ++k) dq[k] = desc[at[k]];
 #pragma unroll
@@ -548,7 +554,7 @@ __global__ __launch_bounds__(64 * MW) void match_kernel(DevIndex ix, const uint6
   }
 }
 
-template <bool DESC>
+template <int DESC>
 int launch_match(const smetric_index *idx, const uint64_t *keys, const int64_t *blk_off, int32_t n_req,
                  int64_t n_blocks, int32_t *matched, const uint64_t *desc, const uint32_t *inv, const ProbeHdr *ph,
                  hipStream_t stream) {
@@ -578,7 +584,7 @@ extern "C" int smetric_match(const smetric_index *idx, const uint64_t *keys, con
   if (!idx || n_req < 0 || n_blocks < 0) return SMETRIC_EINVAL;
   if (n_req == 0) return SMETRIC_OK;
   if (!blk_off || !matched || (n_blocks > 0 && !keys) || !idx->slots) return SMETRIC_EINVAL;
-  return launch_match<false>(idx, keys, blk_off, n_req, n_blocks, matched, nullptr, nullptr, nullptr, stream);
+  return launch_match<S_WALK>(idx, keys, blk_off, n_req, n_blocks, matched, nullptr, nullptr, nullptr, stream);
 }
 
 extern "C" int smetric_match_probed(const smetric_index *idx, const void *probe, uint64_t probe_bytes,
@@ -591,5 +597,7 @@ extern "C" int smetric_match_probed(const smetric_index *idx, const void *probe,
     return SMETRIC_EWORKSPACE;
   ProbeView pv;
   probe_layout(n_blocks, &pv, const_cast<void *>(probe));
-  return launch_match<true>(idx, keys, blk_off, n_req, n_blocks, matched, pv.desc_p, pv.inv, pv.hdr, stream);
+  if (direct_batch(uint64_t(n_blocks)))
+    return launch_match<S_DIRECT>(idx, keys, blk_off, n_req, n_blocks, matched, pv.desc_p, pv.inv, pv.hdr, stream);
+  return launch_match<S_REGION>(idx, keys, blk_off, n_req, n_blocks, matched, pv.desc_p, pv.inv, pv.hdr, stream);
 }

@@ -520,6 +520,99 @@ __global__ __launch_bounds__(TB) void probe_kernel(DevIndex ix, ProbeView pv) {
   }
 }
 
+// ---------------------------------------------------------------------------------
+// Direct form: batches of at most DIRECT_MAX blocks
+// ---------------------------------------------------------------------------------
+// The state from given keys: one workgroup per request.
+__global__ __launch_bounds__(TB) void direct_partition_kernel(ProbeView pv, const uint64_t *__restrict__ keys,
+                                                              const int64_t *__restrict__ blk_off, int32_t n_req,
+                                                              int64_t n_blocks) {
+  const int32_t r = blockIdx.x;
+  int64_t b0, nb;
+  const bool ok = request_tiles(blk_off, r, n_req, n_blocks, b0, nb);
+  if (threadIdx.x == 0) direct_flag(pv, r, n_req, n_blocks, ok);
+  if (!ok) return;
+  for (int64_t j = threadIdx.x; j < nb; j += blockDim.x) {
+    pv.part_key[b0 + j] = keys[b0 + j];
+    pv.part_req[b0 + j] = uint32_t(r);
+  }
+}
+
+// Holder descriptor of one key.
+__device__ uint64_t describe(const DevIndex &ix, uint64_t key) {
+  DescWalk w;
+  desc_init(w, key, home_bucket(key, ix.n_buckets));
+  bool empty;
+  do {
+    ulonglong2 kk[SLOTS / 2];
+    keys_load(ix, w.cw.b, kk);
+    const KeyScan sc = scan_keys(kk, key);
+    desc_fold(ix, w, sc.match, first_val(ix, w.cw.b, sc.match));
+    empty = sc.empty;
+  } while (!w.done && chain_next(ix, w.cw, empty));
+  desc_close(w);
+  return w.out;
+}
+
+// The lookup, one workgroup per request: its blocks are described in order, blockDim.x at
+// a time, up to the first group that holds a block of no instance -- the match reads
+// nothing past that block -- and the groups after it get NONE without a read, under the
+// same condition as the region-ordered form's bound (see above).  The whole chip walks a
+// few thousand chains at once, so a search for the bound would only add round trips.
+__global__ __launch_bounds__(512) void direct_lookup_kernel(DevIndex ix, ProbeView pv, const uint64_t *__restrict__ keys,
+                                                            const int64_t *__restrict__ blk_off, int32_t n_req,
+                                                            int64_t n_blocks) {
+  __shared__ uint32_t miss_at[8];
+  const int32_t r = blockIdx.x;
+  const int t = threadIdx.x, nt = blockDim.x;
+  int64_t b0, nb;
+  const bool tiles = request_tiles(blk_off, r, n_req, n_blocks, b0, nb);
+  const bool rec = n_req <= DIRECT_REQ;
+  if (t == 0 && (!tiles || (rec && pv.hist[r]))) atomicCAS(&pv.hdr->err, 0, SMETRIC_EINVAL);
+  if (!tiles) nb = 0;
+  const bool bounded = ix.hdr->n_entries + uint64_t(n_blocks) <= ix.capacity;
+  int64_t j0 = 0, hi = nb;
+  for (; j0 < nb; j0 += nt) {
+    const int64_t j = j0 + t;
+    uint64_t d = 0;
+    if (j < nb) {
+      d = describe(ix, keys[b0 + j]);
+      pv.desc_p[b0 + j] = d;
+    }
+    if (!bounded) continue;
+    const uint64_t miss = __ballot(j < nb && desc_kind(d) == D_NONE);
+    if ((t & 63) == 0) miss_at[t >> 6] = miss ? uint32_t(t) + __builtin_ctzll(miss) : 0xFFFFFFFFu;
+    __syncthreads();
+    uint32_t first = 0xFFFFFFFFu;
+    for (int w = 0; w < nt / 64; ++w) first = miss_at[w] < first ? miss_at[w] : first;
+    __syncthreads();
+    if (first != 0xFFFFFFFFu) {
+      hi = j0 + first;
+      j0 += nt;
+      break;
+    }
+  }
+  for (int64_t j = j0 + t; j < nb; j += nt) pv.desc_p[b0 + j] = make_desc(D_NONE, 0, 0);
+  if (t == 0) {  // blocks before the bound were probed; those read from it on found it
+    const uint32_t searched = uint32_t((j0 < nb ? j0 : nb) - hi), skipped = uint32_t(nb - hi);
+    if (rec) {
+      if (r == 0) pv.hdr->n_rec = uint64_t(n_req);
+      pv.base[r] = (uint64_t(skipped) << 32) | searched;
+    } else if (skipped) {
+      atomicAdd(&pv.hdr->n_skip, (unsigned long long)skipped);
+      atomicAdd(&pv.hdr->n_search, (unsigned long long)searched);
+    }
+  }
+}
+
+// Threads per request of the direct kernels: about one group per request.
+int direct_threads(int64_t n_blocks, int32_t n_req, int most) {
+  const int64_t mean = n_req > 0 ? n_blocks / n_req : 0;
+  int nt = 64;
+  while (nt < most && nt < mean) nt <<= 1;
+  return nt;
+}
+
 }  // namespace
 }  // namespace smk
 
@@ -572,6 +665,13 @@ extern "C" int smetric_probe_partition(const smetric_index *idx, const uint64_t 
   if (int rc = probe_args(idx, keys, blk_off, n_req, n_blocks, probe, probe_bytes)) return rc;
   ProbeView pv;
   probe_layout(n_blocks, &pv, probe);
+  if (direct_batch(uint64_t(n_blocks))) {
+    if (direct_needs_clear(n_req)) partition_head(pv, false, stream);
+    if (n_req > 0)
+      hipLaunchKernelGGL(direct_partition_kernel, dim3(n_req), dim3(direct_threads(n_blocks, n_req, TB)), 0, stream, pv,
+                         keys, blk_off, n_req, n_blocks);
+    return hip_rc(hipGetLastError());
+  }
   const DevIndex ix = dev_view(idx);  // geometry only: the table's contents are not read here
   partition_head(pv, false, stream);
   return partition_tail(ix, pv, keys, blk_off, n_req, uint64_t(n_blocks), false, stream);
@@ -587,6 +687,16 @@ extern "C" int smetric_probe_lookup(const smetric_index *idx, void *probe, uint6
   ProbeView pv;
   probe_layout(n_blocks, &pv, probe);
   const DevIndex ix = dev_view(idx);
+  if (direct_batch(uint64_t(n_blocks))) {
+    // more requests than records: the header's counts are cleared first
+    if (n_req > DIRECT_REQ)
+      hipLaunchKernelGGL(zero2_kernel, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint64_t *>(&pv.hdr->n_skip),
+                         uint64_t(2), nullptr, uint64_t(0));
+    if (n_req > 0)
+      hipLaunchKernelGGL(direct_lookup_kernel, dim3(n_req), dim3(direct_threads(n_blocks, n_req, 512)), 0, stream, ix, pv,
+                         keys, blk_off, n_req, n_blocks);
+    return hip_rc(hipGetLastError());
+  }
   const uint64_t nw = skip_words(uint64_t(n_blocks < 1 ? 1 : n_blocks));
   // the skip bitmap (whole 64-bit words: its allocation is rounded up to 256 bytes) and
   // the probe counters, one launch
@@ -611,6 +721,22 @@ extern "C" int smetric_probe_stats(const void *probe, uint64_t probe_bytes, int6
   if (hipMemcpyAsync(&h, pv.hdr, sizeof(h), hipMemcpyDeviceToHost, stream) != hipSuccess ||
       hipStreamSynchronize(stream) != hipSuccess)
     return SMETRIC_EHIP;
+  if (direct_batch(uint64_t(n_blocks)) && h.n_rec > 0 && h.n_rec <= uint64_t(DIRECT_REQ)) {
+    uint64_t rec[2048];
+    for (uint64_t r = 0; r < h.n_rec; r += 2048) {
+      const uint64_t m = h.n_rec - r < 2048 ? h.n_rec - r : 2048;
+      if (hipMemcpyAsync(rec, pv.base + r, 8 * m, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+          hipStreamSynchronize(stream) != hipSuccess)
+        return SMETRIC_EHIP;
+      for (uint64_t i = 0; i < m; ++i) {
+        h.n_skip += rec[i] >> 32;
+        h.n_search += uint32_t(rec[i]);
+      }
+    }
+  }
+  if (direct_batch(uint64_t(n_blocks))) {
+    if (h.err) h.n = 0;
+  }
   *n_probed = h.n >= h.n_skip ? h.n - h.n_skip : 0;
   *n_search = h.n_search;
   return SMETRIC_OK;

@@ -1,7 +1,8 @@
 """The insert's paths against the oracle at the sizes where they part: refreshes of entries
-many requests share."""
+many requests share, and batches around the limits of the one-workgroup insert."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2607_08565_amd import workload as W
 from tests.parity import Pair, say, to_dev
@@ -48,3 +49,89 @@ def test_refresh_of_entries_shared_by_many_requests(I, n_inst_used):
         assert insert_both(pair, True, d_keys, d_boff, nb, okeys, blk_off, inst, rng.permutation(R), epoch) == 0
         say(f"  I={I} used={n_inst_used} insert {k}: epoch {epoch}, {nb} blocks")
         pair.compare_index(f"insert {k} at epoch {epoch}")
+
+
+def _sized(rng, R, nb, shared, block=16):
+    """R prompts of nb blocks in all (some empty), those long enough starting with one of
+    three prefixes of `shared` blocks; a few prompts are copies of an earlier one."""
+    cut = np.sort(rng.integers(0, nb + 1, R - 1)) if R > 1 else np.zeros(0, np.int64)
+    n = np.diff(np.concatenate([[0], cut, [nb]]))
+    pre = [rng.integers(0, W.VOCAB, block * shared, dtype=np.int32) for _ in range(3)]
+    ps = []
+    for r in range(R):
+        p = rng.integers(0, W.VOCAB, block * int(n[r]), dtype=np.int32)
+        k = min(len(p), block * shared)
+        p[:k] = pre[int(rng.integers(0, 3))][:k]
+        if r and rng.random() < 0.1 and len(ps[r - 1]) >= len(p):
+            p = ps[r - 1][: len(p)].copy()
+        ps.append(np.concatenate([p, rng.integers(0, W.VOCAB, int(rng.integers(0, block)), dtype=np.int32)]))
+    off = np.zeros(R + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in ps])
+    return np.concatenate(ps), off
+
+
+@pytest.mark.parametrize("probed", [False, True])
+@pytest.mark.parametrize("R,nb", [(1, 0), (1, 1), (1, 1023), (3, 1024), (64, 1025), (1023, 4095), (1024, 4096),
+                                  (1025, 4096), (40, 4097), (1, 4096)])
+def test_insert_around_the_small_batch_limits(R, nb, probed):
+    """Batches of exactly R requests and nb blocks on few and on many instances (keys turning
+    into bitmap records while pairs of theirs wait), entered three times on new targets with
+    rising and falling epochs; then a batch that does not fit and one with a bad target,
+    which change nothing."""
+    rng = np.random.default_rng(1000 * R + nb)
+    for I in (2, 40):
+        pair = Pair(max(64, 3 * nb), I)
+        toks, off = _sized(rng, R, nb, 12)
+        d_boff, n, d_keys, okeys, blk_off = pair.hash_both(toks, off)
+        assert n == nb
+        say(f"  I={I} R={R} blocks={nb} probed={probed}")
+        for epoch in (4, 6, 5):
+            args = (rng.integers(0, I, R), rng.permutation(R), epoch)
+            rc = insert_both(pair, probed, d_keys, d_boff, nb, okeys, blk_off, *args)
+            assert rc in (0, pair.oix.status)
+            pair.compare_index(f"I={I} epoch {epoch}")
+        bad = rng.integers(0, I, R)
+        bad[-1] = I
+        insert_both(pair, probed, d_keys, d_boff, nb, okeys, blk_off, bad, np.arange(R), 9)
+        pair.compare_index(f"I={I} bad target")
+        tight = Pair(max(1, nb // 2), I)
+        insert_both(tight, probed, d_keys, d_boff, nb, okeys, blk_off, rng.integers(0, I, R), np.arange(R), 1)
+        tight.compare_index(f"I={I} capacity {max(1, nb // 2)}")
+
+
+@pytest.mark.parametrize("B,R,nb", [(16, 300, (1 << 18) - 1), (16, 300, 1 << 18), (16, 300, (1 << 18) + 1),
+                                    (32, 9, 5000), (16, 20000, 5000), (16, 16384, 4097), (64, 70, 0)])
+def test_probed_path_around_the_direct_form(B, R, nb):
+    """The fused hash + partition, the lookup, the match and the insert on both sides of the
+    direct form's limits -- blocks, requests with a record of their own -- twice, the second
+    time on an index that holds part of every prompt: rows, index and the lookup's counts."""
+    from paper_2607_08565_amd import smetric as S
+    rng = np.random.default_rng(nb + R)
+    I = 24
+    pair = Pair(3 * nb + 100, I, block=B)
+    toks, off = _sized(rng, R, nb, 30, B)
+    d_boff, n, d_keys, okeys, blk_off = pair.hash_both(toks, off)
+    assert n == nb
+    # enter the first half of every prompt, on several instances
+    half = (np.diff(blk_off) + 1) // 2
+    sel = np.repeat(blk_off[:-1] - np.concatenate([[0], np.cumsum(half)[:-1]]), half) + np.arange(half.sum())
+    hoff = np.concatenate([[0], np.cumsum(half)]).astype(np.int64)
+    hk = okeys[sel.astype(np.int64)]
+    assert pair.insert_both(to_dev(hk if len(hk) else np.ones(1, np.uint64)), to_dev(hoff), len(hk), hk, hoff,
+                            rng.integers(0, I, R), np.arange(R), 1) == 0
+    for epoch in (2, 3):
+        say(f"  B={B} R={R} blocks={nb} epoch {epoch}")
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        keys, state = pair.gix.hash_partition(to_dev(toks if len(toks) else np.zeros(1, np.int32)), to_dev(off), d_boff, nb,
+                                              block_size=B, status=status)
+        assert int(status.item()) == 0 and np.array_equal(keys[:nb].cpu().numpy(), okeys)
+        for _ in range(2):  # a lookup may run again on its state
+            pair.gix.probe_lookup(state, keys, d_boff, nb)
+        om = pair.oix.match(okeys, blk_off)
+        assert np.array_equal(pair.gix.match_probed(state, keys, d_boff, nb).cpu().numpy(), om)
+        probed, searched = S.Index.probe_stats(state, nb)
+        assert int(om.max(1).sum() if len(om) else 0) <= probed <= nb
+        inst, sess = rng.integers(0, I, R).astype(np.int32), rng.permutation(R).astype(np.uint32)
+        pair.gix.insert_probed(state, R, nb, to_dev(inst), to_dev(sess), epoch)
+        assert pair.oix.insert(okeys, blk_off, inst, sess, epoch) == 0
+        pair.compare_index(f"epoch {epoch}")
