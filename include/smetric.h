@@ -369,7 +369,7 @@ int smetric_sessions(const uint64_t *keys, const int64_t *blk_off, int32_t n_req
  * arrives; prefill_cost is Eq. (1) with the request's hit on the target):
  *   q_r[i] = q[i] + sum over r' < r routed to i of prefill_cost(r', c[r'][i]).
  * A parallel pass first records what does not depend on the loads (domain, prev,
- * session_cached, the prefill cost on prev, the deadline); then one wavefront walks the
+ * session_cached, the prefill cost on prev, the deadline); then one workgroup walks the
  * batch with the running loads kept doubled in 128 bits (exact).
  *   q_out      int64[n_instances] (out, optional: NULL) final loads in ns, rounded down
  *   workspace  >= smetric_route_seq_ws_bytes(n_req) bytes (80 per request), 256-B aligned

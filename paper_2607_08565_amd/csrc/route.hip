@@ -25,6 +25,7 @@ namespace {
 constexpr int RW = 4;  // waves per workgroup
 constexpr int RU = 4;  // instances per lane whose loads a route kernel issues together
 typedef __int128 i128;
+typedef unsigned __int128 u128;
 constexpr int64_t NO_DECODE = int64_t(1) << 62;  // decode slack meaning "no live decode"
 
 struct RouteParams {
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(64 * RW) void route_coloc_kernel(
 //         loads -- domain check, prev = argmax c, session_cached, the costs on prev and at
 //         the best other hit, the deadline, and the smallest other est2 on the starting
 //         loads -- into an 80-byte record.
-//   seq   ONE wavefront routes the batch in index order; the running loads 2q[i] live in
+//   seq   one workgroup routes the batch in index order; the running loads 2q[i] live in
 //         LDS as 128-bit integers (and as doubles, exact while they stay below 2^50),
 //         with a lower bound of their minimum.  Per request:
 //           * cached follow-up whose prev meets its deadline: stick (no scan);
@@ -376,23 +377,38 @@ __global__ __launch_bounds__(64 * RW) void route_coloc_kernel(
 //           * otherwise the row is scanned for the argmin with the current loads (in
 //             double precision while every score is an integer below 2^51, else in 128
 //             bits).
-//         The first two need only prev's load, so 64 requests are settled per step (see
-//         route_seq_kernel); the rest go one at a time, their rows (for <= 1024 instances)
-//         and records loaded into registers ahead of use.
+//         The first two need only prev's load, so whole runs of them are settled at once
+//         (see route_seq_kernel); the rest go one at a time, their rows loaded ahead of use.
 // ---------------------------------------------------------------------------------
-constexpr int SEQ_MAX_I = 4096;  // LDS: the loads (64 KB), as doubles (32 KB), step counters (16 KB)
+// floor(x / d) for 0 <= x < 2^128 and 0 < d < 2^32, by 32-bit digits
+__device__ __forceinline__ u128 div128_u32(u128 x, uint32_t d) {
+  u128 q = 0;
+  uint64_t rem = 0;
+#pragma unroll
+  for (int k = 3; k >= 0; --k) {
+    const uint64_t cur = (rem << 32) | uint32_t(x >> (32 * k));
+    q |= u128(cur / d) << (32 * k);
+    rem = cur % d;
+  }
+  return q;
+}
+
+constexpr int SEQ_MAX_I = 4096;  // LDS: the loads (64 KB), as doubles (32 KB)
 
 struct SeqRec {
   int32_t prev;    // argmax c, lowest id
-  int32_t flags;   // bit 0: in domain (apart from q), bit 1: session cached, bit 2: follow-up
+  int32_t flags;   // bit 0: in domain (apart from q), bit 1: session cached, bit 2: follow-up,
+                   // bit 3: no instance but prev can meet the deadline on the loads the batch
+                   // starts with (nor at any later point: loads only grow)
   int32_t L;       // prompt length
   int32_t start;   // (rr_base + r) mod I: where the rotation of rr_argmin starts
   i128 cost_prev;  // 2 x prefill_cost(req, c[prev]), Eq. (1)
   i128 cost_rest;  // 2 x prefill_cost at the largest hit of any other instance: a lower
                    // bound of every other instance's cost (Eq. (1) falls as the hit grows)
-  i128 bound;      // SLACK_num x 2 (b + a L): i meets its deadline iff est2(i) SLACK_den <= bound
-  i128 m0;         // min over i != prev of est2(i) on the loads the batch starts with: a lower
-                   // bound of every other instance's est2 at any later point (loads only grow)
+  i128 lim;        // i meets its deadline iff est2(i) <= lim: the largest integer whose product
+                   // with SLACK_den is at most SLACK_num x 2 (b + a L) (SLACK infinite: 2^126)
+  int64_t c0;      // est2 with no hit (an upper bound of every instance's) if below 2^50, else -1
+  int64_t pad;
 };
 constexpr int64_t SEQ_NO_OTHER = int64_t(1) << 60;  // m0 with no other instance (x 2^30: never meets)
 
@@ -462,36 +478,13 @@ __global__ __launch_bounds__(64 * RW) void route_seq_prep_kernel(const int32_t *
   out.cost_prev = ok ? est2(p, L, bc, 0) : i128(0);
   // one instance: nothing else to bound, any value will do
   out.cost_rest = ok ? est2(p, L, c2 < 0 ? bc : c2, 0) : i128(0);
-  out.bound = i128(p.slack_num) * (i128(2) * (i128(p.slo_b) + i128(p.slo_a) * (ok ? L : 0)));
-  out.m0 = m0;
+  const i128 bound = i128(p.slack_num) * (i128(2) * (i128(p.slo_b) + i128(p.slo_a) * (ok ? L : 0)));
+  out.lim = p.slack_den == 0 ? i128(1) << 126 : i128(div128_u32(u128(bound), uint32_t(p.slack_den)));
+  out.flags |= int32_t(m0 > out.lim) << 3;
+  const i128 c0 = ok ? est2(p, L, 0, 0) : i128(0);
+  out.c0 = c0 < (i128(1) << 50) ? int64_t(c0) : -1;
+  out.pad = 0;
   rec[r] = out;
-}
-
-template <int K>
-struct SeqRow {
-  int32_t v[K];  // c[r][lane + 64 k] (K = 0: read on demand)
-  SeqRec rec;
-};
-
-template <int K>
-__device__ __forceinline__ void seq_load(const int32_t *__restrict__ matched, int32_t I, int32_t r, int32_t n_req,
-                                         const SeqRec *__restrict__ recs, SeqRow<K> &row) {
-  // Unconditional, clamped loads keep this straight-line code, so the compiler can wait
-  // for exactly the loads a request needs; lanes past the last instance are never read.
-  const int lane = threadIdx.x;
-  const int32_t rr = r < n_req ? r : n_req - 1;
-  const int32_t *c = matched + int64_t(rr) * I;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int i = lane + 64 * k;
-    row.v[k] = c[i < I ? i : I - 1];
-  }
-  // Vector loads on purpose: as scalar loads (the index is uniform) they would complete
-  // out of order, and every later wait on LDS or on the current request's scalars would
-  // also wait for these prefetches.
-  int32_t rv = rr;
-  asm volatile("" : "+v"(rv));
-  row.rec = recs[rv];
 }
 
 // Minimum of the running loads (every lane gets it).
@@ -544,342 +537,432 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t k) {
   return (uint64_t(hi) << 32) | lo;
 }
 
-// The running state of the online route, held by its one wavefront (all fields uniform but
-// the LDS arrays).  Besides the exact loads 2q it keeps them as doubles for the scan's fast
-// path: exact while q_small (every 2q below 2^50), which stops holding for good once any
-// load reaches it.  With a1 = 2 C_LIN B and a2 = C_ATT B^2, Eq. (1) doubled is
-// est2(c) = C0 - c (a1 + a2 c) on the request's domain 0 <= c <= L / B, C0 = est2(0).
+// A 2q above every real one's while they are below 2^50, for slots past the last instance.
 constexpr double SEQ_PAD_2Q = 3377699720527872.0;  // 3 x 2^50
 
-struct SeqState {
-  i128 *q2;      // LDS: 2q per instance (exact)
-  double *q2d;   // LDS: the same values as doubles (exact while q_small)
-  i128 qmin;     // a lower bound of min(2q), exact unless qmin_stale
-  bool qmin_stale;
-  bool q_small;  // every 2q < 2^50
-  bool a_ok;     // a1, a2 < 2^53: exact as doubles
-  double a1, a2;
+// The batch in windows of 64 requests, one per lane, whose records stay in registers while
+// the requests are settled in order:
+//   * a cached follow-up puts its prefill on prev whether it sticks or takes the last
+//     resort, so -- as long as every earlier request of a run of them is decided that way --
+//     request l's load on prev is exactly q2[prev] plus the costs of the run's earlier
+//     requests with the same prev.  With that load, "prev meets its deadline" (stick) is
+//     exact, and "min(2q) + cost_rest misses it" (last resort) is exact with any lower bound
+//     of min(2q), which only grows.  A run between two requests that need a scan is settled
+//     in one go by wavefront 0; one that neither rule settles ends it and is scanned.
+//   * a first turn or an evicted session needs the argmin over every instance: a scan.
+// Bound: the chain of decisions, each waiting for the loads the one before left.  What a
+// scan waits for is kept short: NW wavefronts share the instances (KW per lane and
+// wavefront), the rows of the next SEQ_D scans are on their way before they are needed, and
+// the winner's new load is its score (2q + the cost of the request there), which the scan
+// has, so nothing is formed or looked up after it.  One barrier per scan passes the
+// wavefronts' minima on; the wavefront that owns the winner stores its load, which only it
+// reads until the next barrier.
+// A wavefront issues one instruction in about four cycles, so the chain's length in
+// instructions is what counts: deadlines are limits formed by the prep pass (no products
+// here), a run of follow-ups is summed by pointer jumping in 64 bits while every load and
+// cost is below 2^50, and a scan after a scan skips the run logic.  Per request, before and
+// now (24,576-token prompts): 64 instances, all follow-ups 0.097 -> 0.030 us, all first turns
+// 0.80 -> 0.35; 256 instances 0.082 -> 0.040 and 0.93 -> 0.48; 1,024 instances 0.127 -> 0.090,
+// 10 % first turns 0.41 -> 0.18, all first turns 1.43 -> 0.67; 2,048 requests on 4,096
+// instances, 20 % first turns 4.2 -> 0.49.
+constexpr int SEQ_D = 3;     // rows in flight
+constexpr int SEQ_SUP = 64;  // windows whose scans are known ahead
+
+template <int KW>
+struct SeqRow {
+  int32_t v[KW];  // c[r][instance of (wavefront, k, lane)]
 };
 
-// The last-resort test of a cached follow-up whose prev misses its deadline: every other
-// instance i has est2(i) >= min(2q) + cost_rest and est2(i) >= m0, so if either misses the
-// deadline nobody can meet it.  qmin is a lower bound of min(2q) (loads only grow), exact
-// unless qmin_stale; a stale bound that does not settle the test is refreshed first, so the
-// minimum is recomputed only when a request needs it.
-__device__ __forceinline__ bool seq_none_meets(const SeqRec &rec, const RouteParams &p, int32_t I, SeqState &st) {
-  const i128 bound = rec.bound;
-  if (uni(int32_t(rec.m0 * p.slack_den > bound || (st.qmin + rec.cost_rest) * p.slack_den > bound)) != 0) return true;
-  if (!st.qmin_stale) return false;
-  st.qmin = seq_qmin(st.q2, I);
-  st.qmin_stale = false;
-  return uni(int32_t((st.qmin + rec.cost_rest) * p.slack_den > bound)) != 0;
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
+  return (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), l))) << 32) |
+         uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l));
 }
 
-// A load update: the exact value, its double, and whether the doubles stay exact.
-__device__ __forceinline__ void seq_store(SeqState &st, int32_t i, i128 v) {
-  st.q2[i] = v;
-  st.q2d[i] = double(int64_t(v < (i128(1) << 62) ? v : i128(0)));
+__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
+  return (uint64_t(uint32_t(__shfl(int(uint32_t(v >> 32)), src, 64))) << 32) |
+         uint32_t(__shfl(int(uint32_t(v)), src, 64));
+}
+__device__ __forceinline__ i128 shfl128(i128 v, int src) {
+  return i128((u128(shfl64(uint64_t(u128(v) >> 64), src)) << 64) | shfl64(uint64_t(v), src));
 }
 
-// Decide request r.  Every branch below is on wavefront-uniform values (read with
-// readfirstlane), and every lane performs the identical stores, so the code has no divergent
-// regions: the compiler can then wait for exactly the prefetched loads it uses.
-template <int K>
-__device__ __forceinline__ void seq_decide(const SeqRow<K> &row, const int32_t *__restrict__ matched, int32_t r,
-                                           int32_t I, const RouteParams &p, bool q_ok, SeqState &st,
-                                           int32_t *__restrict__ target, uint8_t *__restrict__ branch) {
-  const int lane = threadIdx.x;
-  const int32_t flags = uni(row.rec.flags);
-  if (!q_ok || !(flags & 1)) {
-    target[r] = -1;
-    branch[r] = SMETRIC_INVALID;
+template <int NW, int KW>
+__global__ __launch_bounds__(64 * NW) void route_seq_kernel(const int32_t *__restrict__ matched, int32_t n_req,
+                                                            int32_t I, const int64_t *__restrict__ q, RouteParams p,
+                                                            const SeqRec *__restrict__ recs,
+                                                            int32_t *__restrict__ target, uint8_t *__restrict__ branch,
+                                                            int64_t *__restrict__ q_out) {
+  constexpr int NI = 64 * NW * KW;  // instance slots
+  __shared__ i128 q2[NI];           // 2q per instance (exact)
+  __shared__ double q2d[NI];        // the same as doubles (exact while q_small)
+  __shared__ uint64_t smask[SEQ_SUP];  // per window: its requests that need a scan whatever the loads
+  __shared__ uint64_t pkey[2][NW];  // the wavefronts' minima of a scan, two scans' worth
+  __shared__ i128 pscore[2][NW];
+  __shared__ int32_t pdist[2][NW];
+  __shared__ uint32_t pub[2];       // a settled run's end and q_small, two runs' worth
+  __shared__ int flags0[2];
+  const int lane = threadIdx.x & 63, wave = NW > 1 ? uni(threadIdx.x >> 6) : 0;
+  const int first = wave * 64 * KW;  // this wavefront's instances: first + 64 k + lane
+  if (threadIdx.x < 2) flags0[threadIdx.x] = 0;
+  __syncthreads();
+  for (int32_t i = threadIdx.x; i < NI; i += 64 * NW) {
+    const int64_t qi = i < I ? q[i] : 0;
+    if (qi < 0 || qi >= (int64_t(1) << 62)) flags0[0] = 1;
+    if (qi >= (int64_t(1) << 49)) flags0[1] = 1;
+    q2[i] = i128(2) * qi;
+    // Slots past the last instance score above every real one (see scan below).
+    q2d[i] = i < I ? 2.0 * double(qi < 0 ? 0 : qi) : SEQ_PAD_2Q;
+  }
+  __syncthreads();
+  if (n_req <= 0) {
+    if (q_out)
+      for (int32_t i = threadIdx.x; i < I; i += 64 * NW) q_out[i] = int64_t(q2[i] >> 1);
     return;
   }
-  const int32_t prev = uni(row.rec.prev);
-  const bool cached = flags & 2, follow_up = flags & 4;
-  const bool slack_inf = p.slack_den == 0;
-  const i128 cost_prev = row.rec.cost_prev, bound = row.rec.bound;  // uniform across lanes
-  i128 *q2 = st.q2;
-  const bool meets_prev =
-      follow_up && cached && (slack_inf || uni(int32_t((q2[prev] + cost_prev) * p.slack_den <= bound)) != 0);
-  int32_t t;
-  uint8_t br;
-  i128 cost_t;
-  if (follow_up && cached && meets_prev) {
-    t = prev;
-    br = SMETRIC_STICK;
-    cost_t = cost_prev;
-  } else if (follow_up && cached && !slack_inf && seq_none_meets(row.rec, p, I, st)) {
-    // prev misses its deadline, and every other instance i has est2(i) >= min(2q) +
-    // cost_rest and est2(i) >= m0: nobody can meet it
-    t = prev;
-    br = SMETRIC_LAST_RESORT;
-    cost_t = cost_prev;
-  } else {
-    const int64_t L = uni(row.rec.L);
-    const int32_t tr = follow_up ? 1 : 0;
-    const int32_t start = uni(row.rec.start);
-    const int32_t *c = matched + int64_t(r) * I;
-    MinSD best{0, 0x7FFFFFFF};
-    // Fast path, while every 2q < 2^50 and C0 < 2^50: each candidate's score
-    // 2q + est2 = 2q + C0 - c (a1 + a2 c) is an integer below 2^51, and two fused
-    // multiply-adds in double precision give it exactly, offset by 2^52 so that its bit
-    // pattern holds the score in the low 52 bits under a fixed exponent field.  Shifting the
-    // exponent out leaves room for the rotation distance (I <= 4096): one 64-bit key per
-    // instance, minimised with two 32-bit DPP minima.
-    bool fast = false;
-    if (st.q_small && st.a_ok) {
-      const i128 c0 = est2(p, L, 0, 0);
-      if (c0 < (i128(1) << 50)) {
-        fast = true;
-        const double off = double(int64_t(c0)) + 4503599627370496.0;  // C0 + 2^52, exact
-        const double a1 = st.a1, a2 = st.a2;
-        const double *q2d = st.q2d;
-        uint64_t kmin = ~uint64_t(0);
-        int32_t d = lane >= start ? lane - start : lane - start + I;  // rotation distance of i
-        auto scan_one = [&](int32_t ci, double q2i) {
-          const double cd = double(ci);
-          const double s2 = __builtin_fma(-cd, __builtin_fma(a2, cd, a1), q2i + off);
-          const uint64_t key = (__builtin_bit_cast(uint64_t, s2) << 12) | uint32_t(d);
-          kmin = key < kmin ? key : kmin;
-        };
-        if (K > 0) {
-          // Slots past the last instance hold 2q = 3 x 2^50 (SEQ_PAD_2Q): their scores fall
-          // in [2^51, 2^52) under the same exponent, above every real one, so the loop has
-          // no per-lane conditions and all its LDS reads go out before the first is used.
-          double qv[K > 0 ? K : 1];
-#pragma unroll
-          for (int k = 0; k < (K > 0 ? K : 1); ++k) qv[k] = q2d[lane + 64 * k];
-#pragma unroll
-          for (int k = 0; k < (K > 0 ? K : 1); ++k) {
-            scan_one(row.v[k], qv[k]);
-            d = d + 64 >= I ? d + 64 - I : d + 64;  // I > 64 whenever K > 1
-          }
-        } else {
-          for (int32_t i = lane; i < I; i += 64) {
-            scan_one(c[i], q2d[i]);
-            d = d + 64 >= I ? d + 64 - I : d + 64;
-          }
-        }
-        const uint64_t m = wave_min_u64(kmin);
-        best.s = i128(m >> 12);
-        best.d = int32_t(m & 4095u);
-      }
-    }
-    if (!fast) {
-      if (K > 0) {
-#pragma unroll
-        for (int k = 0; k < (K > 0 ? K : 1); ++k) {
-          const int32_t i = lane + 64 * k;
-          const int32_t ii = i < I ? i : I - 1;
-          const i128 e = q2[ii] + est2(p, L, row.v[k], 0);
-          min_sd(best, e, i < I ? (i >= start ? i - start : i - start + I) : 0x7FFFFFFF);
-        }
-      } else {
-        for (int32_t i = lane; i < I; i += 64)
-          min_sd(best, q2[i] + est2(p, L, c[i], 0), i >= start ? i - start : i - start + I);
-      }
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) min_sd(best, shfl_xor128(best.s, m), __shfl_xor(best.d, m, 64));
-    }
-    const int32_t bal0 = start + uni(best.d);  // start, d < I
-    const int32_t bal = bal0 >= I ? bal0 - I : bal0;
-    if (tr == 0) {
-      t = bal;
-      br = SMETRIC_FIRST_TURN;
-    } else if (!cached) {
-      t = bal;
-      br = SMETRIC_EVICTED;
-    } else if (!slack_inf && uni(int32_t(best.s * p.slack_den > bound)) != 0) {
-      t = prev;
-      br = SMETRIC_LAST_RESORT;
-    } else {
-      t = bal;
-      br = SMETRIC_MIGRATE;
-    }
-    int32_t ct;
-    if (K > 0) {
-      int32_t v = 0;
-#pragma unroll
-      for (int k = 0; k < (K > 0 ? K : 1); ++k)
-        if (k == t / 64) v = row.v[k];
-      ct = uni(__shfl(v, t % 64, 64));
-    } else {
-      ct = uni(c[t]);
-    }
-    cost_t = t == prev ? cost_prev : est2(p, L, ct, 0);
-  }
-  // One wavefront does every LDS access, and its LDS operations complete in program
-  // order, so the next request reads this update without a fence (a fence here would also
-  // wait for the rows prefetched for later requests).  All lanes store the same values.
-  const i128 old = q2[t];
-  target[r] = t;
-  branch[r] = br;
-  seq_store(st, t, old + cost_t);  // the request's prefill joins its target's queue
-  // both flags stay wavefront-uniform (every lane holds the same values): read as scalars
-  st.q_small = st.q_small && uni(int32_t(old + cost_t < (i128(1) << 50))) != 0;
-  if (uni(int32_t(old == st.qmin && cost_t != 0)) != 0) st.qmin_stale = true;
-}
+  const bool q_ok = flags0[0] == 0;
+  bool q_small = flags0[1] == 0;  // every 2q < 2^50 (uniform over the workgroup)
+  const i128 a1i = i128(2) * p.c_lin * p.B, a2i = i128(p.c_att) * p.B * p.B;
+  const bool a_ok = a1i < (i128(1) << 53) && a2i < (i128(1) << 53);  // exact as doubles
+  const double a1 = double(int64_t(a_ok ? a1i : 0)), a2 = double(int64_t(a_ok ? a2i : 0));
+  i128 qmin = 0;           // wavefront 0: a lower bound of min(2q) (loads only grow)
+  bool qmin_stale = true;  // and whether it may be below the minimum
+  int par = 0, pub_par = 0;
+  bool moved = false;  // a scan's load update has not been followed by a barrier
 
-// Requests [rs, re) one at a time, rows and records prefetched D requests ahead.
-template <int K, int D>
-__device__ __forceinline__ void seq_exact_block(const int32_t *__restrict__ matched, int32_t n_req, int32_t I,
-                                                const RouteParams &p, bool q_ok,
-                                                const SeqRec *__restrict__ recs, SeqState &st,
-                                                int32_t *__restrict__ target, uint8_t *__restrict__ branch,
-                                                int32_t rs, int32_t re) {
-  SeqRow<K> ring[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) seq_load<K>(matched, I, rs + d, n_req, recs, ring[d]);
-  for (int32_t r0 = rs; r0 < re; r0 += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int32_t r = r0 + d;
-      if (r < re) {
-        seq_decide<K>(ring[d], matched, r, I, p, q_ok, st, target, branch);
-        seq_load<K>(matched, I, r + D, n_req, recs, ring[d]);
-      }
-    }
-  }
-}
-
-// The batch in blocks of 64 requests, one per lane.  A cached follow-up puts its prefill on
-// prev whether it sticks or takes the last resort, so -- if every earlier request of the
-// block is decided that way -- request l's load on prev is exactly q2[prev] plus the costs
-// of the earlier requests with the same prev.  With that load, "prev meets its deadline"
-// (stick) is exact, and "min(2q) + cost_rest misses it" (last resort) is exact with any
-// lower bound of min(2q), which only grows; out-of-domain requests change nothing.  The
-// requests before the first one not settled this way are decided together, that one
-// alone with the sequential rule, and the next block starts after it.  After two blocks in
-// a row that settle nothing (e.g. first turns, which always need a scan), the next 64
-// requests go through the sequential rule with prefetching.
-template <int K, int D>
-__global__ __launch_bounds__(64) void route_seq_kernel(const int32_t *__restrict__ matched, int32_t n_req,
-                                                       int32_t I, const int64_t *__restrict__ q, RouteParams p,
-                                                       const SeqRec *__restrict__ recs,
-                                                       int32_t *__restrict__ target, uint8_t *__restrict__ branch,
-                                                       int64_t *__restrict__ q_out) {
-  __shared__ i128 q2[SEQ_MAX_I];
-  __shared__ double q2d[SEQ_MAX_I];
-  __shared__ uint32_t n_on[SEQ_MAX_I];  // block requests per prev (0 between blocks)
-  const int lane = threadIdx.x;
-  bool q_ok = true, small = true;
-  for (int32_t i = lane; i < I; i += 64) {
-    const int64_t qi = q[i];
-    if (qi < 0 || qi >= (int64_t(1) << 62)) q_ok = false;
-    if (qi >= (int64_t(1) << 49)) small = false;
-    q2[i] = i128(2) * qi;
-    q2d[i] = 2.0 * double(qi < 0 ? 0 : qi);
-    n_on[i] = 0;
-  }
-  for (int32_t i = I + lane; i < 64 * K; i += 64) q2d[i] = SEQ_PAD_2Q;
-  q_ok = __ballot(!q_ok) == 0;
-  __syncthreads();
-  SeqState st;
-  st.q2 = q2;
-  st.q2d = q2d;
-  st.qmin = seq_qmin(q2, I);  // a lower bound of min(2q) from here on (loads only grow)
-  st.qmin_stale = false;
-  st.q_small = __ballot(!small) == 0;
-  const i128 a1 = i128(2) * p.c_lin * p.B, a2 = i128(p.c_att) * p.B * p.B;
-  st.a_ok = a1 < (i128(1) << 53) && a2 < (i128(1) << 53);
-  st.a1 = double(int64_t(st.a_ok ? a1 : 0));
-  st.a2 = double(int64_t(st.a_ok ? a2 : 0));
-  const bool slack_inf = p.slack_den == 0;
-  int32_t r0 = 0;
-  int streak = 0;
-  while (r0 < n_req) {
-    if (streak >= 2) {
-      const int32_t re = n_req - r0 < 64 ? n_req : r0 + 64;
-      seq_exact_block<K, D>(matched, n_req, I, p, q_ok, recs, st, target, branch, r0, re);
-      r0 = re;
-      streak = 0;
-      continue;
-    }
-    const int32_t nv = n_req - r0 < 64 ? n_req - r0 : 64;
-    const int32_t r = r0 + lane;
+  auto rec_at = [&](int32_t r) {
+    // Vector loads on purpose: as scalar loads they would complete out of order, and every
+    // later wait on LDS or scalars would also wait for these prefetches.
     int32_t rv = r < n_req ? r : n_req - 1;
-    asm volatile("" : "+v"(rv));  // a vector load: see seq_load
-    const SeqRec rec = recs[rv];
-    const bool in = lane < nv;
-    const bool ok = q_ok && (rec.flags & 1);
-    const bool sticky = ok && (rec.flags & 2) && (rec.flags & 4);  // cached follow-up: its prefill goes to prev
-    const int32_t prev = rec.prev;
-    const bool mine = in && sticky;
-    if (mine) atomicAdd(&n_on[prev], 1u);
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    // requests sharing a prev within the block form a group (lanes in index order): each
-    // adds the costs of the group's earlier requests to its load on prev
-    uint64_t todo = __ballot(mine && n_on[prev] > 1);
-    __builtin_amdgcn_wave_barrier();
-    if (mine) n_on[prev] = 0;
-    i128 excl = 0;
-    uint64_t group = 0;  // lanes with my prev (0: nobody else has it)
-    while (todo) {
-      const int32_t p0 = __builtin_amdgcn_readlane(prev, __builtin_ctzll(todo));
-      const uint64_t m = __ballot(mine && prev == p0);
-      todo &= ~m;
-      i128 run = 0;
-      for (uint64_t mm = m; mm; mm &= mm - 1) {
-        const int l = __builtin_ctzll(mm);
-        if (lane == l) {
-          excl = run;
-          group = m;
-        }
-        run += readlane128(rec.cost_prev, l);
+    asm volatile("" : "+v"(rv));
+    return recs[rv];
+  };
+  auto row_load = [&](int32_t r, SeqRow<KW> &row) {
+    const int32_t *c = matched + int64_t(r >= 0 && r < n_req ? r : n_req - 1) * I;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+      const int32_t i = first + 64 * k + lane;
+      row.v[k] = c[i < I ? i : I - 1];  // clamped and unconditional, so nothing waits for it here
+    }
+  };
+
+  // The scans of the next SEQ_SUP windows: the wavefronts share the windows.
+  uint64_t my_mask = 0;   // lane l: window sup + l
+  int32_t sup = 0;
+  const int32_t n_win = (n_req + 63) / 64;
+  auto look_ahead = [&]() {
+    constexpr int PER = SEQ_SUP / NW;
+    if (NW > 1) __syncthreads();
+#pragma unroll 8
+    for (int j = 0; j < PER; ++j) {
+      const int32_t w = sup + wave * PER + j, r = w * 64 + lane;
+      int32_t rv = r < n_req ? r : n_req - 1;
+      asm volatile("" : "+v"(rv));
+      const int32_t f = recs[rv].flags;
+      const uint64_t m = __ballot(r < n_req && q_ok && (f & 1) && (f & 6) != 6);
+      if (lane == 0) smask[wave * PER + j] = m;
+    }
+    if (NW > 1) __syncthreads();
+    my_mask = smask[lane];
+  };
+  // the next scans to request rows for: the rest of window fw's, then the windows after it
+  int32_t fw = 0;
+  uint64_t fm = 0;
+  auto next_scan = [&]() -> int32_t {  // -1: no more within these windows
+    if (!fm) {
+      const int a = fw - sup;
+      const uint64_t later = a >= SEQ_SUP - 1 ? 0 : __ballot(my_mask != 0) & (~uint64_t(0) << (a + 1));
+      if (!later) return -1;
+      fw = sup + int32_t(__builtin_ctzll(later));
+      fm = readlane_u64(my_mask, fw - sup);
+    }
+    const int32_t r = fw * 64 + int32_t(__builtin_ctzll(fm));
+    fm &= fm - 1;
+    return r;
+  };
+
+  int32_t win = 0, w0 = 0, cur = 0;  // the window; its requests before cur are settled
+  SeqRec rec;
+  uint64_t scm = 0, stm = 0;
+  uint64_t same = 0;  // the window's cached follow-ups with this lane's prev (this lane's bit included)
+  bool small_costs = false;  // their costs are all below 2^50
+  double off = 0.0;   // this lane's C0 + 2^52, exact while off_ok
+  bool off_ok = false;
+  int prev_bits = 1;
+  while (prev_bits < 12 && (1 << prev_bits) < I) ++prev_bits;
+  int32_t tv = -1;    // this lane's request's decision (wavefront 0), stored with the window's
+  int32_t bv = SMETRIC_INVALID;
+  auto open_window = [&]() {
+    rec = rec_at(w0 + lane);
+    const bool ok = w0 + lane < n_req && q_ok && (rec.flags & 1);
+    scm = readlane_u64(my_mask, win - sup);
+    const bool sticky = ok && (rec.flags & 6) == 6;
+    stm = __ballot(sticky);
+    off_ok = a_ok && rec.c0 >= 0;
+    off = double(off_ok ? rec.c0 : int64_t(0)) + 4503599627370496.0;
+    if (wave == 0 && stm) {
+      small_costs = __ballot(sticky && rec.c0 < 0) == 0;
+      same = stm;
+      for (int b = 0; b < prev_bits; ++b) {
+        const bool set = (rec.prev >> b) & 1;
+        const uint64_t m = __ballot(set);
+        same &= set ? m : ~m;
       }
     }
-    const i128 q_pre = mine ? q2[prev] : i128(0);
-    const i128 q_prev = q_pre + excl;
-    bool settled = !ok;  // out of domain: settled, nothing queued
-    uint8_t br = SMETRIC_INVALID;
-    const bool stick = sticky && (slack_inf || (q_prev + rec.cost_prev) * p.slack_den <= rec.bound);
-    bool none = sticky && !stick &&
-                ((st.qmin + rec.cost_rest) * p.slack_den > rec.bound || rec.m0 * p.slack_den > rec.bound);
-    if (st.qmin_stale && __ballot(in && sticky && !stick && !none)) {  // a stale bound left one open
-      st.qmin = seq_qmin(q2, I);
-      st.qmin_stale = false;
-      none = sticky && !stick && (st.qmin + rec.cost_rest) * p.slack_den > rec.bound;
-      none |= sticky && !stick && rec.m0 * p.slack_den > rec.bound;
+    tv = -1;
+    bv = SMETRIC_INVALID;
+  };
+  auto close_window = [&]() {
+    if (wave == 0 && w0 + lane < n_req) {
+      target[w0 + lane] = tv;
+      branch[w0 + lane] = uint8_t(bv);
     }
-    if (stick) {
-      settled = true;
-      br = SMETRIC_STICK;
-    } else if (none) {
-      settled = true;
+  };
+
+  // Decide request w0 + l by a scan over its row.  open: a cached follow-up that neither
+  // rule settled.
+  auto scan = [&](const SeqRow<KW> &row, int l, bool open) {
+    const int32_t start = __builtin_amdgcn_readlane(rec.start, l);
+    const int32_t flags = __builtin_amdgcn_readlane(rec.flags, l);
+    int32_t t;
+    int32_t br = open ? SMETRIC_MIGRATE : (flags & 4) ? SMETRIC_EVICTED : SMETRIC_FIRST_TURN;
+    bool late = false;  // open: not even the best instance meets the deadline
+    if (q_small && __builtin_amdgcn_readlane(int(off_ok), l)) {
+      // While every 2q < 2^50 and C0 < 2^50 each candidate's score 2q + est2 = 2q + C0 -
+      // c (a1 + a2 c) is an integer below 2^51, and two fused multiply-adds in double
+      // precision give it exactly, offset by 2^52 so that its bit pattern holds the score in
+      // the low 52 bits under a fixed exponent field.  Shifting the exponent out leaves room
+      // for the rotation distance (I <= 4096): one 64-bit key per instance.  Slots past the
+      // last instance hold 2q = 3 x 2^50: their scores fall in [2^51, 2^52), above every
+      // real one.
+      const double o = __builtin_bit_cast(double, readlane_u64(__builtin_bit_cast(uint64_t, off), l));
+      double qv[KW];
+#pragma unroll
+      for (int k = 0; k < KW; ++k) qv[k] = q2d[first + 64 * k + lane];
+      uint64_t kmin = ~uint64_t(0);
+#pragma unroll
+      for (int k = 0; k < KW; ++k) {
+        const double cd = double(row.v[k]);
+        const double s2 = __builtin_fma(-cd, __builtin_fma(a2, cd, a1), qv[k] + o);
+        const int32_t i = first + 64 * k + lane;
+        const int32_t d = i >= start ? i - start : i - start + I;
+        const uint64_t key = (__builtin_bit_cast(uint64_t, s2) << 12) | uint32_t(d);
+        kmin = key < kmin ? key : kmin;
+      }
+      uint64_t m = wave_min_u64(kmin);
+      if (NW > 1) {
+        if (lane == 0) pkey[par][wave] = m;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m = pkey[par][w] < m ? pkey[par][w] : m;
+        m = (uint64_t(uint32_t(uni(int32_t(m >> 32)))) << 32) | uint32_t(uni(int32_t(uint32_t(m))));
+      }
+      const uint64_t score = m >> 12;
+      t = start + int32_t(m & 4095u);
+      t = t >= I ? t - I : t;
+      late = open && i128(score) > readlane128(rec.lim, l);
+      if (!late) {
+        // One wavefront's LDS operations complete in program order, so the owner's next
+        // scan reads this without a fence.  All its lanes store the same values.
+        if (NW == 1 || t / (64 * KW) == wave) {
+          q2[t] = i128(score);
+          q2d[t] = __builtin_bit_cast(double, score | (uint64_t(0x433) << 52)) - 4503599627370496.0;
+        }
+        q_small = score < (uint64_t(1) << 50);
+      }
+    } else {
+      const int64_t L = __builtin_amdgcn_readlane(rec.L, l);
+      const int32_t *c = matched + int64_t(w0 + l) * I;
+      MinSD best{0, 0x7FFFFFFF};
+#pragma unroll 1
+      for (int32_t i = first + lane; i < first + 64 * KW && i < I; i += 64)
+        min_sd(best, q2[i] + est2(p, L, c[i], 0), i >= start ? i - start : i - start + I);
+#pragma unroll 1
+      for (int m = 32; m >= 1; m >>= 1) min_sd(best, shfl_xor128(best.s, m), __shfl_xor(best.d, m, 64));
+      if (NW > 1) {
+        if (lane == 0) {
+          pscore[par][wave] = best.s;
+          pdist[par][wave] = best.d;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int w = 0; w < NW; ++w) min_sd(best, pscore[par][w], pdist[par][w]);
+      }
+      const i128 score = readlane128(best.s, 0);
+      t = start + uni(best.d);
+      t = t >= I ? t - I : t;
+      late = open && score > readlane128(rec.lim, l);
+      if (!late) {
+        if (NW == 1 || t / (64 * KW) == wave) {
+          q2[t] = score;
+          q2d[t] = double(int64_t(score < (i128(1) << 62) ? score : i128(0)));
+        }
+        q_small = q_small && score < (i128(1) << 50);
+      }
+    }
+    par ^= 1;
+    if (late) {  // rare: prev takes it; its load is read between two barriers
       br = SMETRIC_LAST_RESORT;
+      t = __builtin_amdgcn_readlane(rec.prev, l);
+      const i128 now = readlane128(q2[t], 0) + readlane128(rec.cost_prev, l);
+      if (NW > 1) __syncthreads();
+      if (wave == 0) {
+        q2[t] = now;
+        q2d[t] = double(int64_t(now < (i128(1) << 62) ? now : i128(0)));
+      }
+      if (NW > 1) __syncthreads();
+      q_small = q_small && now < (i128(1) << 50);
     }
-    const uint64_t open = __ballot(in && !settled);
-    const int32_t f = open ? __builtin_ctzll(open) : nv;  // requests [r0, r0 + f) are decided
-    // the first request not settled needs its row: requested now, used below
-    SeqRow<K> row;
-    if (f < nv) seq_load<K>(matched, I, r0 + f, n_req, recs, row);
-    if (lane < f) {
-      target[r] = ok ? prev : -1;
-      branch[r] = br;
+    tv = lane == l ? t : tv;
+    bv = lane == l ? br : bv;
+    qmin_stale = true;
+    moved = true;
+  };
+
+  // Wavefront 0 settles the cached follow-ups `run` of lanes [cur, s): returns where that
+  // ends.  T = int64_t while every load and cost is below 2^50 (64 costs and a load stay below
+  // 2^57, and limits are cut to 2^62), else i128.
+  auto settle_as = [&](uint64_t run, int s, auto zero) -> int {
+    using T = decltype(zero);
+    const bool mine = (run >> lane) & 1;
+    const int32_t prev = rec.prev;
+    const T cost = T(rec.cost_prev), rest = T(rec.cost_rest);
+    const T lim = sizeof(T) == 16 ? T(rec.lim) : T(rec.lim < (i128(1) << 62) ? rec.lim : i128(1) << 62);
+    // requests sharing a prev within the run, in index order: each adds the costs of the
+    // run's earlier ones to its load on prev, summed by pointer jumping toward lower lanes
+    const uint64_t group = mine ? same & run : 0;
+    const uint64_t before = group & ((uint64_t(1) << lane) - 1);
+    int32_t up = before ? 63 - __builtin_clzll(before) : -1;
+    T sum = cost;  // this lane's and, after k rounds, its 2^k - 1 predecessors'
+    while (__ballot(up >= 0)) {
+      const int src = up >= 0 ? up : lane;
+      T add;
+      if constexpr (sizeof(T) == 16) add = shfl128(sum, src);
+      else add = T(shfl64(uint64_t(sum), src));
+      const int32_t next = __shfl(up, src, 64);
+      if (up >= 0) {
+        sum += add;
+        up = next;
+      }
+    }
+    T q_pre = 0;
+    if (mine) {
+      if constexpr (sizeof(T) == 16) q_pre = q2[prev];
+      else q_pre = T(q2d[prev]);
+    }
+    const T q_new = q_pre + sum;  // prev's load with this request's prefill
+    const bool stick = mine && q_new <= lim;
+    const bool hopeless = (rec.flags & 8) != 0;
+    bool none = mine && !stick && (hopeless || T(qmin) + rest > lim);
+    if (qmin_stale && __ballot(mine && !stick && !none)) {  // a stale bound left one open
+      if constexpr (sizeof(T) == 16) {
+        qmin = seq_qmin(q2, I);
+      } else {  // positive doubles order as their bit patterns
+        uint64_t k = ~uint64_t(0);
+        for (int32_t i = lane; i < I; i += 64) {
+          const uint64_t b = __builtin_bit_cast(uint64_t, q2d[i]);
+          k = b < k ? b : k;
+        }
+        qmin = i128(int64_t(__builtin_bit_cast(double, wave_min_u64(k))));
+      }
+      qmin_stale = false;
+      none |= mine && !stick && T(qmin) + rest > lim;
+    }
+    const uint64_t unsettled = __ballot(mine && !stick && !none);
+    const int f = unsettled ? int(__builtin_ctzll(unsettled)) : s;
+    const uint64_t decided = f >= 64 ? ~uint64_t(0) : (uint64_t(1) << f) - 1;
+    if (mine && lane < f) {
+      tv = prev;
+      bv = stick ? SMETRIC_STICK : SMETRIC_LAST_RESORT;
     }
     // prev's new load, written by the last of the decided requests with that prev
-    const uint64_t decided = f >= 64 ? ~uint64_t(0) : (uint64_t(1) << f) - 1;
     const uint64_t after_me = lane == 63 ? uint64_t(0) : ~((uint64_t(2) << lane) - 1);
     const bool last = mine && lane < f && (group & after_me & decided) == 0;
     __builtin_amdgcn_wave_barrier();
-    if (last) seq_store(st, prev, q_prev + rec.cost_prev);
-    st.q_small = st.q_small && __ballot(last && q_prev + rec.cost_prev >= (i128(1) << 50)) == 0;
+    if (last) {
+      q2[prev] = i128(q_new);
+      q2d[prev] = double(int64_t(i128(q_new) < (i128(1) << 62) ? i128(q_new) : i128(0)));
+    }
+    q_small = q_small && __ballot(last && i128(q_new) >= (i128(1) << 50)) == 0;
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     // the minimum can only have moved if an instance at the minimum took load
-    if (__ballot(mine && lane < f && q_pre == st.qmin)) st.qmin_stale = true;
-    r0 += f;
-    if (f < nv) {  // the first request not settled: the sequential rule
-      seq_decide<K>(row, matched, r0, I, p, q_ok, st, target, branch);
-      r0 += 1;
-      streak = f == 0 ? streak + 1 : 0;
+    if (__ballot(mine && lane < f && q_pre == T(qmin))) qmin_stale = true;
+    return f;
+  };
+
+  // Settles requests up to the next scan, whose lane is then cur; false at the end of the
+  // windows looked ahead at.
+  auto advance = [&]() -> bool {
+#pragma unroll 1
+    while (true) {
+      const int32_t nv = n_req - w0 < 64 ? n_req - w0 : 64;
+      const uint64_t from = cur < 64 ? ~uint64_t(0) << cur : 0;
+      const int32_t s = (scm & from) ? int32_t(__builtin_ctzll(scm & from)) : nv;
+      const uint64_t run = stm & from & (s >= 64 ? ~uint64_t(0) : (uint64_t(1) << s) - 1);
+      int32_t f = s;  // the run [cur, f) is settled
+      if (run) {
+        if (NW > 1 && moved) __syncthreads();
+        moved = false;
+        if (wave == 0) {
+          f = q_small && small_costs ? settle_as(run, s, int64_t(0))
+                                     : settle_as(run, s, i128(0));
+          if (NW > 1 && lane == 0) pub[pub_par] = uint32_t(f) | (uint32_t(q_small) << 8);
+        }
+        if (NW > 1) {
+          __syncthreads();
+          const uint32_t v = uint32_t(uni(int32_t(pub[pub_par])));
+          f = int32_t(v & 255u);
+          q_small = (v >> 8) & 1u;
+          pub_par ^= 1;
+        }
+      }
+      cur = f;
+      if (f < s) {  // rare: the row is fetched now
+        SeqRow<KW> row;
+        row_load(w0 + f, row);
+#pragma unroll
+        for (int k = 0; k < KW; ++k) asm volatile("" : "+v"(row.v[k]));  // waited for here, not where paths join
+        scan(row, f, true);
+        cur = f + 1;
+        continue;
+      }
+      if (f < nv) return true;
+      close_window();
+      ++win;
+      w0 += 64;
+      cur = 0;
+      if (win >= n_win || win - sup >= SEQ_SUP) return false;
+      open_window();
+    }
+  };
+
+#pragma unroll 1
+  for (; sup < n_win; sup += SEQ_SUP) {
+    look_ahead();
+    open_window();
+    fw = sup;
+    fm = readlane_u64(my_mask, 0);
+    SeqRow<KW> ring[SEQ_D];
+#pragma unroll
+    for (int d = 0; d < SEQ_D; ++d) row_load(next_scan(), ring[d]);
+    // unrolled, so that the loads in flight at a scan are known and it waits for its own row
+    // only; every scan of these windows comes by in the order in which the rows were requested
+    bool more = true;
+#pragma unroll 1
+    while (more) {
+#pragma unroll
+      for (int d = 0; d < SEQ_D; ++d) {
+        if (!(cur < 64 && ((scm >> cur) & 1)))
+          if (!(more = advance())) break;
+        scan(ring[d], cur, false);
+        ++cur;
+        row_load(next_scan(), ring[d]);
+      }
     }
   }
   __syncthreads();
   if (q_out)
-    for (int32_t i = lane; i < I; i += 64) {
+    for (int32_t i = threadIdx.x; i < I; i += 64 * NW) {
       const i128 v = q2[i] >> 1;
       q_out[i] = v > i128(INT64_MAX) ? INT64_MAX : int64_t(v);
     }
@@ -903,7 +986,6 @@ __global__ __launch_bounds__(64) void route_seq_kernel(const int32_t *__restrict
 //         decided by rescoring its listed candidates on the current state.
 //         The scores est2 x n are compared in 192 bits: over a batch both factors grow.
 // ---------------------------------------------------------------------------------
-typedef unsigned __int128 u128;
 constexpr int SEQC_MAX_I = 4096;  // LDS: 2q (64 KB), n and the step counters (16 KB each)
 
 struct SeqCRec {
@@ -915,19 +997,6 @@ struct SeqCRec {
   i128 cost_prev;  // 2 x prefill_cost(req, c[prev])
   i128 thr;        // prev meets the deadline iff its doubled queue is at most thr
 };
-
-// floor(x / d) for 0 <= x < 2^128 and 0 < d < 2^32, by 32-bit digits
-__device__ __forceinline__ u128 div128_u32(u128 x, uint32_t d) {
-  u128 q = 0;
-  uint64_t rem = 0;
-#pragma unroll
-  for (int k = 3; k >= 0; --k) {
-    const uint64_t cur = (rem << 32) | uint32_t(x >> (32 * k));
-    q |= u128(cur / d) << (32 * k);
-    rem = cur % d;
-  }
-  return q;
-}
 
 __device__ __forceinline__ bool tpot_pass(int64_t slack, i128 cost2) {
   return slack >= NO_DECODE || cost2 <= i128(2) * slack;
@@ -1158,10 +1227,6 @@ struct Key3 {
 };
 __device__ __forceinline__ bool key_less(const Key3 &a, const Key3 &b) {
   return a.k2 < b.k2 || (a.k2 == b.k2 && (a.k1 < b.k1 || (a.k1 == b.k1 && a.k0 < b.k0)));
-}
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
-  const int lo = __shfl(int(uint32_t(v)), src, 64), hi = __shfl(int(uint32_t(v >> 32)), src, 64);
-  return (uint64_t(uint32_t(hi)) << 32) | uint32_t(lo);
 }
 __device__ __forceinline__ Key3 key_shfl(const Key3 &k, int src) {
   return Key3{shfl64(k.k2, src), shfl64(k.k1, src), shfl64(k.k0, src)};
@@ -1690,18 +1755,20 @@ int route_seq_launch(const int32_t *matched, int32_t n_req, int32_t n_instances,
   if (n_req > 0)
     hipLaunchKernelGGL(route_seq_prep_kernel, dim3((n_req + RW - 1) / RW), dim3(64 * RW), 0, stream, matched, n_req,
                        n_instances, prompt_len, hist_len, turn, q, rp, rr_base, recs);
-  const int kk = (n_instances + 63) / 64;
-#define SEQ_LAUNCH(K, D)                                                                                       \
-  hipLaunchKernelGGL((route_seq_kernel<K, D>), dim3(1), dim3(64), 0, stream, matched, n_req, n_instances,         \
+#define SEQ_LAUNCH(NW, KW)                                                                                     \
+  hipLaunchKernelGGL((route_seq_kernel<NW, KW>), dim3(1), dim3(64 * (NW)), 0, stream, matched, n_req, n_instances,  \
                      q, rp, recs, target, branch, q_out)
-  // prefetch depth D: D * (K + 4) vector loads in flight (K row words and a 64-byte
-  // record per request) stay within the 63 the wait counter tracks
-  if (kk <= 1) SEQ_LAUNCH(1, 8);
-  else if (kk <= 2) SEQ_LAUNCH(2, 8);
-  else if (kk <= 4) SEQ_LAUNCH(4, 7);
-  else if (kk <= 8) SEQ_LAUNCH(8, 5);
-  else if (kk <= 16) SEQ_LAUNCH(16, 3);
-  else SEQ_LAUNCH(0, 8);
+  // One wavefront while it holds the instances in 8 slots per lane: a barrier and the exchange of
+  // the minima cost 0.2 us of a scan's 0.35 to 0.67 (all first turns, us per request: 256
+  // instances 0.48 by one wavefront, 0.56 by four; 500: 0.59 and 0.61; 1,024: 0.81 by one,
+  // 0.73 by two, 0.67 by four).
+  if (n_instances <= 64) SEQ_LAUNCH(1, 1);
+  else if (n_instances <= 128) SEQ_LAUNCH(1, 2);
+  else if (n_instances <= 256) SEQ_LAUNCH(1, 4);
+  else if (n_instances <= 512) SEQ_LAUNCH(1, 8);
+  else if (n_instances <= 1024) SEQ_LAUNCH(4, 4);
+  else if (n_instances <= 2048) SEQ_LAUNCH(8, 4);
+  else SEQ_LAUNCH(8, 8);
 #undef SEQ_LAUNCH
   return hip_rc(hipGetLastError());
 }
