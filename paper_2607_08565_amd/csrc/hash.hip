@@ -13,6 +13,8 @@
 //    every load instruction covers 1 KB of contiguous HBM.  Four lanes share a block;
 //    each forms the NH products of its two token pairs and a quad reduction (DPP quad
 //    permutes) yields the block digest.
+//  * B = 32, 64, 128, 256: the same kernel, a block read as B / 16 sub-blocks of 16 whose
+//    digests (sums of products) add up to the block's.
 //  * other even B: one wavefront per request; lane l digests block l of the tile.
 //  Digests go through LDS so that lane l then owns block l of the tile; the chain is an
 //  inclusive scan of affine maps x -> M x + e_l across the wavefront, done with DPP moves
@@ -176,7 +178,11 @@ __device__ __forceinline__ void load_tile16(const int32_t *x, int64_t tile, int6
 // MODE H_DIRECT: also the direct form of the probe state -- each key and its request in
 // block order, and the request's validity.
 enum HashMode { H_KEYS = 0, H_COUNT = 1, H_DIRECT = 2 };
-template <int NW, int MODE>
+// G > 1: blocks of 16 G tokens (G a power of two up to 16), read as G sub-blocks of 16.  A
+// lane's sub-blocks all have the same place in their blocks (64 is a multiple of G), so its
+// offset constants stay in registers; a tile of 64 blocks takes G loads of 64 sub-blocks,
+// whose digests are summed over each block through LDS.
+template <int NW, int MODE, int G>
 __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restrict__ tokens,
                                                          int64_t n_tokens,
                                                          const int64_t *__restrict__ tok_off,
@@ -189,16 +195,27 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
                                                          uint64_t nb_inv, uint64_t clen, int *probe_err,
                                                          ProbeView pv) {
   constexpr bool COUNT = MODE == H_COUNT;
+  constexpr int B = 16 * G;
+  static_assert(G == 1 || !COUNT, "longer blocks are counted by the partition");
   __shared__ uint64_t dig[NW][64];
+  __shared__ uint64_t bdig[G > 1 ? NW : 1][64];  // G > 1: the tile's block digests
   __shared__ uint64_t agg[NW];
   __shared__ unsigned int lh[COUNT ? 2 * NREG : 1];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = blockIdx.x;
   int64_t t0, b0, nb;
-  const bool ok = request_ok(tok_off, blk_off, r, n_tokens, n_blocks, 16, t0, b0, nb);
-  if (MODE == H_DIRECT && threadIdx.x == 0) {
+  const bool ok = request_ok(tok_off, blk_off, r, n_tokens, n_blocks, B, t0, b0, nb);
+  if (MODE == H_DIRECT) {
+    // blocks of 16: a token range that does not give its block range makes the state invalid;
+    // longer ones keep the caller's earlier keys, as the two separate calls would
     int64_t tb, tn;
-    direct_flag(pv, r, n_req, n_blocks, request_tiles(blk_off, r, n_req, n_blocks, tb, tn) && ok);
+    const bool tiles = request_tiles(blk_off, r, n_req, n_blocks, tb, tn);
+    if (threadIdx.x == 0) direct_flag(pv, r, n_req, n_blocks, tiles && (ok || G > 1));
+    if (G > 1 && !ok && tiles)
+      for (int64_t j = threadIdx.x; j < tn; j += 64 * NW) {
+        pv.part_key[tb + j] = keys[tb + j];
+        pv.part_req[tb + j] = uint32_t(r);
+      }
   }
   if (!ok) {
     if (threadIdx.x == 0 && status) atomicCAS(status, 0, SMETRIC_EINVAL);
@@ -212,18 +229,19 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
   // them while every wavefront's first tile is in flight, and the others read them from LDS.
   // (the powers common to all lanes are formed by every wavefront in scalar registers)
   __shared__ uint64_t s_lane[3][64];  // M^(l+1), M^(l % 16 + 1), M^(l - 31)
-  __shared__ uint32_t s_k[16];        // K[0 .. 15]
+  __shared__ uint32_t s_k[B];         // K
   const int q = lane & 3;
   const int32_t *x = tokens + t0;
   Tile16 cur, nxt;
-  load_tile16(x, wave, nb, q, lane, cur);
-  ChainConsts cc = chain_uniform(seed, 16);
+  const int64_t nsub = nb * G;
+  load_tile16(x, int64_t(wave) * G, nsub, q, lane, cur);
+  ChainConsts cc = chain_uniform(seed, B);
   if (wave == 0) {
     chain_lanes(cc);
     s_lane[0][lane] = cc.Mlane;
     s_lane[1][lane] = cc.Mrow;
     s_lane[2][lane] = cc.Mhalf;
-    if (lane < 16) s_k[lane] = uint32_t(splitmix_out(seed, lane));
+    for (int t = lane; t < B; t += 64) s_k[t] = uint32_t(splitmix_out(seed, t));
   }
   __syncthreads();
   cc.Mlane = s_lane[0][lane];
@@ -236,31 +254,47 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
   const uint64_t Mw = ((wave & 1) ? M64 : 1ull) * ((wave & 2) ? M128 : 1ull) * ((wave & 4) ? M256 : 1ull) *
                       ((wave & 8) ? M512 : 1ull);
   const uint64_t Mstep = NW == 2 ? M128 : (NW == 4 ? M256 : (NW == 8 ? M512 : M1024));
-  // this lane's four offset constants: K[4q .. 4q+3], q = lane % 4
-  const uint32_t k0 = s_k[4 * q + 0], k1 = s_k[4 * q + 1], k2 = s_k[4 * q + 2], k3 = s_k[4 * q + 3];
+  // this lane's four offset constants: K[4q .. 4q+3] of its sub-block's place, q = lane % 4
+  const uint32_t *kp = s_k + 16 * ((lane >> 2) % G) + 4 * q;
+  const uint32_t k0 = kp[0], k1 = kp[1], k2 = kp[2], k3 = kp[3];
   const int64_t n_tiles = (nb + 63) / 64;
   uint64_t carry = cc.s_init;  // chain state before the step's first block
   const uint64_t c_lo = COUNT ? uint64_t(b0) / clen : 0, B1 = (c_lo + 1) * clen, B2 = B1 + clen;
   if (COUNT && threadIdx.x < 2 * NREG) lh[threadIdx.x] = 0;  // first used after the step's barrier
   for (int64_t step0 = 0; step0 < n_tiles; step0 += NW) {
     const int64_t tile = step0 + wave;
-    load_tile16(x, tile + NW, nb, q, lane, nxt);
     const int64_t j0 = tile * 64;
     const int64_t left = nb - j0;
     const int n_valid = int(left <= 0 ? 0 : (left < 64 ? left : 64));
+#pragma unroll 1
+    for (int g = 0; g < G; ++g) {
+      load_tile16(x, (g + 1 < G ? tile : tile + NW - 1) * G + g + 1, nsub, q, lane, nxt);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int4 v = cur.v[u];
-      uint64_t part = uint64_t(uint32_t(v.x) + k0) * uint64_t(uint32_t(v.y) + k1) +
-                      uint64_t(uint32_t(v.z) + k2) * uint64_t(uint32_t(v.w) + k3);
-      part += dpp64<0xB1>(part);  // quad_perm [1,0,3,2]
-      part += dpp64<0x4E>(part);  // quad_perm [2,3,0,1]
-      if (q == 0) dig[wave][16 * u + (lane >> 2)] = part;
+      for (int u = 0; u < 4; ++u) {
+        const int4 v = cur.v[u];
+        uint64_t part = uint64_t(uint32_t(v.x) + k0) * uint64_t(uint32_t(v.y) + k1) +
+                        uint64_t(uint32_t(v.z) + k2) * uint64_t(uint32_t(v.w) + k3);
+        part += dpp64<0xB1>(part);  // quad_perm [1,0,3,2]
+        part += dpp64<0x4E>(part);  // quad_perm [2,3,0,1]
+        if (q == 0) dig[wave][16 * u + (lane >> 2)] = part;
+      }
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      if (G > 1) {
+        cur = nxt;
+        if (lane < 64 / G) {
+          uint64_t d = 0;
+#pragma unroll
+          for (int i = 0; i < G; ++i) d += dig[wave][lane * G + i];
+          bdig[wave][g * (64 / G) + lane] = d;
+        }
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      }
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     // local inclusive scan of the tile's affine maps from state 0
-    const uint64_t v = affine_scan64(lane < n_valid ? finalise(dig[wave][lane] + uint64_t(j0 + lane)) : 0, cc);
+    const uint64_t dl = G > 1 ? bdig[G > 1 ? wave : 0][lane] : dig[wave][lane];
+    const uint64_t v = affine_scan64(lane < n_valid ? finalise(dl + uint64_t(j0 + lane)) : 0, cc);
     if (lane == 63) agg[wave] = v;
     __syncthreads();
     // inclusive scan of the tiles' aggregates over lanes 0..NW-1: lane w holds
@@ -288,7 +322,7 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
     }
     carry = Mstep * carry + readlane64u(a, NW - 1);  // used only when every tile of this step was full
     __syncthreads();
-    cur = nxt;
+    if (G == 1) cur = nxt;
   }
   if (COUNT && threadIdx.x < 2 * NREG) {  // the loop ended on a barrier: lh is complete
     const unsigned int v = lh[threadIdx.x];
@@ -296,7 +330,7 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
   }
 }
 
-// Any even B in [2, 256].  DIRECT: as hash16_kernel's H_DIRECT, but a request's token range
+// Any even B in [2, 256] (used for those that are not 16 times a power of two).  DIRECT: as hash16_kernel's H_DIRECT, but a request's token range
 // does not make the probe state invalid (its keys are then the caller's earlier ones).
 template <bool DIRECT>
 __global__ __launch_bounds__(64 * WAVES) void hash_generic_kernel(
@@ -348,6 +382,45 @@ __global__ __launch_bounds__(64 * WAVES) void hash_generic_kernel(
   }
 }
 
+// Blocks of 16 to 256 tokens, a power of two: the tiled kernel, with as many wavefronts per
+// request as its prompts have tiles of 64 blocks (8 for blocks of 16: see HASH_NW).  Bound by
+// the token stream.  4,096 prompts of 14,000 tokens, before (one wavefront per request, each
+// lane reading its own block) and now: blocks of 32 69 -> 39 us, 64 97 -> 39, 128 94 -> 41; 500 of
+// 40,000, blocks of 256: 34 -> 15 us (5.3 TB/s).
+template <int MODE, int G>
+void launch_hash_tiles(const int32_t *tokens, int64_t n_tokens, const int64_t *tok_off, const int64_t *blk_off,
+                       int32_t n_req, int64_t n_blocks, uint64_t seed, uint64_t *keys, int32_t *status,
+                       const ProbeView &pv, hipStream_t stream) {
+  const int64_t mean = n_blocks / n_req;
+  auto go = [&](auto *kernel, int nw) {
+    hipLaunchKernelGGL(kernel, dim3(n_req), dim3(64 * nw), 0, stream, tokens, n_tokens, tok_off, blk_off, n_req, n_blocks,
+                       seed, keys, status, static_cast<uint32_t *>(nullptr), uint64_t(0), uint64_t(0), uint64_t(1),
+                       static_cast<int *>(nullptr), pv);
+  };
+  if (G == 1 || mean > 256) go(hash16_kernel<HASH_NW, MODE, G>, HASH_NW);
+  else if (mean > 128) go(hash16_kernel<4, MODE, G>, 4);
+  else go(hash16_kernel<2, MODE, G>, 2);
+}
+
+// Keys of a batch, and with DIRECT the direct form of its probe state.
+template <bool DIRECT>
+void launch_hash(const int32_t *tokens, int64_t n_tokens, const int64_t *tok_off, const int64_t *blk_off, int32_t n_req,
+                 int64_t n_blocks, int32_t block_size, uint64_t seed, uint64_t *keys, int32_t *status,
+                 const ProbeView &pv, hipStream_t stream) {
+  constexpr int MODE = DIRECT ? H_DIRECT : H_KEYS;
+  auto *tiles = block_size == 16    ? launch_hash_tiles<MODE, 1>
+                : block_size == 32  ? launch_hash_tiles<MODE, 2>
+                : block_size == 64  ? launch_hash_tiles<MODE, 4>
+                : block_size == 128 ? launch_hash_tiles<MODE, 8>
+                : block_size == 256 ? launch_hash_tiles<MODE, 16>
+                                    : nullptr;
+  if (tiles)
+    tiles(tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, seed, keys, status, pv, stream);
+  else
+    hipLaunchKernelGGL(hash_generic_kernel<DIRECT>, dim3((n_req + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, stream,
+                       tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, int(block_size), seed, keys, status, pv);
+}
+
 }  // namespace
 }  // namespace smk
 
@@ -363,14 +436,8 @@ extern "C" int smetric_hash_blocks(const int32_t *tokens, int64_t n_tokens, cons
   if (n_req == 0) return SMETRIC_OK;
   if (!tok_off || !blk_off || (n_tokens > 0 && !tokens) || (n_blocks > 0 && !keys))
     return SMETRIC_EINVAL;
-  const dim3 grid((n_req + WAVES - 1) / WAVES), block(64 * WAVES);
-  if (block_size == 16)
-    hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_KEYS>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens, tok_off,
-                       blk_off, n_req, n_blocks, seed, keys, status, static_cast<uint32_t *>(nullptr), uint64_t(0),
-                       uint64_t(0), uint64_t(1), static_cast<int *>(nullptr), ProbeView{});
-  else
-    hipLaunchKernelGGL(hash_generic_kernel<false>, grid, block, 0, stream, tokens, n_tokens, tok_off,
-                       blk_off, n_req, n_blocks, int(block_size), seed, keys, status, ProbeView{});
+  launch_hash<false>(tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, block_size, seed, keys, status, ProbeView{},
+                     stream);
   return hip_rc(hipGetLastError());
 }
 
@@ -386,26 +453,20 @@ extern "C" int smetric_hash_partition(const int32_t *tokens, int64_t n_tokens, c
   probe_layout(n_blocks, &pv, probe);
   if (direct_batch(uint64_t(n_blocks))) {
     if (direct_needs_clear(n_req)) partition_head(pv, false, stream);
-    if (n_req > 0 && block_size == 16)
-      hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_DIRECT>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens,
-                         tok_off, blk_off, n_req, n_blocks, seed, keys, status, static_cast<uint32_t *>(nullptr),
-                         uint64_t(0), uint64_t(0), uint64_t(1), static_cast<int *>(nullptr), pv);
-    else if (n_req > 0)
-      hipLaunchKernelGGL(hash_generic_kernel<true>, dim3((n_req + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, stream,
-                         tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, int(block_size), seed, keys, status, pv);
+    if (n_req > 0)
+      launch_hash<true>(tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, block_size, seed, keys, status, pv, stream);
     return hip_rc(hipGetLastError());
   }
   const DevIndex ix = dev_view(idx);  // geometry only
   const bool counted = block_size == 16 && n_req > 0;
   partition_head(pv, counted, stream);
   if (counted)
-    hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_COUNT>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens,
+    hipLaunchKernelGGL((hash16_kernel<HASH_NW, H_COUNT, 1>), dim3(n_req), dim3(64 * HASH_NW), 0, stream, tokens, n_tokens,
                        tok_off, blk_off, n_req, n_blocks, seed, keys, status, pv.hist, ix.n_buckets, ix.nb_inv,
                        partition_chunk(uint64_t(n_blocks)), &pv.hdr->err, ProbeView{});
   else if (n_req > 0)
-    hipLaunchKernelGGL(hash_generic_kernel<false>, dim3((n_req + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, stream,
-                       tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, int(block_size), seed, keys, status,
-                       ProbeView{});
+    launch_hash<false>(tokens, n_tokens, tok_off, blk_off, n_req, n_blocks, block_size, seed, keys, status, ProbeView{},
+                       stream);
   return partition_tail(ix, pv, keys, blk_off, n_req, uint64_t(n_blocks), counted, stream);
 }
 
