@@ -259,16 +259,11 @@ __host__ __device__ inline uint32_t desc_kind(uint64_t d) { return uint32_t(d >>
 __host__ __device__ inline uint32_t desc_inst(uint64_t d) { return uint32_t(d >> 46) & 0xFFFFu; }
 __host__ __device__ inline uint64_t desc_x(uint64_t d) { return d & DESC_X_MASK; }
 
-// Work split of the region-ordered kernels: a fixed grid of FLAT_WG workgroups whose
-// iterations advance through the region-ordered arrays together (iteration t covers
-// items [t * FLAT_WG * 256, (t + 1) * FLAT_WG * 256)), so the live window of the table
-// slides; PART_WG workgroups partition contiguous chunks of blocks.
-constexpr int FLAT_WG = 2048;
+// Work split of the region-ordered kernels: a fixed grid whose iterations advance through
+// the region-ordered arrays together, so the live window of the table slides; PART_WG
+// workgroups partition contiguous chunks of blocks.
 constexpr int PART_WG = 1024;
 constexpr int WG_THREADS = 256;
-inline uint64_t flat_span() { return uint64_t(FLAT_WG) * WG_THREADS; }
-// items one workgroup of the fixed grid handles at most (its output segment size)
-inline uint64_t flat_segment(uint64_t n) { return (n + flat_span() - 1) / flat_span() * WG_THREADS; }
 
 // Probe state shared by smetric_probe and the calls that consume it.
 struct ProbeHdr {

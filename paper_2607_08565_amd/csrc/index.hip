@@ -368,8 +368,8 @@ struct WsHdr {
   unsigned long long nsub;     // region-ordered insert: bins per region (a power of two)
   unsigned long long n_dd2;    // region-ordered insert: fallback pair-table slots in use
   unsigned long long n_over;   // region-ordered insert: candidates in bins too large for LDS
-  int req_bad;                 // region-ordered insert: some request's target or session is invalid
   int inl;                     // region-ordered insert: refreshes done by the classify pass
+  int pad1;
   unsigned long long turns;    // find pass: new pairs, workgroups that have ended, errors (ins_check_last)
   unsigned long long pad[20];
 };
@@ -426,6 +426,10 @@ static_assert(BIN_CAP + WG_THREADS < DT, "an LDS pair table never fills");
 
 // Workgroups of the find and apply passes: at most 2 FIND_WG.
 constexpr int FIND_WG = 256;
+// Workgroups of the region-ordered insert's first pass, and of its dedupe pass (as many as
+// the device holds at its LDS use; each takes a turn on one word, see ins_check_last).
+constexpr int HEAD_WG = 64;
+constexpr int DEDUPE_WG = 512;
 
 struct InsWs {
   WsHdr *hdr;
@@ -442,7 +446,7 @@ struct InsWs {
   uint32_t *hist2;  // [NREG][KCH][NSUB_MAX] candidates of each bin in each chunk
   uint32_t *base2;  // [NREG][KCH][NSUB_MAX] first bin-order position of each (chunk, bin)
   uint32_t *bstart; // [NBIN_MAX + 1] first bin-order position of each bin
-  uint32_t *bdist;  // [NBIN_MAX] distinct new pairs of each bin
+  uint32_t *bad;    // [HEAD_WG] some request's target or session is invalid
   Cand *bcand;      // candidates in bin order
   NewPair *np;      // bin order: distinct new pairs
   uint64_t n_dedupe;
@@ -480,7 +484,7 @@ uint64_t insert_ws_layout(int64_t n_blocks, InsWs *ws, void *base) {
   const uint64_t o_h2 = take(4ull * NREG * KCH * NSUB_MAX);
   const uint64_t o_b2 = take(4ull * NREG * KCH * NSUB_MAX);
   const uint64_t o_bs = take(4ull * (NBIN_MAX + 1));
-  const uint64_t o_bd = take(4ull * NBIN_MAX);
+  const uint64_t o_bad = take(4ull * HEAD_WG);
   const uint64_t o_bc = take(sizeof(Cand) * n);
   const uint64_t o_np = take(sizeof(NewPair) * n);
   if (ws) {
@@ -498,7 +502,7 @@ uint64_t insert_ws_layout(int64_t n_blocks, InsWs *ws, void *base) {
     ws->hist2 = reinterpret_cast<uint32_t *>(b + o_h2);
     ws->base2 = reinterpret_cast<uint32_t *>(b + o_b2);
     ws->bstart = reinterpret_cast<uint32_t *>(b + o_bs);
-    ws->bdist = reinterpret_cast<uint32_t *>(b + o_bd);
+    ws->bad = reinterpret_cast<uint32_t *>(b + o_bad);
     ws->bcand = reinterpret_cast<Cand *>(b + o_bc);
     ws->np = reinterpret_cast<NewPair *>(b + o_np);
     ws->n_dedupe = nd;
@@ -598,7 +602,7 @@ __device__ __forceinline__ void memory_done() {
 // complete before its turn, so no cache is written back.  n_entries: as read when the kernel
 // began (nothing else changes it meanwhile).
 constexpr int TURN_SHIFT = 40, ERR_SHIFT = 52;  // 2^40 new pairs, 2^12 workgroups
-static_assert(2 * FIND_WG < (1 << 12), "turns and errors fit their fields");
+static_assert(2 * FIND_WG < (1 << 12) && DEDUPE_WG < (1 << 12), "turns and errors fit their fields");
 template <bool PAIRS>
 __device__ void ins_check_last(const DevIndex &ix, const InsWs &ws, int64_t n_blocks, unsigned long long n_entries,
                                uint32_t n_new, uint64_t n_pairs, bool bad) {
@@ -795,7 +799,10 @@ __global__ void spill_kernel(DevIndex ix, const uint64_t *trig, const unsigned l
 // ---------------------------------------------------------------------------------
 // Region-ordered insert, from the descriptors of smetric_probe
 // ---------------------------------------------------------------------------------
-// Pipeline (no sort, no global atomics on the way to the distinct new pairs):
+// Pipeline (no sort, no global atomics on the way to the distinct new pairs), nine launches
+// (thirteen before the clear took the request checks, the count the sizing, the scatter the
+// fallback table's clear and the dedupe the check: 4.6 us each behind busy kernels; batches of
+// 1 to 5 M blocks 13 us faster each):
 //   classify   per block in region order: refresh position, or candidate appended to the
 //              region's part of the workgroup's segment; when no error can abort the
 //              insert (checked beforehand: keys, requests, capacity for every block) the
@@ -805,7 +812,8 @@ __global__ void spill_kernel(DevIndex ix, const uint64_t *trig, const unsigned l
 //              pair share a bin
 //   dedupe     one workgroup per bin: an LDS pair table keeps each (key, instance) once
 //              with its lowest request; bins above BIN_CAP use the global pair table
-//   check      all-or-nothing: EINVAL or EFULL leave the index unchanged
+//              The last workgroup checks all-or-nothing: EINVAL or EFULL leave the index
+//              unchanged
 //   refresh    epoch = max(old, epoch) at the classified positions (if not done above)
 //   place      distinct new pairs in bin (so region) order; spill and deferred as above
 // find_member with each bucket read whole (keys and values in one 128-byte request), so
@@ -883,7 +891,8 @@ __global__ __launch_bounds__(TB) void insp_classify_kernel(DevIndex ix, ProbeVie
   }
   // No error can abort this insert (valid keys and requests; even if every block were a new
   // entry the index would not overflow): refreshes are done here, in place.
-  const bool inl = !pv.hdr->bad_key && !ws.hdr->req_bad && ix.hdr->n_entries + n <= ix.capacity;
+  const bool req_bad = __ballot(ws.bad[tid & (HEAD_WG - 1)] != 0) != 0;  // one flag per lane
+  const bool inl = !pv.hdr->bad_key && !req_bad && ix.hdr->n_entries + n <= ix.capacity;
   if (blockIdx.x == 0 && tid == 0) ws.hdr->inl = inl;
   Cand *seg = ws.cand + uint64_t(blockIdx.x) * ws.seg;
   constexpr int CU = 2;
@@ -975,14 +984,17 @@ __global__ __launch_bounds__(TB) void insp_classify_kernel(DevIndex ix, ProbeVie
   }
 }
 
-// Flags a request whose target or session is out of range (the classify pass then takes
-// the path that checks every block before the index changes).
-__global__ __launch_bounds__(TB) void insp_valid_kernel(DevIndex ix, InsWs ws, const int32_t *instance,
-                                                        const uint32_t *session, int32_t n_req) {
-  bool bad = false;
+// Clears the workspace's header and flags requests whose target or session is out of range
+// (the classify pass then takes the path that checks every block before the index changes):
+// each of HEAD_WG workgroups leaves its own flag, so nothing has to be cleared before.
+__global__ __launch_bounds__(TB) void insp_head_kernel(DevIndex ix, InsWs ws, const int32_t *instance,
+                                                       const uint32_t *session, int32_t n_req) {
+  if (blockIdx.x == 0 && threadIdx.x < sizeof(WsHdr) / 8) reinterpret_cast<uint64_t *>(ws.hdr)[threadIdx.x] = 0;
+  int bad = 0;
   for (int32_t r = blockIdx.x * TB + threadIdx.x; r < n_req; r += gridDim.x * TB)
     bad |= instance[r] < 0 || instance[r] >= ix.n_inst || session[r] >= SESSION_LIMIT;
-  if (bad) atomicOr(&ws.hdr->req_bad, 1);
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) ws.bad[blockIdx.x] = uint32_t(bad);
 }
 
 // Sum of n 32-bit counts, by one workgroup of TB threads (eight loads in flight per thread).
@@ -1012,13 +1024,10 @@ __device__ unsigned long long sum_counts(const uint32_t *cnt, uint32_t n) {
 
 // total candidates -> bins per region: the least power of two that keeps the mean bin at
 // or below BIN_TARGET candidates (at most NSUB_MAX)
-__global__ __launch_bounds__(TB) void insp_size_kernel(InsWs ws) {
-  const unsigned long long c = sum_counts(ws.cand_cnt, INS_WG);
-  if (threadIdx.x != 0) return;
-  ws.hdr->n_cand = c;
-  uint64_t nsub = 1;
-  while (nsub < NSUB_MAX && nsub * NREG * BIN_TARGET < c) nsub <<= 1;
-  ws.hdr->nsub = nsub;
+__device__ __forceinline__ uint32_t bins_per_region(unsigned long long n_cand) {
+  uint32_t nsub = 1;
+  while (nsub < uint32_t(NSUB_MAX) && uint64_t(nsub) * NREG * BIN_TARGET < n_cand) nsub <<= 1;
+  return nsub;
 }
 
 // Bin of a key among NREG * nsub equal ranges of home buckets; bin / nsub is its region.
@@ -1055,13 +1064,19 @@ __device__ __forceinline__ const Cand *chunk_item(const InsWs &ws, const ChunkPa
   return ws.cand + cp.at[lo] + (v - cp.pre[lo]);
 }
 
-// Count pass of the bin partition: workgroup (g, c) histograms its chunk over region g's
+// Count pass of the bin partition: every workgroup sizes the bins from the segments' counts
+// (4 KB each, cheaper than a launch), then workgroup (g, c) histograms its chunk over region g's
 // bins (eight candidates per thread per round, loads first) and records the chunk's size.
 __global__ __launch_bounds__(TB) void insp_bcount_kernel(DevIndex ix, InsWs ws) {
   __shared__ ChunkParts cp;
   __shared__ uint32_t h[NSUB_MAX];
   const int g = blockIdx.x / KCH, c = blockIdx.x % KCH;
-  const uint32_t nsub = uint32_t(ws.hdr->nsub);
+  const unsigned long long n_cand = sum_counts(ws.cand_cnt, INS_WG);
+  const uint32_t nsub = bins_per_region(n_cand);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ws.hdr->n_cand = n_cand;
+    ws.hdr->nsub = nsub;
+  }
   for (int s = threadIdx.x; s < NSUB_MAX; s += TB) h[s] = 0;
   chunk_parts(ws, g, c, cp);  // synchronises
   const uint32_t m = cp.pre[SEG_PER_CH];
@@ -1138,24 +1153,10 @@ __global__ __launch_bounds__(SCAN_T) void insp_bscan_kernel(InsWs ws) {
   }
 }
 
-// fallback pair-table size for the oversized bins: a power of two >= 2 x their candidates;
-// every thread sizes it (no separate launch), the first records it, all clear its slots
-__global__ void insp_size2_kernel(InsWs ws) {
-  const unsigned long long c = ws.hdr->n_over;
-  uint64_t nd = 0;
-  if (c) {
-    nd = 64;
-    while (nd < 2 * c && nd < ws.n_dedupe) nd <<= 1;
-  }
-  const uint64_t t0 = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t0 == 0) ws.hdr->n_dd2 = nd;
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t h = t0; h < nd; h += stride) ws.dd[h] = DSlot{0, 0};
-}
-
 // Scatter pass: workgroup (g, c) moves its chunk into bin order one tile at a time (LDS
 // ranks per bin, the tile regrouped by bin in LDS, each bin's part written as one run
-// after the previous tile's).
+// after the previous tile's).  The workgroups also size and clear the fallback pair table of
+// the oversized bins (a power of two >= 2 x their candidates) for the pass after this one.
 constexpr int U2 = 8;
 constexpr int TILE2 = U2 * TB;
 static_assert(NSUB_MAX % TB == 0, "bins per thread in the scans");
@@ -1166,6 +1167,12 @@ __global__ __launch_bounds__(TB) void insp_bscatter_kernel(DevIndex ix, InsWs ws
   __shared__ uint16_t ssub[TILE2];
   const int g = blockIdx.x / KCH, c = blockIdx.x % KCH, t = threadIdx.x;
   const uint32_t nsub = uint32_t(ws.hdr->nsub);
+  if (const unsigned long long over = ws.hdr->n_over) {
+    uint64_t nd = 64;
+    while (nd < 2 * over && nd < ws.n_dedupe) nd <<= 1;
+    if (blockIdx.x == 0 && t == 0) ws.hdr->n_dd2 = nd;
+    for (uint64_t h = uint64_t(blockIdx.x) * TB + t; h < nd; h += uint64_t(gridDim.x) * TB) ws.dd[h] = DSlot{0, 0};
+  }
   const uint32_t *b2 = ws.base2 + (uint64_t(g) * KCH + c) * NSUB_MAX;
   for (uint32_t s = t; s < NSUB_MAX; s += TB) {
     run[s] = s < nsub ? b2[s] : 0;
@@ -1274,33 +1281,26 @@ __device__ __forceinline__ void lds_pair(unsigned long long *tk, unsigned long l
 constexpr int DD_T = 512;
 constexpr int DD_U = BIN_CAP / DD_T;
 static_assert(BIN_CAP % DD_T == 0 && DT % DD_T == 0, "whole candidates and slots per thread");
-__global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(InsWs ws) {
+__global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(DevIndex ix, InsWs ws) {
   __shared__ unsigned long long tk[DT], tw[DT];
   __shared__ uint32_t wt[DD_T / 64];
-  __shared__ unsigned int nfb;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const uint32_t nbin = uint32_t(ws.hdr->nsub) * NREG;
   const uint64_t nd2 = ws.hdr->n_dd2;
+  const unsigned long long n_entries = ix.hdr->n_entries;
+  uint32_t n_new = 0;  // this thread's share of the workgroup's distinct new pairs
+  bool bad = t == 0 && blockIdx.x == 0 && ws.hdr->err != 0;  // an error the classify pass met
   for (uint32_t b = blockIdx.x; b < nbin; b += gridDim.x) {
     const uint32_t lo = ws.bstart[b], hi = ws.bstart[b + 1], m = hi - lo;
-    if (m == 0) {
-      if (t == 0) ws.bdist[b] = 0;
-      continue;
-    }
+    if (m == 0) continue;
     if (m > uint32_t(BIN_CAP)) {
-      if (t == 0) nfb = 0;
-      __syncthreads();
-      uint32_t mine = 0;
       for (uint32_t k = lo + t; k < hi; k += DD_T) {
         const Cand e = ws.bcand[k];
         const int64_t h = dedupe_pair<false>(ws, nd2, e.key, e.w2);
         ws.np[k] = h >= 0 ? NewPair{e.key, NP_FALLBACK | uint64_t(h)} : NewPair{KEY_EMPTY, 0};
-        mine += h >= 0;
+        n_new += h >= 0;
+        bad |= h == -2;
       }
-      if (mine) atomicAdd(&nfb, mine);
-      __syncthreads();
-      if (t == 0) ws.bdist[b] = nfb;
-      __syncthreads();
       continue;
     }
     Cand e[DD_U];
@@ -1343,23 +1343,10 @@ __global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(InsWs ws) {
       if (k != KEY_EMPTY) ws.np[lo + pre++] = NewPair{uint64_t(k), uint64_t(tw[t * Q + j])};
     }
     for (uint32_t k = lo + total + t; k < hi; k += DD_T) ws.np[k] = NewPair{KEY_EMPTY, 0};
-    if (t == 0) ws.bdist[b] = total;
+    n_new += occ;
     __syncthreads();
   }
-}
-
-__global__ __launch_bounds__(TB) void insp_check_kernel(DevIndex ix, InsWs ws) {
-  const unsigned long long c = sum_counts(ws.bdist, uint32_t(ws.hdr->nsub) * NREG);
-  if (threadIdx.x != 0) return;
-  WsHdr *h = ws.hdr;
-  h->n_new = c;
-  const int e = h->err != 0 ? h->err : (ix.hdr->n_entries + c > ix.capacity ? SMETRIC_EFULL : 0);
-  if (e != 0) {
-    h->abort = 1;
-    set_status(ix.hdr, e);
-  } else {
-    ix.hdr->n_entries += c;
-  }
+  ins_check_last<false>(ix, ws, 0, n_entries, n_new, 0, bad);
 }
 
 // The refreshes, when the classify pass could not do them (run by the placement's grid
@@ -1377,7 +1364,7 @@ __device__ void refresh_pass(const DevIndex &ix, const ProbeView &pv, const InsW
   }
 }
 
-// place: the distinct new pairs in bin order (so in region order), all FLAT_WG
+// place: the distinct new pairs in bin order (so in region order), all PLACE_WG
 // workgroups advancing through it together
 __global__ __launch_bounds__(TB) void insp_place_kernel(DevIndex ix, ProbeView pv, InsWs ws,
                                                         const uint32_t *session, uint32_t epoch) {
@@ -2448,20 +2435,13 @@ extern "C" int smetric_index_insert_probed(smetric_index *idx, const void *probe
                        n_req, n_blocks, session, epoch, TB);
     return ins_convert(ix, ws, session, epoch, stream);
   }
-  int rc;
-  if ((rc = fill(ws.hdr, sizeof(WsHdr), 0, stream))) return rc;
-  const dim3 flat(FLAT_WG), blk(TB);
-  const dim3 chunks(NREG * KCH);
-  hipLaunchKernelGGL(insp_valid_kernel, dim3(grid_for(uint64_t(n_req))), blk, 0, stream, ix, ws, instance, session,
-                     n_req);
+  const dim3 blk(TB), chunks(NREG * KCH);
+  hipLaunchKernelGGL(insp_head_kernel, dim3(HEAD_WG), blk, 0, stream, ix, ws, instance, session, n_req);
   hipLaunchKernelGGL(insp_classify_kernel, dim3(INS_WG), blk, 0, stream, ix, pv, ws, instance, session, epoch);
-  hipLaunchKernelGGL(insp_size_kernel, dim3(1), blk, 0, stream, ws);
   hipLaunchKernelGGL(insp_bcount_kernel, chunks, blk, 0, stream, ix, ws);
   hipLaunchKernelGGL(insp_bscan_kernel, dim3(NREG), dim3(SCAN_T), 0, stream, ws);
-  hipLaunchKernelGGL(insp_size2_kernel, dim3(grid_for(ws.n_dedupe)), blk, 0, stream, ws);
   hipLaunchKernelGGL(insp_bscatter_kernel, chunks, blk, 0, stream, ix, ws);
-  hipLaunchKernelGGL(insp_bdedupe_kernel, flat, dim3(DD_T), 0, stream, ws);
-  hipLaunchKernelGGL(insp_check_kernel, dim3(1), blk, 0, stream, ix, ws);
+  hipLaunchKernelGGL(insp_bdedupe_kernel, dim3(DEDUPE_WG), dim3(DD_T), 0, stream, ix, ws);
   hipLaunchKernelGGL(insp_place_kernel, dim3(PLACE_WG), blk, 0, stream, ix, pv, ws, session, epoch);
   hipLaunchKernelGGL(spill_kernel, dim3(64), blk, 0, stream, ix, ws.trig, &ws.hdr->n_trig, &ws.hdr->abort,
                      nullptr, nullptr, ws.np);

@@ -18,7 +18,7 @@
 //   scatter   each chunk again, one tile at a time: regrouped by region in LDS, then
 //             (key, request) written as one contiguous run per region at its region-order
 //             position, and the inverse index block -> position
-//   probe     a fixed grid of FLAT_WG workgroups walks the region-ordered keys; all
+//   probe     a fixed grid of PROBE_WG workgroups walks the region-ordered keys; all
 //             workgroups advance through the regions together, so the live window slides
 //             through the table.  One 128-byte bucket read (keys and values at once) per
 //             bucket of the key's chain -- its home bucket, and when that is full the
@@ -125,33 +125,50 @@ __global__ __launch_bounds__(TB) void part_count_kernel(DevIndex ix, ProbeView p
 }
 
 // Workgroup g: first position of region g (the blocks of every region before it, summed
-// over all chunks), then the running offsets of its chunks, and its own total.
-static_assert(PART_WG == 4 * TB, "each thread of the scan covers 4 chunks");
-__global__ __launch_bounds__(TB) void part_scan_kernel(ProbeView pv) {
-  __shared__ uint32_t wt[TB / 64];
-  __shared__ unsigned long long red[TB / 64];
-  const int g = blockIdx.x, t = threadIdx.x;
-  unsigned long long v = 0;
+// over all chunks), then the running offsets of its chunks, and its own total.  One thread
+// per chunk, whose counts it reads as whole 16-byte words, all requested at once: the kernel
+// is one round trip and two reductions (10.5 -> 5.2 us).
+static_assert(PART_WG <= 1024 && NREG % 4 == 0, "one chunk per thread, its counts in 16-byte words");
+__global__ __launch_bounds__(PART_WG) void part_scan_kernel(ProbeView pv) {
+  __shared__ uint32_t wt[PART_WG / 64];
+  __shared__ unsigned long long red[PART_WG / 64];
+  const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t c[NREG];
+  const uint4 *row = reinterpret_cast<const uint4 *>(pv.hist + uint64_t(t) * NREG);
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    for (int i = 0; i < g; ++i) v += pv.hist[uint64_t(4 * t + j) * NREG + i];
+  for (int i = 0; i < NREG / 4; ++i) {
+    const uint4 v = row[i];
+    c[4 * i] = v.x;
+    c[4 * i + 1] = v.y;
+    c[4 * i + 2] = v.z;
+    c[4 * i + 3] = v.w;
+  }
+  unsigned long long before = 0;  // this chunk's blocks of earlier regions
+  uint32_t mine = 0;              // and of this one
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  if ((t & 63) == 0) red[t >> 6] = v;
+  for (int i = 0; i < NREG; ++i) {
+    before += i < g ? c[i] : 0u;
+    mine = i == g ? c[i] : mine;
+  }
+  uint32_t x = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+    before += __shfl_xor(before, d, 64);
+  }
+  if (lane == 63) wt[wave] = x;
+  if (lane == 0) red[wave] = before;
   __syncthreads();
   unsigned long long off = 0;
+  uint32_t pre = x - mine, total = 0;
 #pragma unroll
-  for (int i = 0; i < TB / 64; ++i) off += red[i];
-  uint32_t c[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) c[j] = pv.hist[uint64_t(4 * t + j) * NREG + g];
-  uint32_t total;
-  uint32_t acc = wg_exclusive_scan(c[0] + c[1] + c[2] + c[3], wt, &total);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    pv.base[uint64_t(4 * t + j) * NREG + g] = off + acc;
-    acc += c[j];
+  for (int i = 0; i < PART_WG / 64; ++i) {
+    off += red[i];
+    pre += i < wave ? wt[i] : 0u;
+    total += wt[i];
   }
+  pv.base[uint64_t(t) * NREG + g] = off + pre;
   if (t == 0) pv.hdr->tot[g] = total;
   if (g == NREG - 1 && t == 0) pv.hdr->n = pv.hdr->err ? 0 : off + total;
 }
@@ -653,7 +670,7 @@ int partition_tail(const DevIndex &ix, ProbeView &pv, const uint64_t *keys, cons
   if (n_req > 0)
     hipLaunchKernelGGL(req_of_kernel, dim3(n_req), dim3(64), 0, stream, pv, blk_off, n_req, int64_t(n));
   if (!counted) hipLaunchKernelGGL(part_count_kernel, dim3(PART_WG), dim3(TB), 0, stream, ix, pv, keys, n);
-  hipLaunchKernelGGL(part_scan_kernel, dim3(NREG), dim3(TB), 0, stream, pv);
+  hipLaunchKernelGGL(part_scan_kernel, dim3(NREG), dim3(PART_WG), 0, stream, pv);
   hipLaunchKernelGGL(part_scatter_kernel, dim3(PART_WG), dim3(TB), 0, stream, ix, pv, keys, n);
   return hip_rc(hipGetLastError());
 }
