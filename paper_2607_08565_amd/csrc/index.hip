@@ -1633,137 +1633,75 @@ __global__ __launch_bounds__(SI_T) void ins_small_kernel(DevIndex ix, ProbeView 
 // ---------------------------------------------------------------------------------
 // Evict / dump
 // ---------------------------------------------------------------------------------
-// All live entries (plain and member slots; headers are not entries): each round's tile of
-// TB x GB buckets in slot order, the tiles wherever their round's reservation fell.
-// Each thread takes GB consecutive buckets per round; a workgroup reserves its round's
-// output with one atomic (one per entry made a single counter the bottleneck).  Optional
-// outputs: each entry's slot (bit 63 set for a member slot) and the number of tombstones,
-// added once per wavefront at the end; with hist1, the eviction's second selection digit
-// (the epoch's low 11 bits) is counted over the entries whose first digit is 0, in LDS,
-// each thread folding runs of its last EC distinct epochs in registers first.
-constexpr int GB = 2;
-constexpr int EC = 4;
-__global__ __launch_bounds__(TB) void gather_kernel(DevIndex ix, uint64_t *keys, uint64_t *vals, uint64_t *pos,
-                                                    unsigned long long *count, unsigned long long *n_tomb,
-                                                    unsigned long long *hist1, uint64_t *toff, uint64_t cap) {
-  __shared__ uint32_t wt[TB / 64];
+// A tile of the table, TILE buckets: lane l of a wavefront takes slot l of its 8 buckets, so
+// that a load instruction covers eight 64-byte runs; a thread of NT holds TILE * SLOTS / NT
+// slots, their loads issued together, from one scalar base (an address each would take as
+// many registers as the data).
+constexpr int TILE = 512;
+template <int NT>
+__device__ __forceinline__ uint32_t tile_word(int u) {  // its key's word in the tile
+  const uint32_t i = uint32_t(u * NT) + threadIdx.x;
+  return (i / SLOTS) * BUCKET_WORDS + i % SLOTS;
+}
+__device__ __forceinline__ uint32_t tile_words(const DevIndex &ix, uint64_t b0) {
+  return uint32_t(ix.n_buckets - b0 < TILE ? ix.n_buckets - b0 : TILE) * BUCKET_WORDS;
+}
+template <int NT>
+__device__ __forceinline__ void load_tile(const DevIndex &ix, uint64_t b0, uint64_t *k, uint64_t *v) {
+  const uint64_t *base = ix.slots + b0 * BUCKET_WORDS;
+  const uint32_t nw = tile_words(ix, b0);
+#pragma unroll
+  for (int u = 0; u < TILE * SLOTS / NT; ++u) {
+    const uint32_t w = tile_word<NT>(u), at = w < nw ? w : 0;
+    k[u] = base[at];
+    v[u] = base[at + SLOTS];
+    if (w >= nw) k[u] = KEY_EMPTY;
+  }
+}
+__device__ __forceinline__ bool is_entry(uint64_t k, uint64_t v) {  // a plain or member slot
+  return k != KEY_EMPTY && k != KEY_TOMB && val_kind(v) != HEADER;
+}
+
+// All live entries for the dump, which sorts them: a workgroup reserves its tile's output
+// with one atomic (one per entry made a single counter the bottleneck).
+__global__ __launch_bounds__(TB) void gather_kernel(DevIndex ix, uint64_t *keys, uint64_t *vals,
+                                                    unsigned long long *count, uint64_t cap) {
+  constexpr int GS = TILE * SLOTS / TB;
+  static_assert(GS * (TB / 64) == 64, "a round's ballots: one per lane of the scan");
+  __shared__ uint32_t pre[64];
   __shared__ unsigned long long wg_base;
-  __shared__ uint32_t h1[2048];
-  __shared__ uint64_t stage[TB * GB * SLOTS];  // one round's entries, one array at a time
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t per_round = uint64_t(TB) * GB;
-  uint32_t tombs = 0, d0_or = 0, d0_and = ~0u;  // the entries' first selection digit (epoch >> 11)
-  uint32_t ce[EC], cn[EC];                       // cached epochs (low bits) and their counts
+  for (uint64_t b0 = uint64_t(blockIdx.x) * TILE; b0 < ix.n_buckets; b0 += uint64_t(gridDim.x) * TILE) {
+    uint64_t k[GS], v[GS], live[GS];
+    load_tile<TB>(ix, b0, k, v);
 #pragma unroll
-  for (int j = 0; j < EC; ++j) cn[j] = ce[j] = 0;
-  if (hist1) {
-    for (int b = threadIdx.x; b < 2048; b += TB) h1[b] = 0;
+    for (int u = 0; u < GS; ++u) {
+      live[u] = __ballot(is_entry(k[u], v[u]));
+      if (lane == 0) pre[u * (TB / 64) + wave] = uint32_t(__popcll(live[u]));
+    }
     __syncthreads();
-  }
-  for (uint64_t b0 = uint64_t(blockIdx.x) * per_round; b0 < ix.n_buckets; b0 += uint64_t(gridDim.x) * per_round) {
-    uint32_t live = 0;  // bit s + SLOTS * g: slot s of bucket g is an entry
-    uint64_t k[GB][SLOTS], v[GB][SLOTS];
+    if (wave == 0) {  // exclusive prefix of the ballots' counts
+      const uint32_t c = pre[lane];
+      uint32_t x = c;
 #pragma unroll
-    for (int g = 0; g < GB; ++g) {
-      const uint64_t b = b0 + uint64_t(threadIdx.x) * GB + g;
-      const ulonglong2 *p = reinterpret_cast<const ulonglong2 *>(ix.slots + (b < ix.n_buckets ? b : 0) * BUCKET_WORDS);
-#pragma unroll
-      for (int i = 0; i < SLOTS / 2; ++i) {
-        const ulonglong2 kk = p[i], vv = p[SLOTS / 2 + i];
-        k[g][2 * i] = kk.x;
-        k[g][2 * i + 1] = kk.y;
-        v[g][2 * i] = vv.x;
-        v[g][2 * i + 1] = vv.y;
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
       }
-#pragma unroll
-      for (int s = 0; s < SLOTS; ++s) {
-        if (b < ix.n_buckets && k[g][s] != KEY_EMPTY && k[g][s] != KEY_TOMB && val_kind(v[g][s]) != HEADER) {
-          live |= 1u << (g * SLOTS + s);
-          const uint32_t ep = val_epoch(v[g][s]);
-          d0_or |= ep >> 11;
-          d0_and &= ep >> 11;
-          if (hist1 && (ep >> 11) == 0) {
-            bool hit = false;
-#pragma unroll
-            for (int j = 0; j < EC; ++j)
-              if (!hit && (cn[j] == 0 || ce[j] == ep)) {
-                ce[j] = ep;
-                ++cn[j];
-                hit = true;
-              }
-            if (!hit) atomicAdd(&h1[ep], 1u);
-          }
-        }
-        tombs += b < ix.n_buckets && k[g][s] == KEY_TOMB;
-      }
-    }
-    // exclusive prefix of the live counts over the workgroup
-    const uint32_t c = __popc(live);
-    uint32_t x = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d, 64);
-      if (lane >= d) x += y;
-    }
-    if (lane == 63) wt[wave] = x;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < TB / 64; ++w) {
-      before += w < wave ? wt[w] : 0;
-      total += wt[w];
-    }
-    if (threadIdx.x == 0) {
-      wg_base = total ? atomicAdd(count, (unsigned long long)total) : 0;
-      if (toff) toff[b0 / per_round] = (uint64_t(wg_base) << 16) | total;  // rounds land anywhere
+      pre[lane] = x - c;
+      if (lane == 63) wg_base = x ? atomicAdd(count, (unsigned long long)x) : 0;
     }
     __syncthreads();
-    // the round's entries go out through LDS, one array at a time, so that consecutive
-    // lanes write consecutive words (a lane writing its own entries straight out scatters
-    // every store instruction over 64 lines)
-    const uint32_t lo = before + x - c;  // this thread's first entry in the round
     const unsigned long long base = wg_base;
-    const uint32_t n_out = base >= cap ? 0u : (cap - base < total ? uint32_t(cap - base) : total);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      if (a == 2 && !pos) break;  // uniform
-      uint32_t j = lo;
-#pragma unroll
-      for (int g = 0; g < GB; ++g)
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-          if ((live >> (g * SLOTS + s)) & 1)
-            stage[j++] = a == 0 ? k[g][s]
-                                : (a == 1 ? val_dump(v[g][s])
-                                          : ((b0 + uint64_t(threadIdx.x) * GB + g) * SLOTS + s) |
-                                                (uint64_t(val_kind(v[g][s]) == MEMBER) << 63));
-      __syncthreads();
-      uint64_t *out = a == 0 ? keys : (a == 1 ? vals : pos);
-      for (uint32_t i = threadIdx.x; i < n_out; i += TB) out[base + i] = stage[i];
-      __syncthreads();  // stage, wt and wg_base are reused
+    for (int u = 0; u < GS; ++u) {
+      const unsigned long long at = base + pre[u * (TB / 64) + wave] + __popcll(live[u] & ((uint64_t(1) << lane) - 1));
+      if (((live[u] >> lane) & 1) && at < cap) {
+        keys[at] = k[u];
+        vals[at] = val_dump(v[u]);
+      }
     }
-  }
-  if (hist1) {
-#pragma unroll
-    for (int j = 0; j < EC; ++j)
-      if (cn[j]) atomicAdd(&h1[ce[j]], cn[j]);
-    __syncthreads();
-    for (int b = threadIdx.x; b < 2048; b += TB)
-      if (h1[b]) atomicAdd(&hist1[b], (unsigned long long)h1[b]);
-  }
-  if (n_tomb) {  // n_tomb[1], n_tomb[2]: OR and AND of the first selection digit
-    uint32_t t = tombs, o = d0_or, a = d0_and;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      t += __shfl_xor(t, d, 64);
-      o |= __shfl_xor(o, d, 64);
-      a &= __shfl_xor(a, d, 64);
-    }
-    if (lane == 0) {
-      if (t) atomicAdd(n_tomb, (unsigned long long)t);
-      atomicOr(n_tomb + 1, (unsigned long long)o);
-      atomicAnd(n_tomb + 2, (unsigned long long)a);
-    }
+    __syncthreads();  // pre and wg_base are reused
   }
 }
 
@@ -1781,20 +1719,29 @@ __device__ int64_t find_header(const DevIndex &ix, uint64_t key) {
   return -1;
 }
 
-// Eviction as a selection: the m-th smallest entry under (epoch, key, instance) is found
-// digit by digit -- epoch in two 11-bit digits, the key in five 12-bit digits and a last
-// 4-bit part joined with the instance's top 6 bits, then the instance's low 10 bits --
-// each digit fixed by one histogram pass over the entries that share the digits fixed
-// so far.  Entries up to and including that bin under the lexicographic digit order are
-// evicted, and the table is rebuilt from the entries above it.  Entries are in
-// the dump's value format (instance << 48 | epoch << 24 | session).
+// Eviction as a selection: the cut is the m-th smallest entry under (epoch, key, instance),
+// and every entry up to it leaves.  That order as two words, of a key and a value in the
+// dump's format (instance << 48 | epoch << 24 | session):
+struct SelCut {
+  uint64_t hi, lo;
+};
+__host__ __device__ __forceinline__ uint64_t sel_hi(uint64_t key, uint32_t epoch) {
+  return (uint64_t(epoch) << 40) | (key >> 24);
+}
+__device__ __forceinline__ bool sel_leaves(uint64_t key, uint64_t hi, uint32_t inst, const SelCut &c) {
+  return hi < c.hi || (hi == c.hi && (((key & 0xFFFFFF) << 16) | inst) <= c.lo);
+}
+// The entries near the cut are settled digit by digit -- epoch in two 11-bit digits, the key
+// in five 12-bit digits and a last 4-bit part joined with the instance's top 6 bits, then the
+// instance's low 10 bits -- each digit fixed by one histogram pass over the entries that
+// share the digits fixed so far, until the whole of a bin goes.
 constexpr int SEL_LEVELS = 9;
 constexpr int SEL_BINS = 4096;
 struct SelPrefix {
   int level;  // digits fixed so far
   uint32_t digit[SEL_LEVELS];
 };
-__device__ __forceinline__ uint32_t sel_digit(uint64_t key, uint64_t v, int l) {
+__host__ __device__ __forceinline__ uint32_t sel_digit(uint64_t key, uint64_t v, int l) {
   const uint32_t ep = dump_epoch(v), inst = dump_inst(v);
   switch (l) {
     case 0: return ep >> 11;
@@ -1808,111 +1755,457 @@ __device__ __forceinline__ uint32_t sel_digit(uint64_t key, uint64_t v, int l) {
     default: return inst & 0x3FFu;
   }
 }
-// -1: below the prefix (evicted), 0: on it, 1: above it
-__device__ __forceinline__ int sel_cmp(uint64_t key, uint64_t v, const SelPrefix &p) {
-  for (int l = 0; l < p.level; ++l) {
-    const uint32_t d = sel_digit(key, v, l);
-    if (d != p.digit[l]) return d < p.digit[l] ? -1 : 1;
-  }
-  return 0;
+__device__ __forceinline__ bool sel_on(uint64_t key, uint64_t v, const SelPrefix &p) {
+  for (int l = 0; l < p.level; ++l)
+    if (sel_digit(key, v, l) != p.digit[l]) return false;
+  return true;
 }
-// Rebuild, second pass: the entries the tile pass left (tile k's listed by gathered index
-// in list[seg, seg + count), toff[k] = seg << 16 | count), one per thread (all survivors:
-// the tile pass skips evicted entries).  Claims that trigger a key's conversion or are
-// deferred are queued by gathered index for the spill and deferred passes.
+// The largest (epoch, key, instance) on the prefix, but not past `hi`, the end of the range
+// that the entries were taken from: the prefix may reach beyond it.
+__host__ __device__ inline SelCut sel_cut(const SelPrefix &p, uint64_t hi) {
+  uint64_t d[SEL_LEVELS];
+  for (int l = 0; l < SEL_LEVELS; ++l) d[l] = l < p.level ? p.digit[l] : l == 1 ? 0x7FF : l >= 7 ? 0x3FF : 0xFFF;
+  const uint64_t key =
+      (d[2] << 52) | (d[3] << 40) | (d[4] << 28) | (d[5] << 16) | (d[6] << 4) | (d[7] >> 6);
+  const SelCut c = {sel_hi(key, uint32_t((d[0] << 11) | d[1])),
+                    ((key & 0xFFFFFF) << 16) | ((d[7] & 63) << 10) | d[8]};
+  return c.hi > hi ? SelCut{hi, ~uint64_t(0)} : c;
+}
+
+// The eviction's counters, in its workspace.
+struct EvictState {
+  unsigned long long n_entries;               // as the header has it
+  unsigned long long lo, hi;                  // the range of sel_hi that the scan copies out
+  unsigned long long n_in, n_fin;             // copied by the scan; of these, for the last passes
+  unsigned long long n_left, n_trig, n_def;   // the rebuild's lists
+  SelCut cut;                                 // once a kernel decides it
+};
+// The scan's counters: entries, tombstones, entries below the range.  One atomic takes 12 ns
+// on one address, so the workgroups spread over EV_LANES lines, which the host adds up.
+constexpr int EV_LANES = 8, EV_LINE = 16;
+
+// Entries of a wavefront collected in LDS and written out some hundreds at a time, each
+// batch with one reservation.
+constexpr int STAGE = 512;
+struct WaveStage {
+  uint64_t k[TB / 64][STAGE], v[TB / 64][STAGE];
+  uint32_t n[TB / 64];
+  unsigned long long base;
+};
+__device__ __forceinline__ void stage_push(WaveStage &st, uint32_t &n, bool mine, uint64_t k, uint64_t v,
+                                           unsigned long long *count, uint64_t *ck, uint64_t *cv, uint64_t cap) {
+  const uint64_t b = __ballot(mine);
+  if (!b) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t c = uint32_t(__popcll(b));
+  if (n + c > STAGE) {
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(count, (unsigned long long)n);
+    at = __shfl(at, 0, 64);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (uint32_t i = lane; i < n; i += 64)
+      if (at + i < cap) {
+        ck[at + i] = st.k[wave][i];
+        cv[at + i] = st.v[wave][i];
+      }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    n = 0;
+  }
+  if (mine) {
+    const uint32_t at = n + uint32_t(__popcll(b & ((uint64_t(1) << lane) - 1)));
+    st.k[wave][at] = k;
+    st.v[wave][at] = v;
+  }
+  n += c;
+}
+__device__ __forceinline__ void stage_flush(WaveStage &st, uint32_t n, unsigned long long *count, uint64_t *ck,
+                                            uint64_t *cv, uint64_t cap) {  // the whole workgroup
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) st.n[wave] = n;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+  for (int w = 0; w < TB / 64; ++w) {
+    if (w < wave) before += st.n[w];
+    total += st.n[w];
+  }
+  if (threadIdx.x == 0) st.base = total ? atomicAdd(count, (unsigned long long)total) : 0;
+  __syncthreads();
+  const uint64_t at = st.base + before;
+  for (uint32_t i = lane; i < n; i += 64)
+    if (at + i < cap) {
+      ck[at + i] = st.k[wave][i];
+      cv[at + i] = st.v[wave][i];
+    }
+}
+
+// The bin of the 4,096 in h that holds the left-th smallest (1-based), by a whole workgroup
+// of FIN_T: its index (SEL_BINS: none), the count below it and its own.
+constexpr int FIN_T = 1024;
+struct BinPick {
+  uint32_t wt[FIN_T / 64];
+  uint32_t bin, below, count;
+};
+__device__ __forceinline__ void pick_bin(const uint32_t *h, uint32_t left, BinPick &s) {
+  constexpr int PER = SEL_BINS / FIN_T;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t c[PER], sum = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    c[j] = h[t * PER + j];
+    sum += c[j];
+  }
+  uint32_t x = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) s.wt[wave] = x;
+  if (t == 0) s.bin = SEL_BINS;
+  __syncthreads();
+  uint32_t below = x - sum;
+  for (int w = 0; w < wave; ++w) below += s.wt[w];
+  if (below < left && left <= below + sum) {  // one thread
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (below < left && left <= below + c[j]) {
+        s.bin = uint32_t(t * PER + j);
+        s.below = below;
+        s.count = c[j];
+      }
+      below += c[j];
+    }
+  }
+  __syncthreads();
+}
+
+// Where the cut lies, roughly, from a sample: EV_SAMPLE buckets evenly over the table (keys
+// are hashes, but a key's home bucket follows its top bits).  It also clears the counters.
+// Without a sample the range is everything.
+constexpr int EV_SAMPLE = 4096;
+__global__ __launch_bounds__(TB) void evict_sample_kernel(DevIndex ix, EvictState *st, unsigned long long *counts,
+                                                          uint64_t *sample) {
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      EvictState z{};
+      z.n_entries = ix.hdr->n_entries;
+      z.hi = ~0ull;
+      *st = z;
+    }
+    if (threadIdx.x < EV_LANES * EV_LINE) counts[threadIdx.x] = 0;
+  }
+  if (!sample) return;
+  const uint32_t i = blockIdx.x * TB + threadIdx.x;  // EV_SAMPLE * SLOTS threads
+  const uint64_t b = (uint64_t(i / SLOTS) * ix.n_buckets) / EV_SAMPLE;
+  const uint64_t *p = ix.slots + b * BUCKET_WORDS + i % SLOTS;
+  const uint64_t k = p[0], v = p[SLOTS];
+  sample[i] = is_entry(k, v) ? sel_hi(k, val_epoch(v)) : ~uint64_t(0);
+}
+// The range for the scan: from the bin of the sample's order statistic six standard
+// deviations below the cut's expected rank to the bin of the one as far above it (and 16 on
+// each side, for entries of one key that lie together).  A range that misses the cut shows
+// in the scan's counts.  One workgroup, the sample in registers, radix digits in LDS.
+__global__ __launch_bounds__(FIN_T) void evict_range_kernel(const uint64_t *__restrict__ sample, uint32_t frac_num,
+                                                            uint32_t frac_den, EvictState *st) {
+  constexpr int PER = EV_SAMPLE * SLOTS / FIN_T;
+  __shared__ uint32_t h[SEL_BINS];
+  __shared__ BinPick bp;
+  __shared__ unsigned long long s_or, s_and;
+  __shared__ uint32_t s_n;
+  const int t = threadIdx.x;
+  uint64_t x[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) x[u] = sample[u * FIN_T + t];
+  if (t == 0) {
+    s_or = s_n = 0;
+    s_and = ~0ull;
+  }
+  __syncthreads();
+  uint64_t o = 0, a = ~uint64_t(0);
+  uint32_t c = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (x[u] != ~uint64_t(0)) {
+      o |= x[u];
+      a &= x[u];
+      ++c;
+    }
+  atomicOr(&s_or, (unsigned long long)o);
+  atomicAnd(&s_and, (unsigned long long)a);
+  atomicAdd(&s_n, c);
+  __syncthreads();
+  const uint32_t n = s_n;
+  if (n == 0) return;  // the range stays everything
+  const uint64_t diff = s_or ^ s_and;
+  const double q = double(frac_num) / double(frac_den), r = q * double(n);
+  const double dev = 6.0 * sqrt(double(n) * q * (1.0 - q)) + 16.0;
+  for (int side = 0; side < 2; ++side) {
+    const double rr = side ? r + dev + 1.0 : r - dev;
+    if (rr < 1.0 || rr > double(n)) continue;  // open on this side
+    uint32_t left = uint32_t(rr);
+    int shift = diff ? 64 - __clzll((long long)diff) : 0;  // bits below are not fixed yet (at most 62)
+    uint64_t pre = s_or >> shift;
+    uint32_t on = n;
+    while (shift > 0 && on > 8) {
+      const int w = shift < 12 ? shift : 12;
+      for (int b = t; b < SEL_BINS; b += FIN_T) h[b] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (x[u] != ~uint64_t(0) && (x[u] >> shift) == pre)
+          atomicAdd(&h[uint32_t(x[u] >> (shift - w)) & ((1u << w) - 1u)], 1u);
+      __syncthreads();
+      pick_bin(h, left, bp);
+      left -= bp.below;
+      on = bp.count;
+      shift -= w;
+      pre = (pre << w) | bp.bin;
+      __syncthreads();
+    }
+    if (t == 0) {
+      if (side) st->hi = ((pre + 1) << shift) - 1;
+      else st->lo = pre << shift;
+    }
+  }
+}
+
+// The one pass that decides: the whole table read once, its entries and tombstones counted,
+// those below the range counted and those in it copied out.  Bound by the read of 128 bytes
+// a bucket: 50M entries in 9.5M buckets 238 us, 5.1 TB/s.  (Gathering every entry with its
+// slot and selecting over the gathered arrays moved those bytes four times: 851 us and two
+// passes of 229 to 468 us.)
+__global__ __launch_bounds__(TB) void evict_scan_kernel(DevIndex ix, EvictState *st, unsigned long long *counts,
+                                                        uint64_t *ck, uint64_t *cv, uint64_t cap) {
+  __shared__ WaveStage stage;
+  __shared__ uint32_t wc[TB / 64][3];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t lo = st->lo, hi = st->hi;
+  constexpr int GS = TILE * SLOTS / TB;
+  uint32_t live = 0, tombs = 0, below = 0, staged = 0;
+  for (uint64_t b0 = uint64_t(blockIdx.x) * TILE; b0 < ix.n_buckets; b0 += uint64_t(gridDim.x) * TILE) {
+    uint64_t k[GS], v[GS];
+    load_tile<TB>(ix, b0, k, v);
+#pragma unroll
+    for (int u = 0; u < GS; ++u) {
+      const bool e = is_entry(k[u], v[u]);
+      const uint64_t a = sel_hi(k[u], val_epoch(v[u]));
+      live += e;
+      tombs += k[u] == KEY_TOMB;
+      below += e && a < lo;
+      stage_push(stage, staged, e && a >= lo && a <= hi, k[u], val_dump(v[u]), &st->n_in, ck, cv, cap);
+    }
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    live += __shfl_xor(live, d, 64);
+    tombs += __shfl_xor(tombs, d, 64);
+    below += __shfl_xor(below, d, 64);
+  }
+  if (lane == 0) {
+    wc[wave][0] = live;
+    wc[wave][1] = tombs;
+    wc[wave][2] = below;
+  }
+  stage_flush(stage, staged, &st->n_in, ck, cv, cap);
+  if (threadIdx.x < 3) {
+    unsigned long long x = 0;
+    for (int w = 0; w < TB / 64; ++w) x += wc[w][threadIdx.x];
+    if (x) atomicAdd(&counts[(blockIdx.x % EV_LANES) * EV_LINE + threadIdx.x], x);
+  }
+}
+
+// One selection pass: the histogram of the next digit over the entries on the prefix.
+__global__ __launch_bounds__(TB) void sel_hist_kernel(const uint64_t *__restrict__ keys,
+                                                      const uint64_t *__restrict__ vals, uint64_t n, SelPrefix p,
+                                                      unsigned long long *hist) {
+  __shared__ uint32_t h[SEL_BINS];
+  for (int b = threadIdx.x; b < SEL_BINS; b += TB) h[b] = 0;
+  __syncthreads();
+  const uint64_t stride = uint64_t(gridDim.x) * TB;
+  for (uint64_t i = uint64_t(blockIdx.x) * TB + threadIdx.x; i < n; i += stride) {
+    const uint64_t k = keys[i], v = vals[i];
+    if (sel_on(k, v, p)) atomicAdd(&h[sel_digit(k, v, p.level)], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < SEL_BINS; b += TB)
+    if (h[b]) atomicAdd(&hist[b], (unsigned long long)h[b]);
+}
+
+// The entries on the prefix, few enough for one workgroup, copied out for it.
+__global__ __launch_bounds__(TB) void sel_copy_kernel(const uint64_t *__restrict__ keys,
+                                                      const uint64_t *__restrict__ vals, uint64_t n, SelPrefix p,
+                                                      unsigned long long *count, uint64_t *ck, uint64_t *cv,
+                                                      uint64_t cap) {
+  __shared__ WaveStage stage;
+  uint32_t staged = 0;
+  const uint64_t stride = uint64_t(gridDim.x) * TB;
+  for (uint64_t i0 = uint64_t(blockIdx.x) * TB; i0 < n; i0 += stride) {  // whole wavefronts iterate together
+    const uint64_t i = i0 + threadIdx.x;
+    const uint64_t k = keys[i < n ? i : 0], v = vals[i < n ? i : 0];
+    stage_push(stage, staged, i < n && sel_on(k, v, p), k, v, count, ck, cv, cap);
+  }
+  stage_flush(stage, staged, count, ck, cv, cap);
+}
+
+// The selection's last passes over at most SEL_FIN entries, by one workgroup and without the
+// host (a pass with the host in it costs 25 us): each remaining digit's histogram in LDS and
+// its bin, until the whole bin goes; the cut is left in st.  Passes read the entries in
+// rounds of FIN_U per thread, loads issued together; once FIN_L or fewer are on the prefix
+// they are kept in LDS.  n_c, when given, is the number that was copied out: it has to be n.
+constexpr uint64_t SEL_FIN = uint64_t(1) << 16;
+constexpr int FIN_U = 8, FIN_L = 1024;
+__global__ __launch_bounds__(FIN_T) void sel_finish_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
+                                                           const uint64_t *__restrict__ vals, uint64_t n, SelPrefix p,
+                                                           unsigned long long rem, unsigned long long on_prefix,
+                                                           const unsigned long long *n_c, EvictState *st) {
+  __shared__ SelPrefix sp;
+  __shared__ uint32_t h[SEL_BINS];
+  __shared__ uint64_t lk[FIN_L], lv[FIN_L];
+  __shared__ BinPick bp;
+  __shared__ uint32_t n_list;
+  static_assert(FIN_L <= FIN_T, "one listed entry per thread");
+  const int t = threadIdx.x;
+  if (t == 0) {
+    sp = p;
+    n_list = 0;
+  }
+  const bool whole = !n_c || *n_c == n;
+  int level = p.level;
+  uint32_t left = uint32_t(rem), on = uint32_t(on_prefix);  // at most SEL_FIN
+  bool listed = false;
+  while (whole && level < SEL_LEVELS && left < on) {
+    for (int b = t; b < SEL_BINS; b += FIN_T) h[b] = 0;
+    __syncthreads();
+    if (listed) {
+      if (uint32_t(t) < n_list && sel_on(lk[t], lv[t], sp)) atomicAdd(&h[sel_digit(lk[t], lv[t], level)], 1u);
+    } else {
+      for (uint64_t i0 = 0; i0 < n; i0 += FIN_T * FIN_U) {
+        uint64_t k[FIN_U], v[FIN_U];
+#pragma unroll
+        for (int u = 0; u < FIN_U; ++u) {
+          const uint64_t i = i0 + u * FIN_T + t;
+          k[u] = keys[i < n ? i : 0];
+          v[u] = vals[i < n ? i : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < FIN_U; ++u) {
+          if (i0 + u * FIN_T + t >= n || !sel_on(k[u], v[u], sp)) continue;
+          atomicAdd(&h[sel_digit(k[u], v[u], level)], 1u);
+          if (on <= FIN_L) {
+            const uint32_t at = atomicAdd(&n_list, 1u);
+            if (at < FIN_L) {
+              lk[at] = k[u];
+              lv[at] = v[u];
+            }
+          }
+        }
+      }
+      listed = on <= FIN_L;
+    }
+    __syncthreads();
+    pick_bin(h, left, bp);
+    if (bp.bin == SEL_BINS) break;  // fewer entries on the prefix than counted before
+    left -= bp.below;
+    on = bp.count;
+    ++level;
+    if (t == 0) {
+      sp.digit[level - 1] = bp.bin;
+      sp.level = level;
+    }
+    __syncthreads();
+  }
+  if (t == 0) {
+    if (!whole || left != on) set_status(ix.hdr, SMETRIC_EINTERNAL);  // the full tuple is unique
+    st->cut = sel_cut(sp, st->hi);
+  }
+}
+
+// Rebuild, second pass: the entries the tile pass left, one per thread (all survivors).
+// Claims that trigger a key's conversion or are deferred are queued by their place in the
+// list for the spill and deferred passes.
 __global__ __launch_bounds__(TB) void rebuild_claim_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
-                                                           const uint64_t *__restrict__ vals, const uint64_t *list,
-                                                           const uint64_t *__restrict__ toff, uint64_t n_tiles,
-                                                           uint64_t *trig, unsigned long long *n_trig, uint64_t *def,
+                                                           const uint64_t *__restrict__ vals,
+                                                           const unsigned long long *n_left, uint64_t *trig,
+                                                           unsigned long long *n_trig, uint64_t *def,
                                                            unsigned long long *n_def, uint64_t cap) {
-  for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)  // whole workgroups iterate together
-  for (uint32_t i0 = 0; i0 < uint32_t(toff[tile] & 0xFFFF); i0 += TB) {
-    const uint64_t seg = toff[tile] >> 16;
-    const uint32_t n = uint32_t(toff[tile] & 0xFFFF);
-    const uint32_t i = i0 + threadIdx.x;
+  const uint64_t n = *n_left < cap ? *n_left : cap;
+  for (uint64_t i0 = uint64_t(blockIdx.x) * TB; i0 < n; i0 += uint64_t(gridDim.x) * TB) {
+    const uint64_t i = i0 + threadIdx.x;
     int64_t tk = -1, df = -1;
     if (i < n) {
-      const uint64_t t = list[seg + i];
-      const uint64_t k = keys[t], v = vals[t];
+      const uint64_t k = keys[i], v = vals[i];
       bool trg;
       const int pl = place_new(ix, k, dump_inst(v), dump_epoch(v), dump_session(v), trg, true);
       if (pl == FAILED || pl == REFRESHED) set_status(ix.hdr, SMETRIC_EINTERNAL);  // survivors are distinct
-      else if (pl == DEFERRED) df = int64_t(t);
-      else if (trg) tk = int64_t(t);
+      else if (pl == DEFERRED) df = int64_t(i);
+      else if (trg) tk = int64_t(i);
     }
     append_wave(n_trig, trig, cap, tk);
     append_wave(n_def, def, cap, df);
   }
 }
 
-// Rebuild, first pass: workgroup k writes the whole of the cleared table's tile k (the
-// gather's round of TB x GB buckets), assembled in LDS.  The gather wrote each tile's
-// entries in slot order, so the entries whose old slot lay in the tile are one
-// contiguous run.  The surviving plain entries whose home bucket lies in the tile are
-// placed without a walk: with c(b) of them homed at bucket b, home b's entries take the
-// consecutive slots from S(b) on, S(b) = max(SLOTS b, S(b - 1) + c(b - 1)), i.e. with P
-// the exclusive prefix sum of c, S(b) = P(b) + max over j <= b of (SLOTS j - P(j)).  Every
-// slot from an entry's home bucket up to its own is then taken, as linear probing
+// Rebuild, first pass: workgroup k rewrites the whole of the table's tile k in place, assembled in LDS: the entries above the cut whose home bucket lies in
+// the tile are placed without a walk.  With c(b) of them homed at bucket b, home b's entries
+// take the consecutive slots from S(b) on, S(b) = max(SLOTS b, S(b - 1) + c(b - 1)), i.e.
+// with P the exclusive prefix sum of c, S(b) = P(b) + max over j <= b of (SLOTS j - P(j)).
+// Every slot from an entry's home bucket up to its own is then taken, as linear probing
 // requires, and the class bit of each entry past its home bucket goes into that bucket's
 // mask.  Everything else -- members (a key's plain slots are capped at T + 1 before its
 // conversion, which the claim pass enforces), entries homed in another tile, entries past
-// the tile's last slot -- is listed for the claim pass, which enters it from its home
-// bucket in the written table: tile k's list takes the gathered indexes of its entries'
-// run, left_list[seg, seg + count), and toff[k] becomes seg << 16 | count.
-__global__ __launch_bounds__(TB) void rebuild_tile_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
-                                                          const uint64_t *__restrict__ vals,
-                                                          const uint64_t *__restrict__ pos, uint64_t *toff,
-                                                          SelPrefix cut, uint64_t *left_list) {
-  constexpr int RT = TB * GB;
-  constexpr int PER = RT * SLOTS / TB;  // entries of the run per thread
-  static_assert(RT == 2 * TB, "two buckets per thread in the scans");
+// the tile's last slot -- is copied to the list that the claim pass enters from the home
+// buckets of the written table.  Bound by the table's read and write, 128 bytes a bucket
+// each way, two workgroups' tiles to a compute unit's LDS: a third of 47.5M entries 473 us,
+// 5.1 TB/s (560 us from gathered entries; a workgroup of 256 takes so many registers for its
+// 16 slots a thread that one runs on a compute unit: 1,040 us).
+__global__ __launch_bounds__(TILE) void rebuild_tile_kernel(DevIndex ix, SelCut cut_host, const SelCut *cut_dev,
+                                                          uint64_t *lk, uint64_t *lv, unsigned long long *n_left,
+                                                          uint64_t cap, unsigned long long n_entries) {
+  const SelCut cut = cut_dev ? *cut_dev : cut_host;
+  constexpr int RT = TILE, GS = SLOTS;  // one bucket per thread in the scans, SLOTS slots to place
+  constexpr uint32_t GONE = RT, LEFT = RT + 1;
   __shared__ uint64_t tb[RT * BUCKET_WORDS];  // the tile: keys, then values, per bucket
   __shared__ uint32_t tm[RT];                 // the tile's displacement masks
   __shared__ uint32_t hc[RT];                 // entries homed at each bucket, then S(b)
-  __shared__ uint32_t wsum[TB / 64], wmax[TB / 64];
-  __shared__ uint16_t lo[RT * SLOTS];         // the entries left, as offsets in the run
+  __shared__ uint32_t wsum[RT / 64], wmax[RT / 64];
   __shared__ uint32_t n_lo;
+  __shared__ unsigned long long lo_base;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const uint64_t b_lo = uint64_t(blockIdx.x) * RT;
   const uint64_t nb = ix.n_buckets - b_lo < uint64_t(RT) ? ix.n_buckets - b_lo : uint64_t(RT);
-  const uint64_t seg = toff[blockIdx.x] >> 16;
-  const uint32_t cnt = uint32_t(toff[blockIdx.x] & 0xFFFF);  // <= RT * SLOTS
-  for (int i = t; i < RT * BUCKET_WORDS; i += TB) tb[i] = (i % BUCKET_WORDS) < SLOTS ? KEY_EMPTY : VAL_UNSET;
-  for (int i = t; i < RT; i += TB) tm[i] = hc[i] = 0;
+  if (blockIdx.x == 0 && t == 0) {
+    ix.hdr->n_entries = n_entries;
+    ix.hdr->rec_used = 0;
+  }
+  uint64_t k[GS], v[GS];
+  load_tile<RT>(ix, b_lo, k, v);
+  for (int i = t; i < RT * BUCKET_WORDS; i += RT) tb[i] = (i % BUCKET_WORDS) < SLOTS ? KEY_EMPTY : VAL_UNSET;
+  for (int i = t; i < RT; i += RT) tm[i] = hc[i] = 0;
   if (t == 0) n_lo = 0;
   __syncthreads();
-  // thread t takes entries t + TB u of the run: survivors homed in the tile count
-  // themselves at their home (the count is their rank there), the rest are listed
-  uint64_t k[PER], v[PER];
-  uint32_t home[PER], rank[PER];  // home: offset in the tile, RT when not placed here
-  bool member[PER];
+  // survivors homed in the tile count themselves at their home (the count is their rank
+  // there), the rest are listed
+  uint32_t home[GS], rank[GS];  // home: offset in the tile, or GONE or LEFT (rank: place in the list)
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {  // every load issued before any is used
-    const uint32_t i = uint32_t(u * TB + t), c = i < cnt ? i : 0u;
-    k[u] = keys[seg + c];
-    v[u] = vals[seg + c];
-    member[u] = pos[seg + c] >> 63;
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const uint32_t i = uint32_t(u * TB + t);
-    home[u] = RT;
+  for (int u = 0; u < GS; ++u) {
+    home[u] = GONE;
     rank[u] = 0;
-    if (i < cnt && sel_cmp(k[u], v[u], cut) > 0) {  // survives
+    if (is_entry(k[u], v[u]) && !sel_leaves(k[u], sel_hi(k[u], val_epoch(v[u])), val_inst(v[u]), cut)) {
       const uint64_t h = home_bucket(k[u], ix.n_buckets);
-      if (!member[u] && h >= b_lo && h < b_lo + nb) {
+      if (val_kind(v[u]) != MEMBER && h >= b_lo && h < b_lo + nb) {
         home[u] = uint32_t(h - b_lo);
         rank[u] = atomicAdd(&hc[home[u]], 1u);
       } else {
-        lo[atomicAdd(&n_lo, 1u)] = uint16_t(i);
+        home[u] = LEFT;
+        rank[u] = atomicAdd(&n_lo, 1u);
       }
     }
   }
   __syncthreads();
-  // S(b) over the tile: thread t holds buckets 2t, 2t + 1; exclusive sums P and running
-  // maxima of SLOTS j - P(j) across the workgroup (wavefront scans, then the waves' totals)
-  const uint32_t c0 = hc[2 * t], c1 = hc[2 * t + 1];
-  uint32_t sum = c0 + c1;  // inclusive prefix sum over the threads
+  // S(b) over the tile, thread t holding bucket t: exclusive sums P and running maxima of
+  // SLOTS j - P(j) across the workgroup (wavefront scans, then the waves' totals)
+  const uint32_t c = hc[t];
+  uint32_t sum = c;  // inclusive prefix sum over the threads
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t y = __shfl_up(sum, d, 64);
@@ -1922,10 +2215,8 @@ __global__ __launch_bounds__(TB) void rebuild_tile_kernel(DevIndex ix, const uin
   __syncthreads();
   uint32_t before = 0;
   for (int w = 0; w < wave; ++w) before += wsum[w];
-  const uint32_t p0 = before + sum - c0 - c1, p1 = p0 + c0;  // P(2t), P(2t + 1)
-  int32_t m = int32_t(SLOTS * 2 * t) - int32_t(p0);
-  const int32_t m1 = int32_t(SLOTS * (2 * t + 1)) - int32_t(p1);
-  m = m1 > m ? m1 : m;  // this thread's maximum; then inclusive running maxima
+  const uint32_t pt = before + sum - c;  // P(t)
+  int32_t m = int32_t(SLOTS * t) - int32_t(pt);
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const int32_t y = __shfl_up(m, d, 64);
@@ -1933,42 +2224,40 @@ __global__ __launch_bounds__(TB) void rebuild_tile_kernel(DevIndex ix, const uin
   }
   if (lane == 63) wmax[wave] = uint32_t(m);
   __syncthreads();
-  int32_t mb = INT32_MIN;  // the maximum over the earlier threads
-  for (int w = 0; w < wave; ++w) mb = int32_t(wmax[w]) > mb ? int32_t(wmax[w]) : mb;
-  {
-    const int32_t prev = __shfl_up(m, 1, 64);
-    if (lane > 0 && prev > mb) mb = prev;
-  }
-  const int32_t a0 = int32_t(SLOTS * 2 * t) - int32_t(p0), a1 = int32_t(SLOTS * (2 * t + 1)) - int32_t(p1);
-  const int32_t m0 = a0 > mb ? a0 : mb, m01 = a1 > m0 ? a1 : m0;
-  __syncthreads();  // every c(b) read before S(b) replaces it
-  hc[2 * t] = uint32_t(int32_t(p0) + m0);
-  hc[2 * t + 1] = uint32_t(int32_t(p1) + m01);
+  for (int w = 0; w < wave; ++w) m = int32_t(wmax[w]) > m ? int32_t(wmax[w]) : m;
+  hc[t] = uint32_t(int32_t(pt) + m);  // S(t): only thread t reads c(t)
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    if (home[u] == RT) continue;
+  for (int u = 0; u < GS; ++u) {
+    if (home[u] >= RT) continue;
     const uint32_t at = hc[home[u]] + rank[u];  // slot index in the tile
     if (at >= uint32_t(nb) * SLOTS) {           // past the tile's last slot
-      lo[atomicAdd(&n_lo, 1u)] = uint16_t(u * TB + t);
+      rank[u] = atomicAdd(&n_lo, 1u);
+      home[u] = LEFT;
       continue;
     }
     const uint32_t b = at / SLOTS, s = at % SLOTS;
     tb[b * BUCKET_WORDS + s] = k[u];
-    tb[b * BUCKET_WORDS + SLOTS + s] = make_val(dump_inst(v[u]), PLAIN, dump_epoch(v[u]), dump_session(v[u]));
+    tb[b * BUCKET_WORDS + SLOTS + s] = make_val(val_inst(v[u]), PLAIN, val_epoch(v[u]), val_session(v[u]));
     if (b > home[u]) atomicOr(&tm[home[u]], 1u << (2 * key_cls(k[u]) + (b == home[u] + 1 ? 0 : 1)));
   }
   __syncthreads();
-  const uint32_t n_left = n_lo;
-  for (uint32_t j = t; j < n_left; j += TB) left_list[seg + j] = seg + lo[j];
-  if (t == 0) toff[blockIdx.x] = (seg << 16) | n_left;
-  for (uint64_t i = t; i < nb; i += TB) {
+  if (t == 0) lo_base = n_lo ? atomicAdd(n_left, (unsigned long long)n_lo) : 0;
+  for (uint64_t i = t; i < nb; i += RT) {
     if (MASK_W == 16) reinterpret_cast<uint16_t *>(ix.mask)[b_lo + i] = uint16_t(tm[i]);
     else ix.mask[b_lo + i] = uint8_t(tm[i]);
   }
   ulonglong2 *dst = reinterpret_cast<ulonglong2 *>(ix.slots + b_lo * BUCKET_WORDS);
   const ulonglong2 *src = reinterpret_cast<const ulonglong2 *>(tb);
-  for (uint64_t w = t; w < nb * (BUCKET_WORDS / 2); w += TB) dst[w] = src[w];
+  for (uint64_t w = t; w < nb * (BUCKET_WORDS / 2); w += RT) dst[w] = src[w];
+  __syncthreads();
+  const uint64_t base = lo_base;
+#pragma unroll
+  for (int u = 0; u < GS; ++u)
+    if (home[u] == LEFT && base + rank[u] < cap) {
+      lk[base + rank[u]] = k[u];
+      lv[base + rank[u]] = val_dump(v[u]);
+    }
 }
 
 // Enter the deferred pairs once their keys are converted (or, with the pool exhausted,
@@ -2001,80 +2290,59 @@ __global__ void deferred_kernel(DevIndex ix, const uint64_t *items, const unsign
   }
 }
 
-__global__ void set_counts_kernel(IndexHdr *h, unsigned long long n_entries, int reset_records) {
-  h->n_entries = n_entries;
-  if (reset_records) h->rec_used = 0;
-}
-
-// Eviction in place: the gathered entries at or below the cut become tombstones (a member
-// also leaves its key's bitmap); every other entry keeps its slot.  Tombstones are never
+// Eviction in place: the entries at or below the cut become tombstones (a member also
+// leaves its key's bitmap); every other entry keeps its slot.  Tombstones are never
 // reclaimed by inserts, so the caller rebuilds the table instead once they would pass an
-// eighth of the slots.
-__device__ void tomb_entry(const DevIndex &ix, uint64_t k, uint64_t v, uint64_t ps) {
-  const uint64_t slot = ps & ~(uint64_t(1) << 63);
-  ix.slots[(slot / SLOTS) * BUCKET_WORDS + slot % SLOTS] = KEY_TOMB;
-  if (ps >> 63) {
-    const int64_t h = find_header(ix, k);
-    if (h < 0) {
-      set_status(ix.hdr, SMETRIC_EINTERNAL);
-      return;
+// eighth of the slots.  Values first, and the keys of those alone whose epoch the cut
+// reaches: where few leave, most of the keys' halves of the buckets are not read (5 % of 50M
+// entries: 288 us; 322 us with twice the slots a thread).
+constexpr int TT = 512;
+__global__ __launch_bounds__(TT) void evict_tomb_kernel(DevIndex ix, SelCut cut_host, const SelCut *cut_dev,
+                                                        unsigned long long n_left) {
+  const SelCut cut = cut_dev ? *cut_dev : cut_host;
+  constexpr int GS = TILE * SLOTS / TT;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ix.hdr->n_entries = n_left;
+  for (uint64_t b0 = uint64_t(blockIdx.x) * TILE; b0 < ix.n_buckets; b0 += uint64_t(gridDim.x) * TILE) {
+    uint64_t *base = ix.slots + b0 * BUCKET_WORDS;
+    const uint32_t nw = tile_words(ix, b0);
+    uint64_t k[GS], v[GS];
+#pragma unroll
+    for (int u = 0; u < GS; ++u) {
+      const uint32_t w = tile_word<TT>(u);
+      v[u] = base[(w < nw ? w : 0) + SLOTS];
     }
-    const uint64_t rec = val_rec(*val_ptr(ix, h));
-    const uint32_t inst = dump_inst(v);
-    atomicAnd(reinterpret_cast<unsigned long long *>(&ix.pool[rec * uint64_t(ix.words) + (inst >> 6)]),
-              ~(1ull << (inst & 63)));
-  }
-}
-__global__ __launch_bounds__(TB) void evict_tomb_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
-                                                        const uint64_t *__restrict__ vals,
-                                                        const uint64_t *__restrict__ pos, uint64_t n, SelPrefix cut) {
-  const uint64_t stride = uint64_t(gridDim.x) * TB;
-  for (uint64_t i = uint64_t(blockIdx.x) * TB + threadIdx.x; i < n; i += stride) {
-    const uint64_t k = keys[i], v = vals[i];
-    if (sel_cmp(k, v, cut) <= 0) tomb_entry(ix, k, v, pos[i]);  // at or below the cut
+#pragma unroll
+    for (int u = 0; u < GS; ++u) {  // against the smallest sel_hi of the value's epoch
+      const uint32_t w = tile_word<TT>(u);
+      k[u] = KEY_EMPTY;
+      if (w < nw && v[u] != VAL_UNSET && val_kind(v[u]) != HEADER && sel_hi(0, val_epoch(v[u])) <= cut.hi) k[u] = base[w];
+    }
+#pragma unroll
+    for (int u = 0; u < GS; ++u) {
+      if (!is_entry(k[u], v[u]) || !sel_leaves(k[u], sel_hi(k[u], val_epoch(v[u])), val_inst(v[u]), cut)) continue;
+      base[tile_word<TT>(u)] = KEY_TOMB;
+      if (val_kind(v[u]) == MEMBER) {
+        const int64_t h = find_header(ix, k[u]);
+        if (h < 0) {
+          set_status(ix.hdr, SMETRIC_EINTERNAL);
+          continue;
+        }
+        const uint64_t rec = val_rec(*val_ptr(ix, h));
+        const uint32_t inst = val_inst(v[u]);
+        atomicAnd(reinterpret_cast<unsigned long long *>(&ix.pool[rec * uint64_t(ix.words) + (inst >> 6)]),
+                  ~(1ull << (inst & 63)));
+      }
+    }
   }
 }
 
-// One selection pass: the histogram of the next digit over the entries on the prefix.
-// With ck non-null those entries are also copied to (ck, cv) (in no particular order; the
-// caller does so only when few are left), so the later passes read them alone.  TOMB
-// (eviction in place, on the copying pass, which reads every entry): the entries below
-// the prefix, all of them evicted, become tombstones here, and the copied entries' slot
-// words go to cpos for the last tombstone pass over the copies alone.
-template <bool TOMB>
-__global__ __launch_bounds__(TB) void sel_hist_kernel(const uint64_t *keys, const uint64_t *vals, uint64_t n,
-                                                      SelPrefix p, unsigned long long *hist, uint64_t *ck,
-                                                      uint64_t *cv, unsigned long long *n_c, DevIndex ix,
-                                                      const uint64_t *pos, uint64_t *cpos) {
-  __shared__ uint32_t h[SEL_BINS];
-  for (int b = threadIdx.x; b < SEL_BINS; b += TB) h[b] = 0;
-  __syncthreads();
-  const uint64_t stride = uint64_t(gridDim.x) * TB;
-  for (uint64_t i = uint64_t(blockIdx.x) * TB + threadIdx.x; i < n; i += stride) {
-    const uint64_t k = keys[i], v = vals[i];
-    const int c = sel_cmp(k, v, p);
-    if (c == 0) {
-      atomicAdd(&h[sel_digit(k, v, p.level)], 1u);
-      if (ck) {
-        const unsigned long long at = atomicAdd(n_c, 1ull);
-        ck[at] = k;
-        cv[at] = v;
-        if (TOMB) cpos[at] = pos[i];
-      }
-    } else if (TOMB && c < 0) {
-      tomb_entry(ix, k, v, pos[i]);
-    }
-  }
-  __syncthreads();
-  for (int b = threadIdx.x; b < SEL_BINS; b += TB)
-    if (h[b]) atomicAdd(&hist[b], (unsigned long long)h[b]);
-}
 struct EvictWs {
-  unsigned long long *count;  // gathered entries, conversion queue, deferred pairs, survivors
-  unsigned long long *hist;   // SEL_BINS counts of the eviction's selection passes
-  uint64_t *ka, *va, *kb, *vb;  // entries and their sort ping-pong buffers
-  uint64_t *ea, *ia;            // eviction's rebuild: conversion queue and deferred pairs
-  uint64_t *toff;               // eviction: per gather tile, output offset << 16 | entry count
+  unsigned long long *count;    // the dump's entry count; EvictState
+  unsigned long long *hist;     // SEL_BINS counts of a selection pass; before, the scan's counters
+  uint64_t *ka, *va, *kb, *vb;  // the dump's entries and their sort ping-pong buffers; eviction: the
+                                // entries in the scan's range (ka, va) and of these the last ones
+                                // (kb, vb), then the entries the rebuild's tile pass leaves (ka, va)
+  uint64_t *ea, *ia;            // eviction: the sample (ea); the conversion queue and deferred pairs
   void *temp;
   size_t temp_bytes;
 };
@@ -2097,8 +2365,7 @@ uint64_t evict_ws_layout(uint64_t cap, EvictWs *ws, void *base) {
     return o;
   };
   const uint64_t o_cnt = take(256), o_hist = take(8 * SEL_BINS), o_ka = take(8 * n), o_va = take(8 * n), o_kb = take(8 * n),
-                 o_vb = take(8 * n), o_ea = take(8 * n), o_ia = take(8 * n), o_toff = take(8 * (n / 512 + 64)),
-                 o_tmp = take(tb);
+                 o_vb = take(8 * n), o_ea = take(8 * n), o_ia = take(8 * n), o_tmp = take(tb);
   if (ws) {
     char *b = static_cast<char *>(base);
     ws->count = reinterpret_cast<unsigned long long *>(b + o_cnt);
@@ -2109,7 +2376,6 @@ uint64_t evict_ws_layout(uint64_t cap, EvictWs *ws, void *base) {
     ws->vb = reinterpret_cast<uint64_t *>(b + o_vb);
     ws->ea = reinterpret_cast<uint64_t *>(b + o_ea);
     ws->ia = reinterpret_cast<uint64_t *>(b + o_ia);
-    ws->toff = reinterpret_cast<uint64_t *>(b + o_toff);
     ws->temp = b + o_tmp;
     ws->temp_bytes = tb;
   }
@@ -2143,8 +2409,7 @@ int gather_sorted(const smetric_index *idx, const EvictWs &ws, uint64_t n, uint6
   int rc = fill(ws.count, 256, 0, s);
   if (rc) return rc;
   const uint64_t n_slots = ix.n_buckets * SLOTS;
-  hipLaunchKernelGGL(gather_kernel, dim3(grid_for(n_slots)), dim3(TB), 0, s, ix, ws.ka, ws.va, nullptr, ws.count,
-                     nullptr, nullptr, nullptr, n);
+  hipLaunchKernelGGL(gather_kernel, dim3(grid_for(n_slots)), dim3(TB), 0, s, ix, ws.ka, ws.va, ws.count, n);
   if ((rc = hip_rc(hipGetLastError()))) return rc;
   unsigned long long got = 0;
   if (hipMemcpyAsync(&got, ws.count, 8, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
@@ -2259,47 +2524,92 @@ extern "C" int smetric_index_evict(smetric_index *idx, uint32_t frac_num, uint32
     return SMETRIC_EWORKSPACE;
   EvictWs ws;
   evict_ws_layout(idx->capacity, &ws, workspace);
-  IndexHdr h;
-  int rc = read_hdr(idx, &h, stream);
-  if (rc) return rc;
-  const uint64_t n = h.n_entries;
-  const uint64_t m = uint64_t((static_cast<unsigned __int128>(n) * frac_num + frac_den - 1) / frac_den);
-  if (m == 0) return SMETRIC_OK;
-  // all entries, tile by tile in slot order
-  if ((rc = fill(ws.count, 256, 0, stream)) || (rc = fill(ws.count + 5, 8, ~uint64_t(0), stream)) ||
-      (rc = fill(ws.hist, 8 * 2048, 0, stream)))
-    return rc;
-  const DevIndex ix = dev_view(idx);
-  uint64_t *pos = ws.kb;  // free until a dump: each entry's slot
-  hipLaunchKernelGGL(gather_kernel, dim3(grid_for(ix.n_buckets * SLOTS)), dim3(TB), 0, stream, ix, ws.ka, ws.va,
-                     pos, ws.count, ws.count + 3, ws.hist, ws.toff, n);
-  unsigned long long cnt[6] = {0, 0, 0, 0, 0, 0};
-  unsigned long long hh[SEL_BINS];
-  if (hipMemcpyAsync(cnt, ws.count, sizeof(cnt), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-      hipMemcpyAsync(hh, ws.hist, 8 * 2048, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-      hipStreamSynchronize(stream) != hipSuccess)
-    return SMETRIC_EHIP;
-  if (cnt[0] != n) return SMETRIC_EINTERNAL;
-  const uint64_t n_tomb = cnt[3];
-  // select the m-th smallest, one digit per pass; stop once its whole bin is evicted
-  SelPrefix p{};
-  uint64_t rem = m;          // rank of the m-th smallest among the entries on the prefix (1-based)
-  uint64_t on_prefix = n;    // entries on the prefix
-  int l0 = 0;
-  if (cnt[4] == cnt[5]) {  // every entry has the same first digit (the epochs' top bits): no pass
-    p.digit[0] = uint32_t(cnt[4]);
-    p.level = l0 = 1;
-    if (cnt[4] == 0 && rem < on_prefix) {  // and the gather counted the second digit: no pass either
-      uint64_t below = 0;
-      int b = 0;
-      while (b < 2048 && below + hh[b] < rem) below += hh[b++];
-      if (b == 2048) return SMETRIC_EINTERNAL;
-      p.digit[1] = uint32_t(b);
-      p.level = l0 = 2;
-      rem -= below;
-      on_prefix = hh[b];
-    }
+  int rc;
+  if (frac_num == 0) {  // nothing leaves
+    IndexHdr h;
+    return read_hdr(idx, &h, stream);
   }
+  const DevIndex ix = dev_view(idx);
+  auto *const st = reinterpret_cast<EvictState *>(ws.count);
+  static_assert(sizeof(EvictState) <= 256 && EV_LANES * EV_LINE <= SEL_BINS, "the workspace's counters");
+  struct {
+    union {
+      EvictState st;
+      char room[256];
+    };
+    unsigned long long counts[EV_LANES * EV_LINE];  // as the workspace holds them
+  } seen;
+  static_assert(sizeof(seen) == 256 + 8 * EV_LANES * EV_LINE, "the state and the counters are one run of it");
+  const uint64_t n_tiles = (ix.n_buckets + TILE - 1) / TILE;
+  // a sample pays from 2^15 buckets on (a scan there copies at most 4 MB); it needs its room
+  const bool sampled = ix.n_buckets >= (uint64_t(1) << 15) && idx->capacity >= uint64_t(EV_SAMPLE) * SLOTS;
+  uint64_t n = 0, m = 0, live = 0, n_tomb = 0, below = 0, inside = 0;
+  for (int round = sampled ? 0 : 1; round < 2; ++round) {  // second: the range missed the cut, take everything
+    hipLaunchKernelGGL(evict_sample_kernel, dim3(round == 0 ? EV_SAMPLE * SLOTS / TB : 1), dim3(TB), 0, stream, ix, st,
+                       ws.hist, round == 0 ? ws.ea : nullptr);
+    if (round == 0)
+      hipLaunchKernelGGL(evict_range_kernel, dim3(1), dim3(FIN_T), 0, stream, ws.ea, frac_num, frac_den, st);
+    hipLaunchKernelGGL(evict_scan_kernel, dim3(n_tiles < 1024 ? n_tiles : 1024), dim3(TB), 0, stream, ix, st, ws.hist,
+                       ws.ka, ws.va, idx->capacity);
+    if ((rc = hip_rc(hipGetLastError()))) return rc;
+    if (hipMemcpyAsync(&seen, ws.count, sizeof(seen), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess)
+      return SMETRIC_EHIP;
+    n = seen.st.n_entries;
+    m = uint64_t((static_cast<unsigned __int128>(n) * frac_num + frac_den - 1) / frac_den);
+    if (m == 0) return SMETRIC_OK;
+    inside = seen.st.n_in;
+    live = n_tomb = below = 0;
+    for (int b = 0; b < EV_LANES; ++b) {
+      live += seen.counts[b * EV_LINE];
+      n_tomb += seen.counts[b * EV_LINE + 1];
+      below += seen.counts[b * EV_LINE + 2];
+    }
+    if (live != n || n > idx->capacity) return SMETRIC_EINTERNAL;
+    if (below < m && m <= below + inside) break;
+  }
+  if (below >= m || m > below + inside) return SMETRIC_EINTERNAL;
+  // select the m-th smallest among the entries in the range: first the digits that its two
+  // ends share, then one digit per pass; stop once a whole bin is evicted
+  SelPrefix p{};
+  uint64_t rem = m - below, on_prefix = inside;  // rank (1-based) among the entries on the prefix
+  for (int l = 0; l < 5; ++l) {                  // the digits that sel_hi holds whole
+    const uint64_t lo = seen.st.lo, hi = seen.st.hi;
+    const uint32_t d = sel_digit(lo << 24, (lo >> 40) << 24, l);
+    if (hi >> 62 || d != sel_digit(hi << 24, (hi >> 40) << 24, l)) break;
+    p.digit[l] = d;
+    p.level = l + 1;
+  }
+  const SelCut *cut_dev = nullptr;  // the cut, once a kernel decides it
+  uint64_t *sk = ws.ka, *sv = ws.va;
+  while (p.level < SEL_LEVELS && rem < on_prefix) {
+    const int grid = grid_for(inside) < 1024 ? grid_for(inside) : 1024;
+    if (on_prefix <= SEL_FIN) {  // few left: copied out if they are spread over more, and the rest without the host
+      const bool copy = inside > SEL_FIN;
+      if (copy)
+        hipLaunchKernelGGL(sel_copy_kernel, dim3(grid), dim3(TB), 0, stream, sk, sv, inside, p, &st->n_fin, ws.kb,
+                           ws.vb, idx->capacity);
+      hipLaunchKernelGGL(sel_finish_kernel, dim3(1), dim3(FIN_T), 0, stream, ix, copy ? ws.kb : sk, copy ? ws.vb : sv,
+                         copy ? on_prefix : inside, p, rem, on_prefix, copy ? &st->n_fin : nullptr, st);
+      cut_dev = &st->cut;
+      break;
+    }
+    unsigned long long hh[SEL_BINS];
+    if ((rc = fill(ws.hist, sizeof(hh), 0, stream))) return rc;
+    hipLaunchKernelGGL(sel_hist_kernel, dim3(grid), dim3(TB), 0, stream, sk, sv, inside, p, ws.hist);
+    if (hipMemcpyAsync(hh, ws.hist, sizeof(hh), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess)
+      return SMETRIC_EHIP;
+    uint64_t sum = 0;
+    int b = 0;
+    while (b < SEL_BINS && sum + hh[b] < rem) sum += hh[b++];
+    if (b == SEL_BINS) return SMETRIC_EINTERNAL;
+    p.digit[p.level++] = uint32_t(b);
+    rem -= sum;
+    on_prefix = hh[b];  // rem == on_prefix: the whole bin goes, the prefix itself is the cut
+  }
+  if (rem < on_prefix && !cut_dev) return SMETRIC_EINTERNAL;  // the full tuple is unique
+  const SelCut cut = sel_cut(p, seen.st.hi);
   // few tombstones: evict in place, the survivors keep their slots.  Tombstones may take
   // an eighth of the slots, and at most half of what stays free with the live entries at
   // capacity (the same eighth under the default 3/4 sizing), so every chain keeps
@@ -2308,71 +2618,25 @@ extern "C" int smetric_index_evict(smetric_index *idx, uint32_t frac_num, uint32
   const uint64_t reserved = idx->capacity + uint64_t(ix.threshold) * ix.n_records;
   const uint64_t tomb_cap_free = n_slots > reserved ? (n_slots - reserved) / 2 : 0;
   const uint64_t tomb_cap = tomb_cap_free < n_slots / 8 ? tomb_cap_free : n_slots / 8;
-  const bool in_place = n_tomb + m <= tomb_cap;
-  const uint64_t *sk = ws.ka, *sv = ws.va, *sp = pos;  // the entries the passes read, and their slots
-  uint64_t sn = n;
-  for (int l = l0; l < SEL_LEVELS && rem < on_prefix; ++l) {
-    p.level = l;
-    // once few entries are left on the prefix, this pass copies them out and the later
-    // passes read those alone
-    const bool compact = sk == ws.ka && on_prefix <= (uint64_t(1) << 20);
-    if ((rc = fill(ws.hist, 8 * SEL_BINS, 0, stream))) return rc;
-    if (compact && (rc = fill(ws.count + 6, 8, 0, stream))) return rc;
-    const int grid = grid_for(sn) < 1024 ? grid_for(sn) : 1024;
-    if (in_place && compact)  // the last pass over every entry also writes the tombstones below the prefix
-      hipLaunchKernelGGL(sel_hist_kernel<true>, dim3(grid), dim3(TB), 0, stream, sk, sv, sn, p, ws.hist, ws.ea,
-                         ws.ia, ws.count + 6, ix, pos, ws.vb);
-    else
-      hipLaunchKernelGGL(sel_hist_kernel<false>, dim3(grid), dim3(TB), 0, stream, sk, sv, sn, p, ws.hist,
-                         compact ? ws.ea : nullptr, compact ? ws.ia : nullptr, ws.count + 6, ix, nullptr, nullptr);
-    unsigned long long n_c = 0;
-    if (hipMemcpyAsync(hh, ws.hist, 8 * SEL_BINS, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-        (compact && hipMemcpyAsync(&n_c, ws.count + 6, 8, hipMemcpyDeviceToHost, stream) != hipSuccess) ||
-        hipStreamSynchronize(stream) != hipSuccess)
-      return SMETRIC_EHIP;
-    if (compact) {
-      if (n_c != on_prefix) return SMETRIC_EINTERNAL;
-      sk = ws.ea;
-      sv = ws.ia;
-      sn = n_c;
-      if (in_place) sp = ws.vb;  // and everything below the copies is a tombstone already
-    }
-    uint64_t below = 0;
-    int b = 0;
-    while (b < SEL_BINS && below + hh[b] < rem) below += hh[b++];
-    if (b == SEL_BINS) return SMETRIC_EINTERNAL;
-    p.digit[l] = uint32_t(b);
-    p.level = l + 1;
-    rem -= below;
-    on_prefix = hh[b];  // rem == on_prefix: the whole bin goes, the prefix itself is the cut
-    if (rem < on_prefix && l + 1 == SEL_LEVELS) return SMETRIC_EINTERNAL;  // the full tuple is unique
-  }
-  if (in_place) {  // the entries still to decide: every one, or the copies of the last full pass
-    hipLaunchKernelGGL(evict_tomb_kernel, dim3(grid_for(sn)), dim3(TB), 0, stream, ix, sk, sv, sp, sn, p);
-    hipLaunchKernelGGL(set_counts_kernel, dim3(1), dim3(1), 0, stream, ix.hdr, (unsigned long long)(n - m), 0);
+  if (n_tomb + m <= tomb_cap) {
+    hipLaunchKernelGGL(evict_tomb_kernel, dim3(n_tiles < MAX_GRID ? n_tiles : MAX_GRID), dim3(TT), 0, stream, ix, cut,
+                       cut_dev, (unsigned long long)(n - m));
     if ((rc = hip_rc(hipGetLastError()))) return rc;
     return hip_rc(hipStreamSynchronize(stream));
   }
   // else rebuild from the survivors (the entries above the cut, exactly n - m of them),
-  // which also clears every tombstone
-  uint64_t *keys = ws.ka, *vals = ws.va;
+  // which also clears every tombstone: the tile pass (writes every bucket: no clear needed),
+  // then the claims for what it left
   if ((rc = fill(ix.pool, ix.n_records * uint64_t(ix.words) * 8, 0, stream))) return rc;
-  hipLaunchKernelGGL(set_counts_kernel, dim3(1), dim3(1), 0, stream, ix.hdr, (unsigned long long)(n - m), 1);
-  // tile pass (writes every bucket: no clear needed), then the claims for what it left
-  const uint64_t n_tiles = (ix.n_buckets + TB * GB - 1) / (TB * GB);
-  uint64_t *left_list = ws.vb;  // free: the entries the tile pass leaves, by gathered index
-  hipLaunchKernelGGL(rebuild_tile_kernel, dim3(n_tiles), dim3(TB), 0, stream, ix, keys, vals, pos, ws.toff, p,
-                     left_list);
-  uint64_t *trig = ws.ea;  // free buffers: the conversion queue and the deferred pairs
-  unsigned long long *n_trig = ws.count + 1;
-  uint64_t *def = ws.ia;
-  unsigned long long *n_def = ws.count + 2;
+  hipLaunchKernelGGL(rebuild_tile_kernel, dim3(n_tiles), dim3(TILE), 0, stream, ix, cut, cut_dev, ws.ka, ws.va,
+                     &st->n_left, idx->capacity, (unsigned long long)(n - m));
   hipLaunchKernelGGL(rebuild_claim_kernel, dim3(n_tiles < MAX_GRID ? n_tiles : MAX_GRID), dim3(TB), 0, stream, ix,
-                     keys, vals, left_list, ws.toff, n_tiles, trig, n_trig, def, n_def, idx->capacity);
-  hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, trig, n_trig, nullptr, keys, nullptr, nullptr);
+                     ws.ka, ws.va, &st->n_left, ws.ea, &st->n_trig, ws.ia, &st->n_def, idx->capacity);
+  hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, ws.ea, &st->n_trig, nullptr, ws.ka, nullptr,
+                     nullptr);
   // every member of a key with a bitmap record is deferred here (millions): the full grid
-  hipLaunchKernelGGL(deferred_kernel, dim3(MAX_GRID), dim3(TB), 0, stream, ix, def, n_def, nullptr, nullptr, nullptr,
-                     0u, keys, vals, nullptr);
+  hipLaunchKernelGGL(deferred_kernel, dim3(MAX_GRID), dim3(TB), 0, stream, ix, ws.ia, &st->n_def, nullptr, nullptr,
+                     nullptr, 0u, ws.ka, ws.va, nullptr);
   if ((rc = hip_rc(hipGetLastError()))) return rc;
   return hip_rc(hipStreamSynchronize(stream));
 }
