@@ -43,11 +43,13 @@ __device__ __forceinline__ i128 est2(const RouteParams &p, int64_t L, int32_t c,
   return i128(2) * q + i128(uint64_t(2 * p.c_lin) * n) + i128(u128_(uint64_t(p.c_att)) * w);
 }
 
+__device__ __forceinline__ int64_t shfl_xor_i64(int64_t v, int m) {
+  const uint32_t lo = uint32_t(__shfl_xor(int(uint32_t(uint64_t(v))), m, 64));
+  const uint32_t hi = uint32_t(__shfl_xor(int(uint32_t(uint64_t(v) >> 32)), m, 64));
+  return int64_t((uint64_t(hi) << 32) | lo);
+}
 __device__ __forceinline__ double shfl_xor_f64(double v, int m) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = uint32_t(__shfl_xor(int(uint32_t(b)), m, 64));
-  const uint32_t hi = uint32_t(__shfl_xor(int(uint32_t(b >> 32)), m, 64));
-  return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+  return __builtin_bit_cast(double, shfl_xor_i64(__builtin_bit_cast(int64_t, v), m));
 }
 
 __device__ __forceinline__ i128 shfl_xor128(i128 v, int m) {
@@ -94,21 +96,24 @@ __global__ __launch_bounds__(64 * RW) void route_kernel(const int32_t *__restric
   // parameters in range).  While C0 and every 2q stay below 2^50, each in-domain score is an
   // integer below 2^51 (and c (a1 + a2 c) <= C0), so two fused multiply-adds give it
   // exactly and doubles compare it exactly.  A wavefront that meets a larger queue scans
-  // again in 128 bits.
+  // again in 128 bits.  (RULE 1: and a load of 2^46 or more, so that 65,536 of them add up
+  // in 64 bits: 16,384 requests over 1,024 instances 36 us, in 128 bits 49.)
   const i128 c0 = i128(2) * p.c_lin * L + i128(p.c_att) * L * L;
-  bool fast = RULE == 0 && ok && c0 < (i128(1) << 50);
+  bool fast = ok && c0 < (i128(1) << 50);
   if (fast) {
     const double a1 = double(2 * p.c_lin * p.B), a2 = double(p.c_att * p.B * p.B), c0d = double(int64_t(c0));
     double bs = 0.0, ps = 0.0;
     bool small = true;
+    int64_t lsum = 0;
     for (int32_t i0 = lane; i0 < I; i0 += 64 * RU) {
       int32_t cv[RU];
-      int64_t qv[RU];
+      int64_t qv[RU], lv[RU];
 #pragma unroll
       for (int u = 0; u < RU; ++u) {
         const int32_t ii = i0 + 64 * u < I ? i0 + 64 * u : I - 1;
         cv[u] = c[ii];
         qv[u] = q[ii];
+        lv[u] = RULE == 1 ? load[ii] : 0;
       }
 #pragma unroll
       for (int u = 0; u < RU; ++u) {
@@ -116,6 +121,10 @@ __global__ __launch_bounds__(64 * RW) void route_kernel(const int32_t *__restric
         if (i >= I) break;
         const int32_t ci = cv[u];
         const int64_t qi = qv[u];
+        if (RULE == 1) {
+          small = small && uint64_t(lv[u]) < (uint64_t(1) << 46);
+          lsum += lv[u];
+        }
         if (ci < 0 || ci > max_c || qi < 0 || qi >= (int64_t(1) << 62)) ok = false;
         small = small && uint64_t(qi) < (uint64_t(1) << 49);
         const double cd = double(ci);
@@ -149,7 +158,9 @@ __global__ __launch_bounds__(64 * RW) void route_kernel(const int32_t *__restric
           bs = obs;
           best_d = od;
         }
+        if (RULE == 1) lsum += shfl_xor_i64(lsum, m);
       }
+      load_sum = lsum;
       prev_e = i128(int64_t(ps));
       best_e = i128(int64_t(bs));
     } else {  // back to the 128-bit scan from the start
@@ -268,6 +279,13 @@ __device__ __forceinline__ void min_sd(MinSD &a, i128 s, int32_t d) {
   }
 }
 
+__device__ __forceinline__ void min_fd(double &as, int32_t &ad, double s, int32_t d) {
+  if (d != 0x7FFFFFFF && (ad == 0x7FFFFFFF || s < as || (s == as && d < ad))) {
+    as = s;
+    ad = d;
+  }
+}
+
 // Route under PD colocation (App. B pseudocode).  Same mapping as route_kernel; each lane
 // also tests the TPOT filter of its instances and keeps two minima of the LMetric score
 // est2 * n_run: over the instances that pass, and over all (used when none passes).
@@ -288,7 +306,68 @@ __global__ __launch_bounds__(64 * RW) void route_coloc_kernel(
 
   int32_t best_c = -1, best_ci = 0x7FFFFFFF;
   MinSD pass{0, 0x7FFFFFFF}, all{0, 0x7FFFFFFF};
-  for (int32_t i0 = lane; i0 < I; i0 += 64 * RU) {  // loads first, as in route_kernel
+  // The scan in doubles, exact under route_kernel's bounds while every score is below 2^53
+  // as well (one that is not rounds to 2^53 or more); the slack's rounding cannot carry it
+  // across a cost below 2^50.  16,384 requests over 1,024 instances 48 us, in 128 bits 76.
+  const i128 c0 = i128(2) * p.c_lin * L + i128(p.c_att) * L * L;
+  bool fast = ok && c0 < (i128(1) << 50);
+  if (fast) {
+    const double a1 = double(2 * p.c_lin * p.B), a2 = double(p.c_att * p.B * p.B), c0d = double(int64_t(c0));
+    double ps = 0.0, as = 0.0;
+    int32_t pd = 0x7FFFFFFF, ad = 0x7FFFFFFF;
+    bool small = true, in = true;
+    for (int32_t i0 = lane; i0 < I; i0 += 64 * RU) {
+      int32_t cv[RU], nv[RU];
+      int64_t qv[RU], sv[RU];
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const int32_t ii = i0 + 64 * u < I ? i0 + 64 * u : I - 1;
+        cv[u] = c[ii];
+        qv[u] = q[ii];
+        nv[u] = n_run[ii];
+        sv[u] = slack[ii];
+      }
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const int32_t i = i0 + 64 * u;
+        if (i >= I) break;
+        const int32_t ci = cv[u], ni = nv[u];
+        const int64_t qi = qv[u];
+        in = in && ci >= 0 && ci <= max_c && ni >= 0;
+        const double cd = double(ci);
+        const double cost = __builtin_fma(-cd, __builtin_fma(a2, cd, a1), c0d);
+        const double sc = (cost + 2.0 * double(qi)) * double(ni);
+        small = small && uint64_t(qi) < (uint64_t(1) << 49) && sc < 9007199254740992.0;
+        if (ci > best_c) {
+          best_c = ci;
+          best_ci = i;
+        }
+        const int32_t d = i >= start ? i - start : i - start + I;
+        min_fd(as, ad, sc, d);
+        if (cost <= 2.0 * double(sv[u])) min_fd(ps, pd, sc, d);
+      }
+    }
+    fast = __ballot(!small) == 0;
+    if (fast) {
+      ok = __ballot(!in) == 0;
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        const int32_t oc = __shfl_xor(best_c, m, 64), oi = __shfl_xor(best_ci, m, 64);
+        if (oc > best_c || (oc == best_c && oi < best_ci)) {
+          best_c = oc;
+          best_ci = oi;
+        }
+        min_fd(as, ad, shfl_xor_f64(as, m), __shfl_xor(ad, m, 64));
+        min_fd(ps, pd, shfl_xor_f64(ps, m), __shfl_xor(pd, m, 64));
+      }
+      all.d = ad;  // the decision needs no score
+      pass.d = pd;
+    } else {  // back to the 128-bit scan from the start
+      best_c = -1;
+      best_ci = 0x7FFFFFFF;
+    }
+  }
+  for (int32_t i0 = lane; !fast && i0 < I; i0 += 64 * RU) {  // loads first, as in route_kernel
     int32_t cv[RU], nv[RU];
     int64_t qv[RU], sv[RU];
 #pragma unroll
@@ -317,9 +396,9 @@ __global__ __launch_bounds__(64 * RW) void route_coloc_kernel(
       if (sv[u] >= NO_DECODE || cost <= i128(2) * sv[u]) min_sd(pass, sc, d);
     }
   }
-  ok = __ballot(!ok) == 0;
+  if (!fast) ok = __ballot(!ok) == 0;
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
+  for (int m = 32; m >= 1 && !fast; m >>= 1) {
     const int32_t oc = __shfl_xor(best_c, m, 64), oi = __shfl_xor(best_ci, m, 64);
     if (oc > best_c || (oc == best_c && oi < best_ci)) {
       best_c = oc;
