@@ -14,8 +14,11 @@
 //           slots of (user_r, turn_r, n, key_r[n-1]) give the earlier requests whose whole
 //           sequence is r's first n keys -- with chained keys (key j determines blocks 0..j)
 //           one key comparison is the whole prefix test; the largest p < r wins;
-//   roots   pointer jumping, ceil(log2 R) rounds (plus one to land in the output), so every
-//           request reaches its chain's first request.
+//           Most lengths have no offer: up to FILT_MAX_REQ requests a bitmap of the offers in
+//           LDS turns them away (one random 16-byte read per key made the join bound by the
+//           L2's lines);
+//   roots   one launch: every request follows the jumps, shortening its own for the others
+//           as it goes, to its chain's first request.
 #include "common.h"
 
 namespace smk {
@@ -44,15 +47,34 @@ __device__ __forceinline__ bool range_ok(const int64_t *blk_off, int32_t r, int6
   return b0 >= 0 && b0 <= b1 && b1 <= n_blocks;
 }
 
-__global__ void offer_clear_kernel(OfferSlot *t, uint64_t ns) {
+// The offers' bitmap: `words` 32-bit words, a power of two, in the session array until the
+// roots are written there; an offer sets two bits of one word.  Keys are hashes already, so
+// a few 32-bit operations spread them.  One length in six passes at FILT_MAX_REQ requests,
+// one in sixty at 32,768.
+constexpr int32_t FILT_MAX_REQ = 1 << 17;
+constexpr uint32_t FILT_MAX_WORDS = 1u << 14;  // 64 KB of LDS, two workgroups to a compute unit
+__device__ __forceinline__ uint32_t filt_base(uint32_t user, uint32_t turn) {
+  return user * 0x9E3779B1u + turn * 0x85EBCA6Bu;
+}
+struct FiltBits {
+  uint32_t word, bits;
+};
+__device__ __forceinline__ FiltBits filt_bits(uint32_t base, uint32_t n, uint64_t last, uint32_t words) {
+  const uint32_t x = (uint32_t(last) ^ base) + n * 0xC2B2AE35u, y = x ^ (x >> 15) ^ uint32_t(last >> 32);
+  return {(y >> 10) & (words - 1), (1u << (y & 31)) | (1u << ((y >> 5) & 31))};
+}
+
+__global__ void offer_clear_kernel(OfferSlot *t, uint64_t ns, uint32_t *filt, uint32_t words) {
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < ns; i += stride) t[i] = OfferSlot{0, 0, 0};
+  const uint64_t t0 = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  for (uint64_t i = t0; i < ns; i += stride) t[i] = OfferSlot{0, 0, 0};
+  for (uint64_t i = t0; i < words; i += stride) filt[i] = 0;
 }
 
 __global__ __launch_bounds__(TB) void offer_kernel(const uint64_t *__restrict__ keys, const int64_t *__restrict__ blk_off,
                                                    int32_t n_req, int64_t n_blocks, const uint32_t *__restrict__ user,
                                                    const int32_t *__restrict__ turn, OfferSlot *t, uint64_t ns,
-                                                   int32_t *status) {
+                                                   uint32_t *filt, uint32_t words, int32_t *status) {
   const int32_t p = int32_t(blockIdx.x) * TB + threadIdx.x;
   if (p >= n_req) return;
   int64_t b0, nb;
@@ -60,7 +82,12 @@ __global__ __launch_bounds__(TB) void offer_kernel(const uint64_t *__restrict__ 
     if (status) atomicCAS(status, 0, SMETRIC_EINVAL);
     return;
   }
-  const uint64_t h = triple_hash(user[p], int64_t(turn[p]) + 1, nb, nb > 0 ? keys[b0 + nb - 1] : 0);
+  const uint64_t last = nb > 0 ? keys[b0 + nb - 1] : 0;
+  const uint64_t h = triple_hash(user[p], int64_t(turn[p]) + 1, nb, last);
+  if (words) {
+    const FiltBits f = filt_bits(filt_base(user[p], uint32_t(turn[p]) + 1), uint32_t(nb), last, words);
+    atomicOr(&filt[f.word], f.bits);
+  }
   uint64_t s = h & (ns - 1);
   for (uint64_t step = 0; step < ns; ++step, s = (s + 1) & (ns - 1)) {
     if (atomicCAS(reinterpret_cast<unsigned long long *>(&t[s].h), 0ull, h) == 0ull) {
@@ -70,59 +97,113 @@ __global__ __launch_bounds__(TB) void offer_kernel(const uint64_t *__restrict__ 
   }
 }
 
-__global__ __launch_bounds__(TB) void query_kernel(const uint64_t *__restrict__ keys, const int64_t *__restrict__ blk_off,
-                                                   int32_t n_req, int64_t n_blocks, const uint32_t *__restrict__ user,
-                                                   const int32_t *__restrict__ turn, const OfferSlot *__restrict__ t,
-                                                   uint64_t ns, int32_t *__restrict__ parent, int32_t *__restrict__ jump) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int32_t r = int32_t(blockIdx.x) * (TB / 64) + wave;
-  if (r >= n_req) return;
-  int64_t b0, nb;
-  const int32_t tr = turn[r];
-  if (!range_ok(blk_off, r, n_blocks, b0, nb) || tr < 0) {
-    if (lane == 0) {
-      parent[r] = -1;
-      jump[r] = -1;
-    }
-    return;
+// The latest earlier request that offered (user, turn, n, last); at most `r` and above `best`.
+__device__ __forceinline__ int32_t find_offer(const uint64_t *keys, const int64_t *blk_off, const uint32_t *user,
+                                              const int32_t *turn, const OfferSlot *t, uint64_t ns, int32_t r,
+                                              uint32_t u, int32_t tr, int64_t n, uint64_t last, int32_t best) {
+  const uint64_t h = triple_hash(u, tr, n, last);
+  uint64_t s = h & (ns - 1);
+  for (uint64_t step = 0; step < ns; ++step, s = (s + 1) & (ns - 1)) {
+    const uint64_t sh = t[s].h;
+    if (sh == 0) break;
+    if (sh != h) continue;
+    const int32_t p = t[s].p;
+    if (p >= r || p <= best) continue;
+    // verify the triple itself (the hash is only a filter)
+    const int64_t pb0 = blk_off[p], pnb = blk_off[p + 1] - pb0;
+    if (user[p] == u && int64_t(turn[p]) + 1 == tr && pnb == n && (n == 0 || keys[pb0 + n - 1] == last)) best = p;
   }
-  const uint32_t u = user[r];
-  int32_t best = -1;
-  if (tr > 0) {
-    for (int64_t n = lane; n <= nb; n += 64) {  // prefix length n: blocks 0 .. n-1
-      const uint64_t last = n > 0 ? keys[b0 + n - 1] : 0;
-      const uint64_t h = triple_hash(u, tr, n, last);
-      uint64_t s = h & (ns - 1);
-      for (uint64_t step = 0; step < ns; ++step, s = (s + 1) & (ns - 1)) {
-        const uint64_t sh = t[s].h;
-        if (sh == 0) break;
-        if (sh != h) continue;
-        const int32_t p = t[s].p;
-        if (p >= r || p <= best) continue;
-        // verify the triple itself (the hash is only a filter)
-        const int64_t pb0 = blk_off[p], pnb = blk_off[p + 1] - pb0;
-        if (user[p] == u && int64_t(turn[p]) + 1 == tr && pnb == n && (n == 0 || keys[pb0 + n - 1] == last))
-          best = p;
+  return best;
+}
+
+// FILT: workgroups of 1024 that keep the bitmap in LDS and take request after request; a lane
+// tests QU lengths, their keys loaded together, and looks up those that pass together at the
+// end of the stretch.  34,000 requests of some 370 blocks: 74 us (91 us with one bit an offer), 130 us
+// as below.  Else a wavefront per request, every length looked up.
+constexpr int QT = 1024, QU = 8;
+template <bool FILT>
+__global__ __launch_bounds__(FILT ? QT : TB) void query_kernel(
+    const uint64_t *__restrict__ keys, const int64_t *__restrict__ blk_off, int32_t n_req, int64_t n_blocks,
+    const uint32_t *__restrict__ user, const int32_t *__restrict__ turn, const OfferSlot *__restrict__ t, uint64_t ns,
+    const uint32_t *__restrict__ filt, uint32_t words, int32_t *__restrict__ parent, int32_t *__restrict__ jump) {
+  __shared__ uint32_t bits[FILT ? FILT_MAX_WORDS : 1];
+  constexpr int WAVES = (FILT ? QT : TB) / 64;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (FILT) {
+    for (uint32_t i = threadIdx.x; i < words; i += QT) bits[i] = filt[i];
+    __syncthreads();
+  }
+  for (int64_t r64 = int64_t(blockIdx.x) * WAVES + wave; r64 < n_req; r64 += int64_t(gridDim.x) * WAVES) {
+    const int32_t r = int32_t(r64);
+    int64_t b0, nb;
+    const int32_t tr = turn[r];
+    if (!range_ok(blk_off, r, n_blocks, b0, nb) || tr < 0) {
+      if (lane == 0) {
+        parent[r] = -1;
+        jump[r] = -1;
+      }
+      continue;
+    }
+    const uint32_t u = user[r];
+    int32_t best = -1;
+    if (tr > 0) {
+      if (FILT) {
+        const uint32_t base = filt_base(u, uint32_t(tr));
+        for (int64_t n0 = lane; n0 <= nb + lane; n0 += 64 * QU) {  // whole wavefronts iterate together
+          uint64_t last[QU];
+#pragma unroll
+          for (int j = 0; j < QU; ++j) {
+            const int64_t n = n0 + 64 * j;  // prefix length n: blocks 0 .. n-1
+            last[j] = n > 0 && n <= nb ? keys[b0 + n - 1] : 0;
+          }
+          uint32_t cand = 0;
+#pragma unroll
+          for (int j = 0; j < QU; ++j) {
+            const int64_t n = n0 + 64 * j;
+            const FiltBits f = filt_bits(base, uint32_t(n), last[j], words);
+            cand |= uint32_t(n <= nb && (bits[f.word] & f.bits) == f.bits) << j;
+          }
+          while (cand) {
+            const int j = __ffs(cand) - 1;
+            cand &= cand - 1;
+            const int64_t n = n0 + 64 * j;
+            best = find_offer(keys, blk_off, user, turn, t, ns, r, u, tr, n, n > 0 ? keys[b0 + n - 1] : 0, best);
+          }
+        }
+      } else {
+        for (int64_t n = lane; n <= nb; n += 64)
+          best = find_offer(keys, blk_off, user, turn, t, ns, r, u, tr, n, n > 0 ? keys[b0 + n - 1] : 0, best);
+      }
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        const int32_t o = __shfl_xor(best, m, 64);
+        best = o > best ? o : best;
       }
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      const int32_t o = __shfl_xor(best, m, 64);
-      best = o > best ? o : best;
+    if (lane == 0) {
+      parent[r] = best;
+      jump[r] = best >= 0 ? best : r;
     }
-  }
-  if (lane == 0) {
-    parent[r] = best;
-    jump[r] = best >= 0 ? best : r;
   }
 }
 
-// One round of pointer jumping: a <- a[a] (invalid requests stay -1).
-__global__ void jump_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst, int32_t n_req) {
-  const int32_t r = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// Every request follows jump to its chain's first (jump[a] == a; invalid requests are -1),
+// writing each jump that it reaches over its own, so that the requests behind it go further
+// a step: some ceil(log2 length) steps where the chain runs together.  Any value a jump has
+// ever held is an ancestor, lower than its request: an old one costs a step and no more, and
+// every walk ends.  (34,000 requests in chains of 8: 5 us;
+// a launch per round of doubling, 17 of them: 80 us.)
+__global__ __launch_bounds__(TB) void roots_kernel(int32_t *jump, int32_t *__restrict__ session, int32_t n_req) {
+  const int32_t r = int32_t(blockIdx.x) * TB + threadIdx.x;
   if (r >= n_req) return;
-  const int32_t a = src[r];
-  dst[r] = a < 0 ? -1 : src[a];
+  int32_t a = __hip_atomic_load(&jump[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  while (a >= 0) {
+    const int32_t b = __hip_atomic_load(&jump[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (b == a) break;
+    __hip_atomic_store(&jump[r], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    a = b;
+  }
+  session[r] = a;
 }
 
 uint64_t offer_slots(int32_t n_req) {
@@ -161,23 +242,21 @@ extern "C" int smetric_sessions(const uint64_t *keys, const int64_t *blk_off, in
   OfferSlot *t = reinterpret_cast<OfferSlot *>(base);
   int32_t *jump = reinterpret_cast<int32_t *>(base + jump_offset(n_req));
   const int rgrid = (n_req + TB - 1) / TB;
+  uint32_t *filt = reinterpret_cast<uint32_t *>(session);
+  uint32_t words = 0;  // the bitmap's, 0: none
+  if (n_req <= FILT_MAX_REQ)
+    for (words = 1; 2 * words <= uint32_t(n_req) && words < FILT_MAX_WORDS;) words *= 2;
   hipLaunchKernelGGL(offer_clear_kernel, dim3(int((ns + TB - 1) / TB < 4096 ? (ns + TB - 1) / TB : 4096)), dim3(TB), 0,
-                     stream, t, ns);
+                     stream, t, ns, filt, words);
   hipLaunchKernelGGL(offer_kernel, dim3(rgrid), dim3(TB), 0, stream, keys, blk_off, n_req, n_blocks, user, turn, t, ns,
-                     status);
-  hipLaunchKernelGGL(query_kernel, dim3((n_req + TB / 64 - 1) / (TB / 64)), dim3(TB), 0, stream, keys, blk_off, n_req,
-                     n_blocks, user, turn, t, ns, parent, jump);
-  // rounds: every chain is shorter than n_req, and each round doubles the distance covered
-  int rounds = 1;
-  while ((int64_t(1) << rounds) < int64_t(n_req)) ++rounds;
-  int32_t *a = jump, *b = session;
-  for (int k = 0; k < rounds; ++k) {
-    hipLaunchKernelGGL(jump_kernel, dim3(rgrid), dim3(TB), 0, stream, a, b, n_req);
-    int32_t *tmp = a;
-    a = b;
-    b = tmp;
-  }
-  // one more round lands the result in `session` (a round at the fixed point changes nothing)
-  if (a != session) hipLaunchKernelGGL(jump_kernel, dim3(rgrid), dim3(TB), 0, stream, a, session, n_req);
+                     filt, words, status);
+  const int qw = (n_req + QT / 64 - 1) / (QT / 64);
+  if (words)
+    hipLaunchKernelGGL(query_kernel<true>, dim3(qw < 512 ? qw : 512), dim3(QT), 0, stream, keys, blk_off, n_req,
+                       n_blocks, user, turn, t, ns, filt, words, parent, jump);
+  else
+    hipLaunchKernelGGL(query_kernel<false>, dim3((n_req + TB / 64 - 1) / (TB / 64)), dim3(TB), 0, stream, keys,
+                       blk_off, n_req, n_blocks, user, turn, t, ns, filt, words, parent, jump);
+  hipLaunchKernelGGL(roots_kernel, dim3(rgrid), dim3(TB), 0, stream, jump, session, n_req);
   return hip_rc(hipGetLastError());
 }
