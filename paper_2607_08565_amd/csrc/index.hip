@@ -58,7 +58,9 @@ __global__ void fill_kernel(uint64_t *p, uint64_t n_words, uint64_t value) {
 
 __global__ void set_int_kernel(int *p, int v) { *p = v; }
 
-__global__ void unset_values_kernel(uint64_t *slots, uint64_t n_buckets) {
+// An index's slots EMPTY with unset values, its header saying that no entry has an epoch.
+__global__ void unset_values_kernel(IndexHdr *h, uint64_t *slots, uint64_t n_buckets) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) h->epoch_top = 1;
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t b = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; b < n_buckets; b += stride) {
     ulonglong2 *v = reinterpret_cast<ulonglong2 *>(slots + b * BUCKET_WORDS + SLOTS);
@@ -306,6 +308,15 @@ __device__ int place_new(const DevIndex &ix, uint64_t key, uint32_t inst, uint32
   *val_ptr(ix, c.slot) = make_val(inst, PLAIN, epoch, sess);
   trigger = c.same == uint32_t(ix.threshold);
   return PLACED;
+}
+
+// Can no entry be above `epoch`?  And the header's bound raised to it, by one thread of an
+// insert that goes through, in a kernel after those that ask.
+__device__ __forceinline__ bool epoch_tops(const DevIndex &ix, uint32_t epoch) {
+  return ix.hdr->epoch_top != 0 && epoch + 1 >= ix.hdr->epoch_top;
+}
+__device__ __forceinline__ void keep_epoch_top(const DevIndex &ix, uint32_t epoch) {
+  if (ix.hdr->epoch_top != 0 && epoch + 1 > ix.hdr->epoch_top) ix.hdr->epoch_top = epoch + 1;
 }
 
 // A REFRESHED pair was counted as new by the capacity check: take it back, one atomic
@@ -753,7 +764,7 @@ __device__ __forceinline__ void apply_pos(const DevIndex &ix, const InsWs &ws, u
   } else if (at) {
     uint64_t *vp = val_ptr(ix, int64_t(at - 1));
     const uint64_t v = *vp;
-    if (val_epoch(v) < epoch) raise_epoch_at(vp, val_kind(v), val_inst(v), epoch);
+    if (val_epoch(v) < epoch) set_epoch_at(vp, val_kind(v), val_inst(v), epoch);
   }
   uncount_refreshed(ix, rf);
   append_wave(&ws.hdr->n_trig, ws.trig, ws.list_cap, tk);  // by pair-table slot
@@ -766,6 +777,7 @@ __global__ __launch_bounds__(NT) void ins_apply_kernel(DevIndex ix, InsWs ws, co
                                                        int64_t n_blocks, const uint32_t *session, uint32_t epoch,
                                                        int per) {
   if (ws.hdr->abort) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) keep_epoch_top(ix, epoch);
   const int lane = threadIdx.x & 63;
   if (blk_off) {
     const int groups = NT / per;
@@ -893,6 +905,7 @@ __global__ __launch_bounds__(TB) void insp_classify_kernel(DevIndex ix, ProbeVie
   // entry the index would not overflow): refreshes are done here, in place.
   const bool req_bad = __ballot(ws.bad[tid & (HEAD_WG - 1)] != 0) != 0;  // one flag per lane
   const bool inl = !pv.hdr->bad_key && !req_bad && ix.hdr->n_entries + n <= ix.capacity;
+  const bool top = epoch_tops(ix, epoch);
   if (blockIdx.x == 0 && tid == 0) ws.hdr->inl = inl;
   Cand *seg = ws.cand + uint64_t(blockIdx.x) * ws.seg;
   constexpr int CU = 2;
@@ -954,18 +967,21 @@ __global__ __launch_bounds__(TB) void insp_classify_kernel(DevIndex ix, ProbeVie
     }
     if (inl) {
       // epoch = max(old, epoch) without a read: the entry is (key, t), a member for a HOT
-      // key and a plain slot otherwise.  Where the slot was found by a walk its value is
-      // already here, and an entry seen at the epoch (or a newer one) is left alone: a
-      // shared prefix's members are refreshed by every request routed to their instance,
-      // and atomics on one address are served one after another.  8,192 requests sharing
-      // 2,048 blocks on 128 instances: this kernel 7.1 -> 1.0 ms per batch; 4,096 requests
-      // sharing 16 prefixes of 128 blocks on 64 instances: 0.74 -> 0.20 ms.  (A value read
-      // before another request's atomic only costs one more atomic; reading it again at
-      // device scope first gave the same times.)
+      // key and a plain slot otherwise.  A store while no entry can be above the epoch: 21M
+      // refreshes in a table of 4.3 GB, this kernel 980 -> 790 us per batch; 3.1M in one of
+      // some 150 MB, 161 -> 68 us.  Where the slot was found by a walk its value is already
+      // here, and an entry seen at the epoch (or a newer one) is left alone: a shared prefix's
+      // members are refreshed by every request routed to their instance, and atomics on one
+      // address are served one after another (8,192 requests sharing 2,048 blocks on 128
+      // instances, with atomics: 7.1 -> 1.0 ms per batch).
 #pragma unroll
       for (int u = 0; u < CU; ++u)
-        if (slot[u] >= 0 && !fresh[u])
-          raise_epoch_at(val_ptr(ix, slot[u]), desc_kind(d[u]) == D_HOT ? MEMBER : PLAIN, uint32_t(t[u]), epoch);
+        if (slot[u] >= 0 && !fresh[u]) {
+          uint64_t *vp = val_ptr(ix, slot[u]);
+          const uint32_t kind = desc_kind(d[u]) == D_HOT ? MEMBER : PLAIN;
+          if (top) set_epoch_at(vp, kind, uint32_t(t[u]), epoch);
+          else raise_epoch_at(vp, kind, uint32_t(t[u]), epoch);
+        }
     } else {
 #pragma unroll
       for (int u = 0; u < CU; ++u)
@@ -1369,6 +1385,7 @@ __device__ void refresh_pass(const DevIndex &ix, const ProbeView &pv, const InsW
 __global__ __launch_bounds__(TB) void insp_place_kernel(DevIndex ix, ProbeView pv, InsWs ws,
                                                         const uint32_t *session, uint32_t epoch) {
   if (ws.hdr->abort) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) keep_epoch_top(ix, epoch);
   const uint64_t n = ws.hdr->n_cand;
   const uint64_t span = uint64_t(gridDim.x) * TB;
   for (uint64_t p0 = uint64_t(blockIdx.x) * TB; p0 < n; p0 += span) {  // whole workgroups iterate together
@@ -1583,6 +1600,7 @@ __global__ __launch_bounds__(SI_T) void ins_small_kernel(DevIndex ix, ProbeView 
   }
   __syncthreads();
   if (err) return;
+  if (t == 0) keep_epoch_top(ix, epoch);
   uint32_t trig = 0, def = 0;  // bit u: pair u converts its key, was deferred
 #pragma unroll
   for (int u = 0; u < SI_U; ++u) {
@@ -2454,7 +2472,8 @@ extern "C" int smetric_index_init(smetric_index *idx, void *mem, uint64_t mem_by
   layout_for(capacity, n_instances, n_slots, L);
   if (int rc2 = fill(mem, L.bytes, 0, stream)) return rc2;
   // every slot EMPTY with an unset value
-  hipLaunchKernelGGL(unset_values_kernel, dim3(grid_for(L.n_buckets)), dim3(TB), 0, stream, idx->slots, L.n_buckets);
+  hipLaunchKernelGGL(unset_values_kernel, dim3(grid_for(L.n_buckets)), dim3(TB), 0, stream,
+                     static_cast<IndexHdr *>(idx->hdr), idx->slots, L.n_buckets);
   return hip_rc(hipGetLastError());
 }
 
