@@ -296,15 +296,14 @@ class Setup:
 CALL_KERNELS = {
     # smetric_hash_partition: the state cleared, the block keys (the hash itself taking the
     # region counts), each block's request, then the region partition's scan and scatter
-    "hash": ["zero2_kernel", "hash16_kernel<8, true>", "req_of_kernel", "part_scan_kernel", "part_scatter_kernel"],
+    "hash": ["zero2_kernel", "hash16_kernel<8, 1, 1>", "req_of_kernel", "part_scan_kernel", "part_scatter_kernel"],
     # smetric_probe_lookup: each request's probe bound, then one holder descriptor per block,
     # in region order
     "probe": ["zero2_kernel", "bound_kernel", "probe_kernel<2>"],
-    "match": ["match_kernel<1, true>"],
+    "match": ["match_kernel<1, 1, 1>"],
     "route": ["route_kernel<0>"],
-    "insert": ["fill_kernel", "insp_valid_kernel", "insp_classify_kernel", "insp_size_kernel", "insp_bcount_kernel",
-               "insp_bscan_kernel", "insp_size2_kernel", "insp_bscatter_kernel",
-               "insp_bdedupe_kernel", "insp_check_kernel", "insp_place_kernel", "spill_kernel",
+    "insert": ["insp_head_kernel", "insp_classify_kernel", "insp_bcount_kernel", "insp_bscan_kernel",
+               "insp_bscatter_kernel", "insp_bdedupe_kernel", "insp_place_kernel", "spill_kernel",
                "deferred_kernel"],
 }
 

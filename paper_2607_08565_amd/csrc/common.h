@@ -58,7 +58,7 @@ __device__ __forceinline__ void set_epoch_at(uint64_t *vp, uint32_t kind, uint32
 // the chain never takes it for an entry.
 constexpr uint64_t VAL_UNSET = uint64_t(3) << 40;
 // The dump's value layout (instance << 48 | epoch << 24 | session), also the layout of the
-// gathered entries that eviction selects on and rebuilds from.
+// entries that an eviction copies out to select among and to enter again.
 __host__ __device__ inline uint64_t val_dump(uint64_t v) {
   return (uint64_t(val_inst(v)) << 48) | (uint64_t(val_epoch(v)) << 24) | val_session(v);
 }

@@ -20,7 +20,7 @@
 // simply stay plain.  Slots are only ever claimed (EMPTY -> key by compare-and-swap) or
 // turned into tombstones, so every slot of a key lies before the first EMPTY slot of its
 // chain.  Eviction selects the oldest entries by (epoch, key, instance) digit by digit
-// over a gathered copy of the entries, then turns them into tombstones in place, or --
+// among those that one scan finds near the cut, then turns them into tombstones in place, or --
 // once tombstones would take too many slots -- rebuilds the table from the survivors.
 //
 // Insert pipeline (no sort, no host synchronisation):
