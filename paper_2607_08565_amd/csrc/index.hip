@@ -1264,8 +1264,9 @@ __global__ __launch_bounds__(TB) void insp_bscatter_kernel(DevIndex ix, InsWs ws
 }
 
 // Enter candidate (key, mine) in a bin's LDS pair table (the pair table's rule: a slot's
-// key is claimed first, then its instance; the same pair keeps the lowest request).
-__device__ __forceinline__ void lds_pair(unsigned long long *tk, unsigned long long *tw, uint64_t key,
+// key is claimed first, then its instance; the same pair keeps the lowest request).  True:
+// the pair is new there.
+__device__ __forceinline__ bool lds_pair(unsigned long long *tk, unsigned long long *tw, uint64_t key,
                                          uint64_t mine) {
   uint32_t h = uint32_t(mix64(key ^ ((mine >> 32) * 0xC2B2AE3D27D4EB4Full))) & (DT - 1);
   for (int step = 0; step < DT; ++step, h = (h + 1) & (DT - 1)) {
@@ -1276,30 +1277,37 @@ __device__ __forceinline__ void lds_pair(unsigned long long *tk, unsigned long l
     while (true) {
       if (w == 0) {
         const unsigned long long prev = atomicCAS(&tw[h], 0ull, (unsigned long long)mine);
-        if (prev == 0) return;
+        if (prev == 0) return true;
         w = prev;
         continue;
       }
       if ((w >> 32) == (mine >> 32)) {
         if (mine < w) atomicMin(&tw[h], (unsigned long long)mine);
-        return;
+        return false;
       }
       break;  // another instance's pair: keep probing
     }
   }
+  return false;
 }
 
 // Dedupe pass: each bin of at most BIN_CAP candidates is deduplicated in an LDS pair
 // table and its distinct pairs written to the front of its range of np (the rest get
-// KEY_EMPTY); a larger bin sends its candidates through the fallback pair table in
-// place.  Workgroups take bins in order; a bin's candidates are loaded (all at once)
+// KEY_EMPTY).  A larger bin is mostly one key's pairs over and over (a prefix that many
+// requests of the batch share): its candidates stream through the same table, DD_S a thread
+// at a time, as long as the distinct pairs leave the table at most half full before each
+// round; a bin of more goes through the fallback pair table in place, from its start.
+// (8,192 requests sharing 2,048 blocks, four batches in all: 14.0 -> 12.9 ms.)  Workgroups take bins in order; a bin's candidates are loaded (all at once)
 // before its table is cleared.
 constexpr int DD_T = 512;
 constexpr int DD_U = BIN_CAP / DD_T;
+constexpr int DD_S = 2;
 static_assert(BIN_CAP % DD_T == 0 && DT % DD_T == 0, "whole candidates and slots per thread");
+static_assert(DT / 2 + DD_S * DD_T < DT, "a round's new pairs never fill the table");
 __global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(DevIndex ix, InsWs ws) {
   __shared__ unsigned long long tk[DT], tw[DT];
   __shared__ uint32_t wt[DD_T / 64];
+  __shared__ uint32_t n_occ;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const uint32_t nbin = uint32_t(ws.hdr->nsub) * NREG;
   const uint64_t nd2 = ws.hdr->n_dd2;
@@ -1309,7 +1317,33 @@ __global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(DevIndex ix, InsWs w
   for (uint32_t b = blockIdx.x; b < nbin; b += gridDim.x) {
     const uint32_t lo = ws.bstart[b], hi = ws.bstart[b + 1], m = hi - lo;
     if (m == 0) continue;
-    if (m > uint32_t(BIN_CAP)) {
+    const bool big = m > uint32_t(BIN_CAP);
+    bool over = false;
+    if (big) {
+      for (int j = t; j < DT; j += DD_T) {
+        tk[j] = 0;
+        tw[j] = 0;
+      }
+      if (t == 0) n_occ = 0;
+      __syncthreads();
+      for (uint32_t k0 = lo; k0 < hi && !over; k0 += DD_S * DD_T) {  // whole workgroups iterate together
+        Cand e[DD_S];
+#pragma unroll
+        for (int u = 0; u < DD_S; ++u) {
+          const uint32_t k = k0 + u * DD_T + t;
+          e[u] = k < hi ? ws.bcand[k] : Cand{KEY_EMPTY, 0};
+        }
+        uint32_t claimed = 0;
+#pragma unroll
+        for (int u = 0; u < DD_S; ++u)
+          if (e[u].key != KEY_EMPTY) claimed += lds_pair(tk, tw, e[u].key, e[u].w2);
+        if (claimed) atomicAdd(&n_occ, claimed);
+        __syncthreads();
+        over = n_occ > uint32_t(DT / 2) && hi - k0 > uint32_t(DD_S * DD_T);
+        __syncthreads();  // read by all before the next round adds
+      }
+    }
+    if (over) {
       for (uint32_t k = lo + t; k < hi; k += DD_T) {
         const Cand e = ws.bcand[k];
         const int64_t h = dedupe_pair<false>(ws, nd2, e.key, e.w2);
@@ -1319,21 +1353,23 @@ __global__ __launch_bounds__(DD_T) void insp_bdedupe_kernel(DevIndex ix, InsWs w
       }
       continue;
     }
-    Cand e[DD_U];
+    if (!big) {
+      Cand e[DD_U];
 #pragma unroll
-    for (int u = 0; u < DD_U; ++u) {
-      const uint32_t k = lo + u * DD_T + t;
-      e[u] = k < hi ? ws.bcand[k] : Cand{KEY_EMPTY, 0};
-    }
-    for (int j = t; j < DT; j += DD_T) {
-      tk[j] = 0;
-      tw[j] = 0;
-    }
-    __syncthreads();
+      for (int u = 0; u < DD_U; ++u) {
+        const uint32_t k = lo + u * DD_T + t;
+        e[u] = k < hi ? ws.bcand[k] : Cand{KEY_EMPTY, 0};
+      }
+      for (int j = t; j < DT; j += DD_T) {
+        tk[j] = 0;
+        tw[j] = 0;
+      }
+      __syncthreads();
 #pragma unroll
-    for (int u = 0; u < DD_U; ++u)
-      if (e[u].key != KEY_EMPTY) lds_pair(tk, tw, e[u].key, e[u].w2);
-    __syncthreads();
+      for (int u = 0; u < DD_U; ++u)
+        if (e[u].key != KEY_EMPTY) lds_pair(tk, tw, e[u].key, e[u].w2);
+      __syncthreads();
+    }
     // compact the occupied slots: thread t owns slots [t Q, t Q + Q)
     constexpr int Q = DT / DD_T;
     uint32_t occ = 0;
