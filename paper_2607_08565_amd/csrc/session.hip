@@ -244,7 +244,16 @@ extern "C" int smetric_sessions(const uint64_t *keys, const int64_t *blk_off, in
   const int rgrid = (n_req + TB - 1) / TB;
   uint32_t *filt = reinterpret_cast<uint32_t *>(session);
   uint32_t words = 0;  // the bitmap's, 0: none
-  if (n_req <= FILT_MAX_REQ)
+  // session may be the memory of another array of the call, read until the roots are
+  // written: no bitmap there then
+  const uint64_t n4 = 4 * uint64_t(n_req);
+  const uintptr_t s0 = reinterpret_cast<uintptr_t>(session), s1 = s0 + n4;
+  auto apart = [&](const void *p, uint64_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    return !bytes || a >= s1 || a + bytes <= s0;
+  };
+  if (n_req <= FILT_MAX_REQ && apart(keys, 8 * uint64_t(n_blocks)) && apart(blk_off, 2 * n4 + 8) && apart(user, n4) &&
+      apart(turn, n4) && apart(parent, n4))
     for (words = 1; 2 * words <= uint32_t(n_req) && words < FILT_MAX_WORDS;) words *= 2;
   hipLaunchKernelGGL(offer_clear_kernel, dim3(int((ns + TB - 1) / TB < 4096 ? (ns + TB - 1) / TB : 4096)), dim3(TB), 0,
                      stream, t, ns, filt, words);

@@ -52,3 +52,27 @@ def test_one_chain(order):
     turn = np.arange(R) if order == "arrival" else np.arange(R)[::-1].copy()
     op = _check(np.zeros(0, np.uint64), np.zeros(R + 1, np.int64), np.zeros(R, np.int64), turn)
     assert (op >= 0).sum() == (R - 1 if order == "arrival" else 0)
+
+
+@pytest.mark.parametrize("over", ["turn", "user", "parent", "keys", "blk_off"])
+@pytest.mark.parametrize("R", [33, 700, 20_000])
+def test_session_written_over_another_array(R, over):
+    """The session array may be one of the call's other arrays: it is written after the last
+    read of them."""
+    rng = np.random.default_rng(R)
+    stream, nb = rng.integers(0, R // 6, R), rng.integers(1, 41, R)
+    blk_off = np.zeros(R + 1, np.int64)
+    blk_off[1:] = np.cumsum(nb)
+    at = np.arange(int(blk_off[-1])) - np.repeat(blk_off[:-1], nb)
+    keys = rng.integers(1, 2**63, (R // 6, 40), dtype=np.int64).astype(np.uint64)[np.repeat(stream, nb), at]
+    user, turn = (stream % 97).astype(np.uint32), (nb // 8).astype(np.int32)
+    op, os_ = oracle.sessions(keys, blk_off, user, turn)
+    assert (op >= 0).any()
+    d_keys, d_user, d_turn, d_off = to_dev(keys.view(np.int64)), to_dev(user.view(np.int32)), to_dev(turn), to_dev(blk_off)
+    parent = torch.empty(R, dtype=torch.int32, device="cuda")
+    session = {"turn": d_turn, "user": d_user, "parent": parent, "keys": d_keys.view(torch.int32)[:R],
+               "blk_off": d_off.view(torch.int32)[:R]}[over]
+    gp, gs = S.sessions(d_keys.view(torch.uint64), d_off, len(at), d_user.view(torch.uint32), d_turn,
+                        parent=parent, session=session)
+    assert np.array_equal(gs.cpu().numpy(), os_)
+    assert over == "parent" or np.array_equal(gp.cpu().numpy(), op)
