@@ -70,12 +70,19 @@ __host__ __device__ inline uint32_t dump_session(uint64_t d) { return uint32_t(d
 struct IndexHdr {
   unsigned long long n_entries;
   int status;
-  unsigned int epoch_top;       // one more than the highest epoch an entry may have; 0: not kept
-                                // (an index whose bytes were written before it was)
+  unsigned int epoch_top;       // one more than the highest epoch an entry may have, where
+                                // epoch_owner is this process; 0: not kept
   unsigned long long rec_used;  // bitmap records handed out (may exceed n_records: exhausted)
-  unsigned long long pad[29];
+  unsigned long long epoch_owner;  // the process whose inserts alone have kept epoch_top
+  unsigned long long pad[28];
 };
 static_assert(sizeof(IndexHdr) == 256, "header size");
+
+// This process, as epoch_owner: the start's time, process number and load address, mixed.
+// An index's bytes may have been through another process since this one wrote them, where a
+// build that knows nothing of epoch_top raised entries past it; such bytes, restored
+// after a restart, carry another owner, and their epochs are then raised by atomics.
+uint64_t process_owner();
 
 // Index view passed by value to kernels.
 struct DevIndex {
@@ -90,6 +97,7 @@ struct DevIndex {
   int32_t threshold;  // spill threshold T
   uint64_t nb_inv;    // floor(2^64 / n_buckets) (any value when n_buckets = 1): see scaled_floor
   uint8_t *mask;      // n_buckets displacement masks (see mask_of)
+  uint64_t owner;     // process_owner()
 };
 
 inline DevIndex dev_view(const smetric_index *ix) {
@@ -105,6 +113,7 @@ inline DevIndex dev_view(const smetric_index *ix) {
   d.threshold = ix->spill_threshold;
   d.nb_inv = d.n_buckets > 1 ? uint64_t((static_cast<unsigned __int128>(1) << 64) / d.n_buckets) : ~uint64_t(0);
   d.mask = reinterpret_cast<uint8_t *>(ix->pool + ix->n_records * uint64_t(ix->bitmap_words));  // after the pool
+  d.owner = process_owner();
   return d;
 }
 // Bytes of the displacement masks (whole 32-bit words: they are set with 32-bit atomics).

@@ -37,9 +37,25 @@
 // the direct form's size takes the region-ordered passes.
 #include <rocprim/device/device_radix_sort.hpp>
 
+#include <time.h>
+#include <unistd.h>
+
 #include "common.h"
 
 namespace smk {
+
+uint64_t process_owner() {
+  static const uint64_t owner = [] {
+    static char here;
+    timespec t{};
+    clock_gettime(CLOCK_REALTIME, &t);
+    uint64_t x = mix64(uint64_t(t.tv_sec) * 1000000000ull + uint64_t(t.tv_nsec));
+    x = mix64(x ^ (uint64_t(getpid()) << 40)) ^ reinterpret_cast<uintptr_t>(&here);
+    return mix64(x) | 1;  // 0: an index written before the word was
+  }();
+  return owner;
+}
+
 namespace {
 
 constexpr int TB = 256;
@@ -59,8 +75,11 @@ __global__ void fill_kernel(uint64_t *p, uint64_t n_words, uint64_t value) {
 __global__ void set_int_kernel(int *p, int v) { *p = v; }
 
 // An index's slots EMPTY with unset values, its header saying that no entry has an epoch.
-__global__ void unset_values_kernel(IndexHdr *h, uint64_t *slots, uint64_t n_buckets) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) h->epoch_top = 1;
+__global__ void unset_values_kernel(IndexHdr *h, uint64_t owner, uint64_t *slots, uint64_t n_buckets) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    h->epoch_top = 1;
+    h->epoch_owner = owner;
+  }
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t b = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; b < n_buckets; b += stride) {
     ulonglong2 *v = reinterpret_cast<ulonglong2 *>(slots + b * BUCKET_WORDS + SLOTS);
@@ -313,7 +332,7 @@ __device__ int place_new(const DevIndex &ix, uint64_t key, uint32_t inst, uint32
 // Can no entry be above `epoch`?  And the header's bound raised to it, by one thread of an
 // insert that goes through, in a kernel after those that ask.
 __device__ __forceinline__ bool epoch_tops(const DevIndex &ix, uint32_t epoch) {
-  return ix.hdr->epoch_top != 0 && epoch + 1 >= ix.hdr->epoch_top;
+  return ix.hdr->epoch_top != 0 && epoch + 1 >= ix.hdr->epoch_top && ix.hdr->epoch_owner == ix.owner;
 }
 __device__ __forceinline__ void keep_epoch_top(const DevIndex &ix, uint32_t epoch) {
   if (ix.hdr->epoch_top != 0 && epoch + 1 > ix.hdr->epoch_top) ix.hdr->epoch_top = epoch + 1;
@@ -2509,7 +2528,7 @@ extern "C" int smetric_index_init(smetric_index *idx, void *mem, uint64_t mem_by
   if (int rc2 = fill(mem, L.bytes, 0, stream)) return rc2;
   // every slot EMPTY with an unset value
   hipLaunchKernelGGL(unset_values_kernel, dim3(grid_for(L.n_buckets)), dim3(TB), 0, stream,
-                     static_cast<IndexHdr *>(idx->hdr), idx->slots, L.n_buckets);
+                     static_cast<IndexHdr *>(idx->hdr), process_owner(), idx->slots, L.n_buckets);
   return hip_rc(hipGetLastError());
 }
 

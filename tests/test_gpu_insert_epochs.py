@@ -2,7 +2,7 @@
 epochs that rise, stay, fall and rise again, in an index that keeps its highest epoch and in
 one whose bytes were written before it was kept (its word in the header zero); inserts that
 change nothing (too large, a bad target) with a higher epoch in between; after an eviction in
-place and after a rebuild."""
+place and after a rebuild; bytes that another process wrote to in between."""
 import numpy as np
 import pytest
 
@@ -41,3 +41,24 @@ def test_epochs_only_rise(R, nb, probed, kept):
             assert pair.oix.evict(1, 30 if k == 4 else 2) == 0
         insert_both(pair, probed, d_keys, d_boff, n, okeys, blk_off, inst, sess, epoch)
         pair.compare_index(f"insert {k} at epoch {epoch}")
+
+
+def test_epochs_raised_by_another_process():
+    """An index's bytes that went through a process that raises epochs and leaves the header's
+    highest one as it was: restored here, its entries keep the newer epochs."""
+    rng = np.random.default_rng(8)
+    R, nb = 3000, 270_000
+    pair = Pair(2 * nb, 40)
+    toks, off = _sized(rng, R, nb, 6)
+    d_boff, n, d_keys, okeys, blk_off = pair.hash_both(toks, off)
+    inst, sess = rng.integers(0, 40, R), rng.permutation(R)
+    for epoch in (1, 20, 10):
+        if epoch == 20:
+            before = pair.gix.mem[12:16].clone()
+        insert_both(pair, True, d_keys, d_boff, n, okeys, blk_off, inst, sess, epoch)
+        if epoch == 20:
+            snap = pair.gix.snapshot()
+            snap[12:16] = before
+            snap[24:32] ^= 0x55  # the process that keeps it
+            pair.gix.restore(snap)
+        pair.compare_index(f"epoch {epoch}")
