@@ -740,7 +740,12 @@ __global__ __launch_bounds__(64 * NW) void route_seq_kernel(const int32_t *__res
       const uint64_t m = __ballot(r < n_req && q_ok && (f & 1) && (f & 6) != 6);
       if (lane == 0) smask[wave * PER + j] = m;
     }
-    if (NW > 1) __syncthreads();
+    if (NW > 1) {
+      __syncthreads();
+    } else {  // lane 0's stores before every lane's load
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
     my_mask = smask[lane];
   };
   // the next scans to request rows for: the rest of window fw's, then the windows after it
