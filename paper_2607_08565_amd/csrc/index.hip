@@ -1954,7 +1954,9 @@ __device__ __forceinline__ void pick_bin(const uint32_t *h, uint32_t left, BinPi
 
 // Where the cut lies, roughly, from a sample: EV_SAMPLE buckets evenly over the table (keys
 // are hashes, but a key's home bucket follows its top bits).  It also clears the counters.
-// Without a sample the range is everything.
+// Without a sample the range is everything.  In an empty index this pass and the two after it
+// stop at the header's count (2^28 slots: 770 us -> 31; a header read by the host alone is 26,
+// but would come before every other eviction).
 constexpr int EV_SAMPLE = 4096;
 __global__ __launch_bounds__(TB) void evict_sample_kernel(DevIndex ix, EvictState *st, unsigned long long *counts,
                                                           uint64_t *sample) {
@@ -1967,7 +1969,7 @@ __global__ __launch_bounds__(TB) void evict_sample_kernel(DevIndex ix, EvictStat
     }
     if (threadIdx.x < EV_LANES * EV_LINE) counts[threadIdx.x] = 0;
   }
-  if (!sample) return;
+  if (!sample || ix.hdr->n_entries == 0) return;
   const uint32_t i = blockIdx.x * TB + threadIdx.x;  // EV_SAMPLE * SLOTS threads
   const uint64_t b = (uint64_t(i / SLOTS) * ix.n_buckets) / EV_SAMPLE;
   const uint64_t *p = ix.slots + b * BUCKET_WORDS + i % SLOTS;
@@ -1985,6 +1987,7 @@ __global__ __launch_bounds__(FIN_T) void evict_range_kernel(const uint64_t *__re
   __shared__ BinPick bp;
   __shared__ unsigned long long s_or, s_and;
   __shared__ uint32_t s_n;
+  if (st->n_entries == 0) return;
   const int t = threadIdx.x;
   uint64_t x[PER];
 #pragma unroll
@@ -2051,6 +2054,7 @@ __global__ __launch_bounds__(TB) void evict_scan_kernel(DevIndex ix, EvictState 
                                                         uint64_t *ck, uint64_t *cv, uint64_t cap) {
   __shared__ WaveStage stage;
   __shared__ uint32_t wc[TB / 64][3];
+  if (st->n_entries == 0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t lo = st->lo, hi = st->hi;
   constexpr int GS = TILE * SLOTS / TB;

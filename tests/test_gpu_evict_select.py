@@ -2,7 +2,8 @@
 dumped entry set: one or few epochs of 65,535 to 100,001 entries, so that the entries left on
 the digits lie at, below and above the 2^16 that one workgroup settles; tables below and above
 the 2^15 buckets from which a sample narrows the entries copied out; a table whose sampled
-buckets hold one epoch and the others another, so that the sample's range misses the cut; keys
+buckets hold one epoch and the others another, so that the sample's range misses the cut; an
+empty table, which is not read; keys
 on several instances (the last digits decide); evicted in place (small fractions of a roomy
 table) and by a rebuild (large ones); bucket counts that are no multiple of a tile."""
 import numpy as np
@@ -77,3 +78,20 @@ def test_sample_that_misses():
         pair.gix.evict(num, den)
         assert pair.oix.evict(num, den) == 0
         pair.compare_index(f"evict {num}/{den}")
+
+
+@pytest.mark.parametrize("slots", [1 << 16, 1 << 19])
+def test_empty_index(slots):
+    """Nothing of the table is read into the workspace: past the counters it stays as it is."""
+    rng = np.random.default_rng(3)
+    pair = Pair(slots // 2, 64, n_slots=slots)
+    ws = pair.gix._workspace(pair.gix.evict_ws_bytes())
+    for _ in range(2):  # never filled; emptied
+        ws.fill_(0xA5)
+        for num, den in ((1, 20), (1, 1)):
+            pair.gix.evict(num, den)
+        assert bool((ws[256 + 8 * 4096:] == 0xA5).all())
+        pair.compare_index("empty")
+        _fill(pair, rng, 5000, 7, 64, 10)
+        pair.gix.evict(1, 1)
+        assert pair.oix.evict(1, 1) == 0
