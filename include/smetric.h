@@ -216,9 +216,8 @@ int smetric_probe(const smetric_index *idx, const uint64_t *keys, const int64_t 
  * only while the index cannot overflow whatever those blocks are (entries + n_blocks <=
  * capacity), so the insert's capacity check stays exact; otherwise every block is probed.
  * Batches of at most 2^18 blocks are not ordered by region (the region order pays for
- * large batches only): their blocks are looked up in request order, in groups, up to the first
- * group with a block that no instance holds, under the same condition; the blocks of that
- * group from the missing one on count as the search's probes.
+ * large batches only): every block is looked up, and under the same condition a request's
+ * blocks from its first of no holder on count as the search's probes.
  * smetric_probe_stats (synchronizes): blocks the last lookup on the state probed, and the
  * probes its bound's searches made. */
 int smetric_probe_partition(const smetric_index *idx, const uint64_t *keys, const int64_t *blk_off,

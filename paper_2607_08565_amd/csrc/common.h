@@ -290,7 +290,7 @@ struct ProbeHdr {
   unsigned long long tot[NREG];     // blocks per region
   unsigned long long n_skip;        // blocks the lookup did not probe (past their request's bound)
   unsigned long long n_search;      // probes the bound's search made
-  unsigned long long n_rec;         // direct form: requests whose counts the lookup left in records (0: above)
+  unsigned long long bounded;       // direct form: the lookup could have left blocks out
 };
 struct ProbeView {
   ProbeHdr *hdr;
@@ -336,7 +336,8 @@ inline uint64_t probe_layout(int64_t n_blocks, ProbeView *v, void *base) {
 
 // Direct form of a probe state, for batches of at most DIRECT_MAX blocks: no region order.
 // The hash (or one pass over the keys) writes part_key and part_req in block order, the
-// lookup desc_p in block order; inv, part_blk, skip and the region counts stay unused.
+// lookup desc_p in block order (and in skip and inv what its counts are taken from); part_blk
+// and the region counts stay unused.
 // Such a batch touches at most DIRECT_MAX lines of the table, which the translation caches
 // hold in any order, and its time is launches and round trips: ordering it took 4 of 5
 // launches and two thirds of the time.  64 requests of 64 to 170 blocks: 118 us of kernels in
@@ -345,11 +346,11 @@ inline uint64_t probe_layout(int64_t n_blocks, ProbeView *v, void *base) {
 // 4,096 sessions in batches of 1 to 5 M blocks (its first ones then direct) takes 5.62
 // against 5.52 ms, at 2^22 6.08, and 1,024 long sessions 8.84 against 7.35 ms.
 // With at most DIRECT_REQ requests every request has a flag word (in `hist`: 0 = valid)
-// that its own workgroup writes, and a record of the lookup's counts (in `base`), so nothing has
-// to be cleared by a launch of its own; with more, errors and counts go to the header.
+// that its own workgroup writes, so nothing has to be cleared by a launch of its own; with
+// more, errors go to the header.
 constexpr uint64_t DIRECT_MAX = uint64_t(1) << 18;
 constexpr int32_t DIRECT_REQ = 16384;
-static_assert(uint64_t(DIRECT_REQ) <= uint64_t(NREG) * PART_WG, "a flag word and a record per request");
+static_assert(uint64_t(DIRECT_REQ) <= uint64_t(NREG) * PART_WG, "a flag word per request");
 inline bool direct_batch(uint64_t n_blocks) { return n_blocks <= DIRECT_MAX; }
 __device__ __forceinline__ bool request_tiles(const int64_t *blk_off, int32_t r, int32_t n_req, int64_t n_blocks,
                                               int64_t &b0, int64_t &nb) {
@@ -365,8 +366,7 @@ __device__ __forceinline__ void direct_flag(const ProbeView &pv, int32_t r, int3
     if (r == 0) {
       pv.hdr->err = 0;
       pv.hdr->n = uint64_t(n_blocks);
-      pv.hdr->n_skip = pv.hdr->n_search = 0;
-      pv.hdr->n_rec = 0;
+      pv.hdr->n_skip = pv.hdr->n_search = pv.hdr->bounded = 0;
     }
   } else {  // the header was cleared by a launch before
     if (!ok) atomicCAS(&pv.hdr->err, 0, SMETRIC_EINVAL);

@@ -540,19 +540,29 @@ __global__ __launch_bounds__(TB) void probe_kernel(DevIndex ix, ProbeView pv) {
 // ---------------------------------------------------------------------------------
 // Direct form: batches of at most DIRECT_MAX blocks
 // ---------------------------------------------------------------------------------
-// The state from given keys: one workgroup per request.
-__global__ __launch_bounds__(TB) void direct_partition_kernel(ProbeView pv, const uint64_t *__restrict__ keys,
-                                                              const int64_t *__restrict__ blk_off, int32_t n_req,
-                                                              int64_t n_blocks) {
+// The state from given keys: one workgroup per request, of as many threads as its blocks
+// fill (one request of 2^18 blocks: 195 us by 256 threads, 72 by 1,024; 134 in region order).
+constexpr int DP_T = 1024;
+__global__ __launch_bounds__(DP_T) void direct_partition_kernel(ProbeView pv, const uint64_t *__restrict__ keys,
+                                                                const int64_t *__restrict__ blk_off, int32_t n_req,
+                                                                int64_t n_blocks) {
   const int32_t r = blockIdx.x;
   int64_t b0, nb;
   const bool ok = request_tiles(blk_off, r, n_req, n_blocks, b0, nb);
   if (threadIdx.x == 0) direct_flag(pv, r, n_req, n_blocks, ok);
   if (!ok) return;
+#pragma unroll 4
   for (int64_t j = threadIdx.x; j < nb; j += blockDim.x) {
     pv.part_key[b0 + j] = keys[b0 + j];
     pv.part_req[b0 + j] = uint32_t(r);
   }
+}
+// Threads per request: about one group of blocks each.
+int direct_threads(int64_t n_blocks, int32_t n_req) {
+  const int64_t mean = n_req > 0 ? n_blocks / n_req : 0;
+  int nt = 64;
+  while (nt < DP_T && nt < mean) nt <<= 1;
+  return nt;
 }
 
 // Holder descriptor of one key.
@@ -571,63 +581,36 @@ __device__ uint64_t describe(const DevIndex &ix, uint64_t key) {
   return w.out;
 }
 
-// The lookup, one workgroup per request: its blocks are described in order, blockDim.x at
-// a time, up to the first group that holds a block of no instance -- the match reads
-// nothing past that block -- and the groups after it get NONE without a read, under the
-// same condition as the region-ordered form's bound (see above).  The whole chip walks a
-// few thousand chains at once, so a search for the bound would only add round trips.
-__global__ __launch_bounds__(512) void direct_lookup_kernel(DevIndex ix, ProbeView pv, const uint64_t *__restrict__ keys,
-                                                            const int64_t *__restrict__ blk_off, int32_t n_req,
-                                                            int64_t n_blocks) {
-  __shared__ uint32_t miss_at[8];
-  const int32_t r = blockIdx.x;
-  const int t = threadIdx.x, nt = blockDim.x;
-  int64_t b0, nb;
-  const bool tiles = request_tiles(blk_off, r, n_req, n_blocks, b0, nb);
-  const bool rec = n_req <= DIRECT_REQ;
-  if (t == 0 && (!tiles || (rec && pv.hist[r]))) atomicCAS(&pv.hdr->err, 0, SMETRIC_EINVAL);
-  if (!tiles) nb = 0;
-  const bool bounded = ix.hdr->n_entries + uint64_t(n_blocks) <= ix.capacity;
-  int64_t j0 = 0, hi = nb;
-  for (; j0 < nb; j0 += nt) {
-    const int64_t j = j0 + t;
-    uint64_t d = 0;
-    if (j < nb) {
-      d = describe(ix, keys[b0 + j]);
-      pv.desc_p[b0 + j] = d;
-    }
-    if (!bounded) continue;
-    const uint64_t miss = __ballot(j < nb && desc_kind(d) == D_NONE);
-    if ((t & 63) == 0) miss_at[t >> 6] = miss ? uint32_t(t) + __builtin_ctzll(miss) : 0xFFFFFFFFu;
-    __syncthreads();
-    uint32_t first = 0xFFFFFFFFu;
-    for (int w = 0; w < nt / 64; ++w) first = miss_at[w] < first ? miss_at[w] : first;
-    __syncthreads();
-    if (first != 0xFFFFFFFFu) {
-      hi = j0 + first;
-      j0 += nt;
-      break;
+// The lookup: every block, one per thread, whatever its request -- the whole chip walks at
+// most DIRECT_MAX chains at once, so a bound on a request's probes would only add round trips.
+// The first threads also check the requests.  For smetric_probe_stats a wavefront leaves
+// two bits a block: no holder (in skip), its request's first (in inv).
+// 2^18 blocks held in a table of 100M entries, as one request: a workgroup per request that
+// stops at its first block of no holder 4,530 us, so 24, in region order 53; as 1,024
+// requests 22, 21 and 62.
+__global__ __launch_bounds__(TB) void direct_lookup_kernel(DevIndex ix, ProbeView pv, const uint64_t *__restrict__ keys,
+                                                           const int64_t *__restrict__ blk_off, int32_t n_req,
+                                                           int64_t n_blocks) {
+  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, span = int64_t(gridDim.x) * blockDim.x;
+  const int lane = threadIdx.x & 63;
+  const bool flags = n_req <= DIRECT_REQ;
+  if (t == 0) pv.hdr->bounded = ix.hdr->n_entries + uint64_t(n_blocks) <= ix.capacity;
+  for (int64_t r = t; r < n_req; r += span) {
+    int64_t b0, nb;
+    if (!request_tiles(blk_off, int32_t(r), n_req, n_blocks, b0, nb) || (flags && pv.hist[r]))
+      atomicCAS(&pv.hdr->err, 0, SMETRIC_EINVAL);
+  }
+  for (int64_t b = t; b - lane < n_blocks; b += span) {  // whole wavefronts iterate together
+    const bool in = b < n_blocks;
+    const uint64_t d = in ? describe(ix, keys[b]) : 0;
+    if (in) pv.desc_p[b] = d;
+    const bool first = in && (b == 0 || pv.part_req[b] != pv.part_req[b - 1]);
+    const uint64_t none = __ballot(in && desc_kind(d) == D_NONE), firsts = __ballot(first);
+    if (lane == 0) {
+      reinterpret_cast<uint64_t *>(pv.skip)[b / 64] = none;
+      reinterpret_cast<uint64_t *>(pv.inv)[b / 64] = firsts;
     }
   }
-  for (int64_t j = j0 + t; j < nb; j += nt) pv.desc_p[b0 + j] = make_desc(D_NONE, 0, 0);
-  if (t == 0) {  // blocks before the bound were probed; those read from it on found it
-    const uint32_t searched = uint32_t((j0 < nb ? j0 : nb) - hi), skipped = uint32_t(nb - hi);
-    if (rec) {
-      if (r == 0) pv.hdr->n_rec = uint64_t(n_req);
-      pv.base[r] = (uint64_t(skipped) << 32) | searched;
-    } else if (skipped) {
-      atomicAdd(&pv.hdr->n_skip, (unsigned long long)skipped);
-      atomicAdd(&pv.hdr->n_search, (unsigned long long)searched);
-    }
-  }
-}
-
-// Threads per request of the direct kernels: about one group per request.
-int direct_threads(int64_t n_blocks, int32_t n_req, int most) {
-  const int64_t mean = n_req > 0 ? n_blocks / n_req : 0;
-  int nt = 64;
-  while (nt < most && nt < mean) nt <<= 1;
-  return nt;
 }
 
 }  // namespace
@@ -685,7 +668,7 @@ extern "C" int smetric_probe_partition(const smetric_index *idx, const uint64_t 
   if (direct_batch(uint64_t(n_blocks))) {
     if (direct_needs_clear(n_req)) partition_head(pv, false, stream);
     if (n_req > 0)
-      hipLaunchKernelGGL(direct_partition_kernel, dim3(n_req), dim3(direct_threads(n_blocks, n_req, TB)), 0, stream, pv,
+      hipLaunchKernelGGL(direct_partition_kernel, dim3(n_req), dim3(direct_threads(n_blocks, n_req)), 0, stream, pv,
                          keys, blk_off, n_req, n_blocks);
     return hip_rc(hipGetLastError());
   }
@@ -705,13 +688,12 @@ extern "C" int smetric_probe_lookup(const smetric_index *idx, void *probe, uint6
   probe_layout(n_blocks, &pv, probe);
   const DevIndex ix = dev_view(idx);
   if (direct_batch(uint64_t(n_blocks))) {
-    // more requests than records: the header's counts are cleared first
-    if (n_req > DIRECT_REQ)
-      hipLaunchKernelGGL(zero2_kernel, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint64_t *>(&pv.hdr->n_skip),
-                         uint64_t(2), nullptr, uint64_t(0));
+    // wavefronts alone while the chip has room for them
+    const int nt = n_blocks <= (int64_t(1) << 16) ? 64 : TB;
+    const int64_t items = n_blocks > n_req ? n_blocks : n_req, grid = (items + nt - 1) / nt;
     if (n_req > 0)
-      hipLaunchKernelGGL(direct_lookup_kernel, dim3(n_req), dim3(direct_threads(n_blocks, n_req, 512)), 0, stream, ix, pv,
-                         keys, blk_off, n_req, n_blocks);
+      hipLaunchKernelGGL(direct_lookup_kernel, dim3(grid < 4096 ? grid : 4096), dim3(nt), 0, stream, ix, pv, keys,
+                         blk_off, n_req, n_blocks);
     return hip_rc(hipGetLastError());
   }
   const uint64_t nw = skip_words(uint64_t(n_blocks < 1 ? 1 : n_blocks));
@@ -738,21 +720,24 @@ extern "C" int smetric_probe_stats(const void *probe, uint64_t probe_bytes, int6
   if (hipMemcpyAsync(&h, pv.hdr, sizeof(h), hipMemcpyDeviceToHost, stream) != hipSuccess ||
       hipStreamSynchronize(stream) != hipSuccess)
     return SMETRIC_EHIP;
-  if (direct_batch(uint64_t(n_blocks)) && h.n_rec > 0 && h.n_rec <= uint64_t(DIRECT_REQ)) {
-    uint64_t rec[2048];
-    for (uint64_t r = 0; r < h.n_rec; r += 2048) {
-      const uint64_t m = h.n_rec - r < 2048 ? h.n_rec - r : 2048;
-      if (hipMemcpyAsync(rec, pv.base + r, 8 * m, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-          hipStreamSynchronize(stream) != hipSuccess)
-        return SMETRIC_EHIP;
-      for (uint64_t i = 0; i < m; ++i) {
-        h.n_skip += rec[i] >> 32;
-        h.n_search += uint32_t(rec[i]);
-      }
-    }
-  }
   if (direct_batch(uint64_t(n_blocks))) {
     if (h.err) h.n = 0;
+    h.n_skip = h.n_search = 0;
+    if (h.bounded && h.n > 0 && h.n <= DIRECT_MAX) {  // blocks from their request's first of no holder on
+      uint64_t none[DIRECT_MAX / 64], firsts[DIRECT_MAX / 64];
+      const uint64_t nw = (h.n + 63) / 64;
+      if (hipMemcpyAsync(none, pv.skip, 8 * nw, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+          hipMemcpyAsync(firsts, pv.inv, 8 * nw, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+          hipStreamSynchronize(stream) != hipSuccess)
+        return SMETRIC_EHIP;
+      bool past = false;
+      for (uint64_t b = 0; b < h.n; ++b) {
+        if ((firsts[b / 64] >> (b % 64)) & 1) past = false;
+        past |= (none[b / 64] >> (b % 64)) & 1;
+        h.n_skip += past;
+      }
+      h.n_search = h.n_skip;
+    }
   }
   *n_probed = h.n >= h.n_skip ? h.n - h.n_skip : 0;
   *n_search = h.n_search;
