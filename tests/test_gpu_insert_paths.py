@@ -187,3 +187,46 @@ def test_few_long_requests(R, nb):
     few, many = lookup_us(d_boff), lookup_us(to_dev(np.arange(1025, dtype=np.int64) * (nb // 1024)))
     say(f"  lookup: {few:.0f} us, as 1,024 requests {many:.0f} us")
     assert few < 5 * many
+
+
+@pytest.mark.parametrize("probed", [False, True])
+@pytest.mark.parametrize("R,shared,own,n_inst", [(16384, 16, 0, 1), (4000, 60, 5, 3), (2000, 128, 0, 40)])
+def test_pairs_entered_by_many_requests(R, shared, own, n_inst, probed):
+    """A new prefix that thousands of requests enter on one or a few instances, with and without
+    blocks of their own: each pair takes the lowest request's session.  Pairs met that often
+    cost no more than as many distinct ones (one atomic each on the same words: 3 times)."""
+    rng = np.random.default_rng(R + n_inst)
+    nb = R * (shared + own)
+    keys = rng.integers(1, 2**63, (R, shared + own), dtype=np.int64).astype(np.uint64)
+    keys[:, :shared] = keys[0, :shared]
+    keys = keys.reshape(-1)
+    blk_off = np.arange(R + 1, dtype=np.int64) * (shared + own)
+    pair = Pair(nb + 1000, 40)
+    inst, sess = rng.integers(0, n_inst, R).astype(np.int32), rng.permutation(R).astype(np.uint32)
+    d_keys, d_off, d_inst, d_sess = to_dev(keys), to_dev(blk_off), to_dev(inst), to_dev(sess)
+    assert insert_both(pair, probed, d_keys, d_off, nb, keys, blk_off, inst, sess, 3) == 0
+    pair.compare_index(f"R={R} shared={shared} own={own} instances={n_inst} probed={probed}")
+    if own or n_inst > 1:
+        return
+    empty = pair.S.Index(nb + 1000, 40)
+    snap = empty.snapshot()
+
+    def insert_us(k):
+        t = []
+        for _ in range(9):
+            empty.restore(snap)
+            state = empty.probe(k, d_off, nb) if probed else None
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            if probed:
+                empty.insert_probed(state, R, nb, d_inst, d_sess, 1)
+            else:
+                empty.insert(k, d_off, nb, d_inst, d_sess, 1)
+            e[1].record()
+            torch.cuda.synchronize()
+            t.append(e[0].elapsed_time(e[1]) * 1e3)
+        return sorted(t)[4]
+
+    same, distinct = insert_us(d_keys), insert_us(to_dev(rng.integers(1, 2**63, nb, dtype=np.int64).astype(np.uint64)))
+    say(f"  insert probed={probed}: {same:.0f} us, distinct pairs {distinct:.0f} us")
+    assert same < 1.5 * distinct
