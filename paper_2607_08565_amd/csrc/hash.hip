@@ -15,7 +15,8 @@
 //    permutes) yields the block digest.
 //  * B = 32, 64, 128, 256: the same kernel, a block read as B / 16 sub-blocks of 16 whose
 //    digests (sums of products) add up to the block's.
-//  * other even B: one wavefront per request; lane l digests block l of the tile.
+//  * other even B, and short prompts of those four: one wavefront per request; lane l
+//    digests block l of the tile.
 //  Digests go through LDS so that lane l then owns block l of the tile; the chain is an
 //  inclusive scan of affine maps x -> M x + e_l across the wavefront, done with DPP moves
 //  (row shifts, then the row broadcasts) and per-lane powers of M.  A tile's carry-in composes the affine maps of
@@ -330,8 +331,9 @@ __global__ __launch_bounds__(64 * NW) void hash16_kernel(const int32_t *__restri
   }
 }
 
-// Any even B in [2, 256] (used for those that are not 16 times a power of two).  DIRECT: as hash16_kernel's H_DIRECT, but a request's token range
-// does not make the probe state invalid (its keys are then the caller's earlier ones).
+// Any even B in [2, 256] (used for those that are not 16 times a power of two, and for short
+// prompts).  DIRECT: as hash16_kernel's H_DIRECT, but a request's token range does not make the
+// probe state invalid (its keys are then the caller's earlier ones).
 template <bool DIRECT>
 __global__ __launch_bounds__(64 * WAVES) void hash_generic_kernel(
     const int32_t *__restrict__ tokens, int64_t n_tokens, const int64_t *__restrict__ tok_off,
@@ -408,7 +410,16 @@ void launch_hash(const int32_t *tokens, int64_t n_tokens, const int64_t *tok_off
                  int64_t n_blocks, int32_t block_size, uint64_t seed, uint64_t *keys, int32_t *status,
                  const ProbeView &pv, hipStream_t stream) {
   constexpr int MODE = DIRECT ? H_DIRECT : H_KEYS;
-  auto *tiles = block_size == 16    ? launch_hash_tiles<MODE, 1>
+  // A tile of 64 longer blocks is worth its G rounds, and two wavefronts' constants, only
+  // where it is half full; few requests wait for the rounds alone, up to a full one.  Both
+  // kernels (one wavefront / tiled) by blocks per prompt, us, blocks of 32: 16,384 prompts of 1
+  // block 14 / 25, of 32 19 / 26, of 64 36 / 26; blocks of 64: 4,096 of 1 7 / 12, of 32 11 / 12,
+  // of 64 30 / 14; of 256: 16,384 of 1 36 / 94, 4,096 of 32 32 / 33, 64 of 64 8 / 11, 1,024 of 64
+  // 16 / 13.
+  const int64_t mean = n_blocks / n_req;
+  const bool tiled = block_size == 16 || mean > (n_req < 256 ? 64 : 32);
+  auto *tiles = !tiled              ? nullptr
+                : block_size == 16  ? launch_hash_tiles<MODE, 1>
                 : block_size == 32  ? launch_hash_tiles<MODE, 2>
                 : block_size == 64  ? launch_hash_tiles<MODE, 4>
                 : block_size == 128 ? launch_hash_tiles<MODE, 8>
