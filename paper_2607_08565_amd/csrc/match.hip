@@ -246,7 +246,9 @@ __device__ __forceinline__ Holders decode(const DevIndex &ix, uint64_t d, uint64
 // positions; S_DIRECT: those of the direct form, in block order.
 enum MatchSrc { S_WALK = 0, S_REGION = 1, S_DIRECT = 2 };
 // S_WALK with NW > 1: the request's chains are walked by NW wavefronts, 64 NW blocks at a
-// time, whose holder sets wavefront 0 reduces from LDS; they stop when it is done.
+// time, whose holder sets wavefront 0 reduces from LDS; they stop when it is done.  In the
+// first round each of the others first looks for the block before its stretch, and where
+// no instance holds it leaves the stretch's sets empty -- no hit gets past such a block.
 template <int WPL, int SRC, int NW>
 __global__ __launch_bounds__(64 * NW) void match_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
                                                         const int64_t *__restrict__ blk_off,
@@ -277,7 +279,8 @@ __global__ __launch_bounds__(64 * NW) void match_kernel(DevIndex ix, const uint6
     if (threadIdx.x == 64) done = 0;
     for (int64_t base = 64 * wave;; base += 64 * NW) {
       const int64_t j = base + lane;
-      if (j < nb) held[64 * wave + lane] = pack_holders(probe(ix, keys[b0 + j]));
+      const bool wanted = base != 64 * wave || base >= nb || probe(ix, keys[b0 + base - 1]).kind != H_NONE;
+      if (j < nb) held[64 * wave + lane] = wanted ? pack_holders(probe(ix, keys[b0 + j])) : PackedHolders{};
       __syncthreads();  // the round's sets are there
       __syncthreads();  // wavefront 0 has read them
       if (done) return;
@@ -383,7 +386,10 @@ __global__ __launch_bounds__(64 * NW) void match_kernel(DevIndex ix, const uint6
 #pragma unroll
           for (int t = 0; t < WPL; ++t) A[t] = holder_word(ix, kind0, rec0, hl0, key0, lane + 64 * t);
         }
-        mode = M_WIDE;
+        bool some = false;
+#pragma unroll
+        for (int t = 0; t < WPL; ++t) some |= A[t] != 0;
+        mode = __ballot(some) ? M_WIDE : M_DONE;  // a bitmap that an eviction emptied holds nobody
       }
       jj = 1;
     }
@@ -640,10 +646,14 @@ extern "C" int smetric_match(const smetric_index *idx, const uint64_t *keys, con
   if (n_req == 0) return SMETRIC_OK;
   if (!blk_off || !matched || (n_blocks > 0 && !keys) || !idx->slots) return SMETRIC_EINVAL;
   // A walk's time is one round trip to the table after another, so a request's chunks of 64
-  // blocks are walked at once by as many wavefronts as it has of them -- up to 8, and while the
-  // chip has wavefronts to spare (8,192 of one per request, measured).  Before
-  // and now: 1 request of 606 blocks 22 -> 12 us, 8 of 1,938 107 -> 56, 512 of 601 98 -> 75, 2,048 of
-  // 1,813 342 -> 264 (by 8 wavefronts 330), 8,192 of 1,823 496 -> 479 (by 4: 625).
+  // blocks are walked at once by as many wavefronts as it has of them -- up to 8, and up to 8,192
+  // in all.  By one wavefront and so, prompts of lognormal length held to 70 %: 1 request of 606
+  // blocks 22 -> 12 us; 512 of 600 on average, 64 -> 39 in a small table and 93 -> 46 in one of 50M
+  // entries; 2,048 of 1,800 210 -> 163 and 337 -> 225; 4,096 of 600 92 -> 86 and 152 -> 125.  4,096
+  // wavefronts, as many as are resident, would be better where all prompts are equally long (1,024 of
+  // 2,000 small 77 -> 62 instead of 86; big 230 -> 132, 178) and worse where they are not (2,048 of
+  // 1,800 171, 259).  Prompts that nobody holds: 1,024 of 2,000 6 -> 8 and 11 -> 15 us (15 and
+  // 34 without the look at the block before).
   const int64_t mean = n_blocks / n_req;
   int nw = 1;
   while (nw < 8 && 64 * nw < mean && int64_t(2 * nw) * n_req <= 8192) nw *= 2;

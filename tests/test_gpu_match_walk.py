@@ -1,7 +1,8 @@
 """The self-contained match against the oracle at each number of wavefronts per request (1, 2, 4
 and 8) and at the edges of their rounds: prompts of 0, 1 and a round's blocks and one less
 or more, shared prefixes held by few instances (lists), by more than a list keeps and by most
-(bitmaps), prompts that miss early, late and not at all."""
+(bitmaps), prompts that miss early, late and not at all, and prompts whose blocks around the
+edges of the wavefronts' stretches are the only ones that nobody holds."""
 import numpy as np
 import pytest
 
@@ -46,3 +47,57 @@ def test_match_rounds(R, lens, I):
     g, o = pair.gix.match(d_keys, d_boff, nb).cpu().numpy(), pair.oix.match(okeys, blk_off)
     assert np.array_equal(g, o), np.argwhere(g != o)[:4]
     say(f"  R={R} I={I} blocks={nb}: hits {int((o > 0).sum())}")
+
+
+@pytest.mark.parametrize("R,nb", [(1, 700), (40, 300), (3000, 130)])
+def test_gaps_at_the_edges_of_stretches(R, nb):
+    """Block j of a prompt is held by nobody, those before and after it by one, a few or most
+    instances (a bitmap): hits end at j, whatever lies behind it."""
+    rng = np.random.default_rng(R)
+    for I, holders in ((6, 1), (6, 4), (300, 200)):
+        gaps = [g for g in (0, 1, 62, 63, 64, 126, 127, 128, 191, 255, 447, 511, 512, nb - 1) if g < nb]
+        n = R * nb
+        pair = Pair(min(R, 40) * nb * (holders + 4) + 2 * n, I, block=2)
+        toks = rng.integers(0, W.VOCAB, 2 * n, dtype=np.int32)
+        off = np.arange(R + 1, dtype=np.int64) * 2 * nb
+        d_boff, n, d_keys, okeys, blk_off = pair.hash_both(toks, off)
+        for g0 in range(0, len(gaps), max(1, R)):  # every gap, some of them once per request
+            at = np.array([gaps[(g0 + r) % len(gaps)] for r in range(R)])
+            pair = Pair(min(R, 40) * nb * (holders + 4) + 2 * n, I, block=2)
+            keep = np.ones(n, bool)
+            keep[blk_off[:-1] + at] = False
+            for r0 in range(0, R, 40):  # many holders for the first 40 prompts, one for the rest
+                rows = np.arange(r0, min(R, r0 + 40))
+                k = np.concatenate([okeys[blk_off[r]:blk_off[r + 1]][keep[blk_off[r]:blk_off[r + 1]]] for r in rows])
+                ko = np.arange(len(rows) + 1, dtype=np.int64) * (nb - 1)
+                for i in rng.permutation(I)[:holders if r0 == 0 else 1]:
+                    assert pair.insert_both(to_dev(k), to_dev(ko), len(k), k, ko, np.full(len(rows), i), rows, 1) == 0
+            gm, om = pair.gix.match(d_keys, d_boff, n).cpu().numpy(), pair.oix.match(okeys, blk_off)
+            assert np.array_equal(gm, om), np.argwhere(gm != om)[:4]
+            assert np.array_equal(om.max(1), at)
+
+
+@pytest.mark.parametrize("I", [100, 5000])
+@pytest.mark.parametrize("R,nb", [(1, 600), (5, 130), (1, 64), (3000, 66)])
+def test_prompts_whose_first_blocks_were_evicted(R, nb, I):
+    """Prompts of which most instances held every block but the last of a wavefront's stretch,
+    after an eviction of everybody's first block: its key's bitmap is there and empty."""
+    rng = np.random.default_rng(R + I)
+    pair = Pair(60 * nb + 5000, I)
+    keys = np.sort(rng.integers(1 << 40, 2**63, nb, dtype=np.int64).astype(np.uint64))  # the lowest key goes first
+    held = np.delete(keys, 63)
+    ko = np.array([0, len(held)], np.int64)
+    who = rng.permutation(I)[:50]
+    for i in who:
+        assert pair.insert_both(to_dev(held), to_dev(ko), len(held), held, ko, [i], [7], 1) == 0
+    blk_off = np.arange(R + 1, dtype=np.int64) * nb
+    okeys = np.tile(keys, R)
+    d_keys, d_off = to_dev(okeys), to_dev(blk_off)
+    for num in (0, 20, 30):  # entries to evict: none, some of the first block's, the rest of them
+        n, _ = pair.gix.stats()
+        pair.gix.evict(num, n)
+        assert pair.oix.evict(num, n) == 0
+        gm, om = pair.gix.match(d_keys, d_off, R * nb).cpu().numpy(), pair.oix.match(okeys, blk_off)
+        assert np.array_equal(gm, om), np.argwhere(gm != om)[:4]
+    pair.compare_index("evicted")
+    assert not om.any()
