@@ -33,7 +33,7 @@
 //              slot, and the thread whose slot becomes the key's (T+1)-th plain slot --
 //              unique, since claims fill a chain in order -- queues the key for conversion
 //   spill      queued keys get a bitmap record, member slots, a header and tombstones
-// Batches of at most SI_MAX blocks take one launch (ins_small_kernel); a probed batch past
+// Batches of at most SI_LINE or SI_MAX blocks take one launch (ins_small_kernel); a probed batch past
 // the direct form's size takes the region-ordered passes.
 #include <rocprim/device/device_radix_sort.hpp>
 
@@ -1506,20 +1506,34 @@ __global__ __launch_bounds__(TB) void insp_place_kernel(DevIndex ix, ProbeView p
 // ---------------------------------------------------------------------------------
 // Insert of a small batch: one launch, one workgroup
 // ---------------------------------------------------------------------------------
-// A batch of at most SI_MAX blocks is bound by launches and by one round trip to memory
-// after another, not by bandwidth: the stages of the general insert (8 launches, 13 from a
-// probe state) each find a few thousand pairs at most.  Here one workgroup takes them
-// all, SI_U pairs per thread, with barriers between the stages: find every pair (from the
-// descriptor where the batch was probed), dedupe the absent ones in an LDS table of pair
-// numbers, check, then refresh and place.  Pairs are numbered in request order (plain) or
+// A batch of a few thousand blocks is bound by launches and by one round trip to memory
+// after another, not by bandwidth: the stages of the general insert (five launches)
+// each find a few thousand pairs at most.  Here one workgroup takes them all, SI_U pairs
+// per thread, with barriers between the stages: find every pair (from the descriptor where
+// the batch was probed), dedupe the absent ones in an LDS table of pair numbers, check, then
+// refresh and place.  Pairs are numbered in request order (plain) or
 // carry their request (probed), so a repeated pair keeps its lowest request.  A thread
 // converts the keys whose (T+1)-th plain slot it claimed and enters the pairs it had to
 // defer, after a barrier each.
-// One agent's requests (64 to 350 blocks each): 26 us of kernels in 8 launches -> 9.3 us in
-// one.  At 4,096 new pairs it takes 29 us, what the five launches of the next size up take.
+// One agent's requests (64 to 350 blocks each): 26 us of kernels in the eight launches that the
+// self-contained insert took before, 9.3 in one.
 constexpr int SI_T = 1024;
 constexpr int SI_U = 4;
 constexpr int SI_MAX = SI_T * SI_U;
+// One launch against five (kernels alone), new pairs, in a small table and in one of 100M
+// entries.  Self-contained, 64 requests of 2,048 blocks in all 26 / 31 and 52 / 45 us, of 3,072
+// 35 / 28 and 70 / 46, of 4,096 48 / 35 and 95 / 56 (existing pairs 27 / 17 and 50 / 25): the line is
+// at half of SI_MAX.  But its find pass takes a request by a workgroup, this kernel any pair
+// by any thread: 4 requests of 3,072 blocks in all 36 / 46 and 69 / 84, of 4,096 47 / 64 and
+// 91 / 112, one of 4,096 48 / 173, 16 of 4,096 48 / 33: few long requests go on to SI_MAX.  Probed
+// 2,048 22 / 31 and 39 / 43, 4,096 41 / 32 and 67 / 45, and the four launches saved are 11 us of the
+// host's: a replay of 64 sessions, bound by the host, 181 us with this kernel up to SI_MAX and
+// 194 with half of that.
+constexpr int SI_LINE = SI_MAX / 2;
+constexpr int SI_LONG = 512;  // blocks per request
+inline bool ins_small(int64_t n_blocks, int32_t n_req) {
+  return n_req <= SI_T && n_blocks <= (n_blocks / n_req >= SI_LONG ? SI_MAX : SI_LINE);
+}
 constexpr int SI_TAB = 2 * SI_MAX;  // never more than half full
 constexpr uint32_t SI_FREE = 0xFFFFFFFFu;
 
@@ -2608,7 +2622,7 @@ extern "C" int smetric_index_insert(smetric_index *idx, const uint64_t *keys, co
   InsWs ws;
   insert_ws_layout(n_blocks, &ws, workspace);
   const DevIndex ix = dev_view(idx);
-  if (n_blocks <= SI_MAX && n_req <= SI_T) {
+  if (ins_small(n_blocks, n_req)) {
     hipLaunchKernelGGL(ins_small_kernel<false>, dim3(1), dim3(SI_T), 0, stream, ix, ProbeView{}, keys, blk_off, n_req,
                        n_blocks, instance, session, epoch);
     return hip_rc(hipGetLastError());

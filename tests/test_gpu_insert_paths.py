@@ -73,7 +73,8 @@ def _sized(rng, R, nb, shared, block=16):
 
 @pytest.mark.parametrize("probed", [False, True])
 @pytest.mark.parametrize("R,nb", [(1, 0), (1, 1), (1, 1023), (3, 1024), (64, 1025), (1023, 4095), (1024, 4096),
-                                  (1025, 4096), (40, 4097), (1, 4096)])
+                                  (1025, 4096), (40, 4097), (1, 4096), (70, 2047), (70, 2048), (70, 2049), (1024, 2048),
+                                  (1025, 2048), (4, 2049), (5, 2559), (5, 2560), (8, 4095), (8, 4096), (1, 4097)])
 def test_insert_around_the_small_batch_limits(R, nb, probed):
     """Batches of exactly R requests and nb blocks on few and on many instances (keys turning
     into bitmap records while pairs of theirs wait), entered three times on new targets with
