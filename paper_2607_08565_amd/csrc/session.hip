@@ -14,9 +14,9 @@
 //           slots of (user_r, turn_r, n, key_r[n-1]) give the earlier requests whose whole
 //           sequence is r's first n keys -- with chained keys (key j determines blocks 0..j)
 //           one key comparison is the whole prefix test; the largest p < r wins;
-//           Most lengths have no offer: up to FILT_MAX_REQ requests a bitmap of the offers in
-//           LDS turns them away (one random 16-byte read per key made the join bound by the
-//           L2's lines);
+//           Most lengths have no offer: up to FILT_MAX_REQ requests of FILT_MEAN blocks or
+//           more a bitmap of the offers in LDS turns them away (one random 16-byte read per
+//           key made the join bound by the L2's lines);
 //   roots   one launch: every request follows the jumps, shortening its own for the others
 //           as it goes, to its chain's first request.
 #include "common.h"
@@ -52,6 +52,11 @@ __device__ __forceinline__ bool range_ok(const int64_t *blk_off, int32_t r, int6
 // a few 32-bit operations spread them.  One length in six passes at FILT_MAX_REQ requests,
 // one in sixty at 32,768.
 constexpr int32_t FILT_MAX_REQ = 1 << 17;
+// Shorter prompts give a wavefront one lookup per lane, and with the bitmap fewer of them
+// wait for theirs at once.  The query without / with it: 131,072 requests of 16 blocks 101 /
+// 123 us, of 63 145 / 166, of 100 239 / 221; 34,000 of 16 18 / 25, of 63 25 / 30, of 100 35 / 36, of
+// 200 59 / 41; 100,000 of none in one chain 50 / 90.
+constexpr int64_t FILT_MEAN = 64;
 constexpr uint32_t FILT_MAX_WORDS = 1u << 14;  // 64 KB of LDS, two workgroups to a compute unit
 __device__ __forceinline__ uint32_t filt_base(uint32_t user, uint32_t turn) {
   return user * 0x9E3779B1u + turn * 0x85EBCA6Bu;
@@ -252,7 +257,7 @@ extern "C" int smetric_sessions(const uint64_t *keys, const int64_t *blk_off, in
     const uintptr_t a = reinterpret_cast<uintptr_t>(p);
     return !bytes || a >= s1 || a + bytes <= s0;
   };
-  if (n_req <= FILT_MAX_REQ && apart(keys, 8 * uint64_t(n_blocks)) && apart(blk_off, 2 * n4 + 8) && apart(user, n4) &&
+  if (n_req <= FILT_MAX_REQ && n_blocks / n_req >= FILT_MEAN && apart(keys, 8 * uint64_t(n_blocks)) && apart(blk_off, 2 * n4 + 8) && apart(user, n4) &&
       apart(turn, n4) && apart(parent, n4))
     for (words = 1; 2 * words <= uint32_t(n_req) && words < FILT_MAX_WORDS;) words *= 2;
   hipLaunchKernelGGL(offer_clear_kernel, dim3(int((ns + TB - 1) / TB < 4096 ? (ns + TB - 1) / TB : 4096)), dim3(TB), 0,
