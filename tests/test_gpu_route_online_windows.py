@@ -1,7 +1,8 @@
 """The online route against the oracle at the sizes where its kernel changes form: instance
 counts around each form's slots, batches around windows of 64 requests and the 64 windows
 looked ahead at, with runs of follow-ups of every length between requests that need a
-scan, prevs shared within a run, out-of-domain requests, and loads on both sides of 2^50."""
+scan, prevs shared within a run, out-of-domain requests, and loads on both sides of 2^50, and
+each form with every load past it."""
 import numpy as np
 import pytest
 
@@ -58,3 +59,15 @@ def test_windows_of_runs_and_scans(I):
             assert len(bad) == 0, (I, R, scan_pct, over, bad[:4], gt[bad[:4]], ot[bad[:4]], gb[bad[:4]], ob[bad[:4]])
             assert np.array_equal(gq, oq), (I, R, over)
         say(f"  I={I} R={R} scans {scan_pct}% prevs {prevs}: branches {np.bincount(ob, minlength=5)[:5].tolist()}")
+
+
+@pytest.mark.parametrize("I", [7, 64, 100, 200, 500, 512, 1000, 2000, 2048, 4000])
+def test_every_load_wide(I):
+    """Scans in 128 bits at each form's slots, the last ones past the last instance."""
+    from paper_2607_08565_amd import smetric as S
+    rng = np.random.default_rng(I)
+    m, L, hist, turn, _ = _batch(rng, 300, I, 60, I, False)
+    q = (1 << 51) + rng.integers(0, 4, I) * W.Q_UNIT_NS
+    got = S.route_seq(*[to_dev(x) for x in (m, L, hist, turn, q)], W.DEFAULT_PARAMS, 5)
+    for g, o in zip(got, oracle.route_seq(m, L, hist, turn, q, W.DEFAULT_PARAMS, 5)):
+        assert np.array_equal(g.cpu().numpy(), o)
