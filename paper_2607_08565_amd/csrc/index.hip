@@ -123,7 +123,7 @@ bool layout_for(uint64_t capacity, int32_t n_inst, uint64_t n_slots, Layout &L) 
   }
   L.slots_off = sizeof(IndexHdr);
   L.pool_off = L.slots_off + L.n_buckets * BUCKET_WORDS * 8;
-  // then the displacement masks, one byte per bucket (dev_view finds them after the pool)
+  // then the displacement masks, MASK_W bits per bucket (dev_view finds them after the pool)
   L.bytes = round_up(L.pool_off + L.n_records * uint64_t(L.words) * 8 + mask_bytes(L.n_buckets), 256);
   return true;
 }
@@ -387,13 +387,11 @@ __device__ bool spill_key(const DevIndex &ix, uint64_t key) {
 // Insert
 // ---------------------------------------------------------------------------------
 struct WsHdr {
-  unsigned long long n_new;    // distinct new pairs listed
   unsigned long long n_pairs;  // pairs over all request ranges
   unsigned long long n_trig;   // keys queued for conversion
   int err;                     // first input error seen by the probe
   int abort;                   // set by the check: leave the index unchanged
   unsigned long long n_cand;   // pairs absent before the batch (region-ordered insert)
-  unsigned long long n_dd;     // dedupe slots in use (a power of two)
   unsigned long long n_def;    // new pairs deferred until their key's conversion
   unsigned long long nsub;     // region-ordered insert: bins per region (a power of two)
   unsigned long long n_dd2;    // region-ordered insert: fallback pair-table slots in use
@@ -401,7 +399,7 @@ struct WsHdr {
   int inl;                     // region-ordered insert: refreshes done by the classify pass
   int pad1;
   unsigned long long turns;    // find pass: new pairs, workgroups that have ended, errors (ins_check_last)
-  unsigned long long pad[20];
+  unsigned long long pad[22];
 };
 static_assert(sizeof(WsHdr) == 256, "ws header size");
 
@@ -450,7 +448,7 @@ constexpr int NSUB_MAX = 1024;              // bins per region, at most
 constexpr int NBIN_MAX = NREG * NSUB_MAX;
 constexpr int BIN_TARGET = 1536;            // nsub keeps the mean bin at or below this
 constexpr int DT = 4096;                    // slots of a bin's LDS pair table
-constexpr int BIN_CAP = 3072;               // larger bins use the fallback pair table
+constexpr int BIN_CAP = 3072;               // larger bins stream through the LDS pair table
 static_assert(INS_WG % KCH == 0 && SEG_PER_CH <= 64, "chunk = whole classify segments");
 static_assert(BIN_CAP + WG_THREADS < DT, "an LDS pair table never fills");
 
@@ -662,8 +660,10 @@ __device__ __forceinline__ void memory_done() {
 // its own: every workgroup adds, in one atomic, its turn, whether it met an error, and its
 // new pairs, and the one whose turn is the last has the totals in the returned word.  The
 // words that pass between workgroups are all accessed by atomics, and a workgroup's are
-// complete before its turn, so no cache is written back.  n_entries: as read when the kernel
-// began (nothing else changes it meanwhile).
+// complete before its turn, so no cache is written back.  This rests on the hardware (an
+// atomic of device scope acts in one place for all dies, and one that has been waited for has
+// acted), not on the memory model, whose release and acquire here cost 5 us of cache
+// write-back.  n_entries: as read when the kernel began (nothing else changes it meanwhile).
 constexpr int TURN_SHIFT = 40, ERR_SHIFT = 52;  // 2^40 new pairs, 2^12 workgroups
 static_assert(2 * FIND_WG < (1 << 12) && DEDUPE_WG < (1 << 12), "turns and errors fit their fields");
 template <bool PAIRS>
@@ -879,7 +879,8 @@ __global__ void spill_kernel(DevIndex ix, const uint64_t *trig, const unsigned l
 //              scan, scatter, as the probe's region partition), so all candidates of a
 //              pair share a bin
 //   dedupe     one workgroup per bin: an LDS pair table keeps each (key, instance) once
-//              with its lowest request; bins above BIN_CAP use the global pair table
+//              with its lowest request; bins above BIN_CAP stream through it, and one whose
+//              distinct pairs would fill it uses the global pair table
 //              The last workgroup checks all-or-nothing: EINVAL or EFULL leave the index
 //              unchanged
 //   refresh    epoch = max(old, epoch) at the classified positions (if not done above)
@@ -1227,8 +1228,9 @@ __global__ __launch_bounds__(SCAN_T) void insp_bscan_kernel(InsWs ws) {
 
 // Scatter pass: workgroup (g, c) moves its chunk into bin order one tile at a time (LDS
 // ranks per bin, the tile regrouped by bin in LDS, each bin's part written as one run
-// after the previous tile's).  The workgroups also size and clear the fallback pair table of
-// the oversized bins (a power of two >= 2 x their candidates) for the pass after this one.
+// after the previous tile's).  The workgroups also size and clear the fallback pair table for
+// the pass after this one: a power of two >= 2 x the candidates of all bins above BIN_CAP,
+// though most of those never need it (what they need shows only there).
 constexpr int U2 = 8;
 constexpr int TILE2 = U2 * TB;
 static_assert(NSUB_MAX % TB == 0, "bins per thread in the scans");

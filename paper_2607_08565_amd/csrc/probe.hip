@@ -33,11 +33,6 @@ namespace {
 
 constexpr int TB = WG_THREADS;
 
-__global__ void zero_kernel(uint64_t *p, uint64_t n_words) {
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n_words; i += stride) p[i] = 0;
-}
-
 // two ranges cleared by one launch
 __global__ void zero2_kernel(uint64_t *p, uint64_t n_words, uint64_t *p2, uint64_t n_words2) {
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
