@@ -3,7 +3,7 @@ dumped entry set: one or few epochs of 65,535 to 100,001 entries, so that the en
 the digits lie at, below and above the 2^16 that one workgroup settles; tables below and above
 the 2^15 buckets from which a sample narrows the entries copied out; a table whose sampled
 buckets hold one epoch and the others another, so that the sample's range misses the cut; an
-empty table, which is not read; keys
+empty table, which is not read; a rebuild of keys held by few and by most instances; keys
 on several instances (the last digits decide); evicted in place (small fractions of a roomy
 table) and by a rebuild (large ones); bucket counts that are no multiple of a tile."""
 import numpy as np
@@ -95,3 +95,19 @@ def test_empty_index(slots):
         _fill(pair, rng, 5000, 7, 64, 10)
         pair.gix.evict(1, 1)
         assert pair.oix.evict(1, 1) == 0
+
+
+@pytest.mark.parametrize("n_keys,holders", [(700, 200), (3000, 40), (40, 3)])
+def test_rebuild_of_widely_held_keys(n_keys, holders):
+    """Members are entered again by the passes after the tiles', in several workgroups' lists."""
+    rng = np.random.default_rng(n_keys)
+    pair = Pair(n_keys * holders + 4000, 256)
+    keys = rng.integers(1, 2**63, n_keys, dtype=np.int64).astype(np.uint64)
+    off = np.array([0, n_keys], np.int64)
+    for k, i in enumerate(rng.permutation(256)[:holders]):
+        assert pair.insert_both(to_dev(keys), to_dev(off), n_keys, keys, off, [i], [k], 1 + k % 5) == 0
+    _fill(pair, rng, 2000, 3, 256, 20)
+    for num, den in ((1, 3), (1, 2)):
+        pair.gix.evict(num, den)
+        assert pair.oix.evict(num, den) == 0
+        pair.compare_index(f"{n_keys} keys on {holders}: evict {num}/{den}")
