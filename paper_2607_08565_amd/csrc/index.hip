@@ -2253,8 +2253,12 @@ __global__ __launch_bounds__(FIN_T) void sel_finish_kernel(DevIndex ix, const ui
 // Rebuild, second pass: the entries the tile pass left, one per thread (all survivors).
 // Claims that trigger a key's conversion or are deferred are queued by their place in the
 // list for the spill and deferred passes; nearly all members are deferred, so a workgroup
-// queues its own with one atomic (a third of 76M entries, 16M of them members: this pass
-// 4.2 ms; 5.7 with an atomic per wavefront).
+// queues its own with one atomic.  The list is in the order of the tiles, more or less, so few
+// workgroups keep the part of the table that is walked at one time small: a third of 76M
+// entries, 16M of them members, 5.7 ms with 4,096 workgroups (and an atomic per wavefront), 1.8
+// with 512, 1.6 with 384, 2.0 with 256; of 155M, 5M of them members, 2.2, 1.4, 0.9 and 1.1.  (From
+// lists per tile, a workgroup each, 4.8 and 1.9.)
+constexpr int CLAIM_WG = 384;
 __global__ __launch_bounds__(TB) void rebuild_claim_kernel(DevIndex ix, const uint64_t *__restrict__ keys,
                                                            const uint64_t *__restrict__ vals,
                                                            const unsigned long long *n_left, uint64_t *trig,
@@ -2779,7 +2783,7 @@ extern "C" int smetric_index_evict(smetric_index *idx, uint32_t frac_num, uint32
   if ((rc = fill(ix.pool, ix.n_records * uint64_t(ix.words) * 8, 0, stream))) return rc;
   hipLaunchKernelGGL(rebuild_tile_kernel, dim3(n_tiles), dim3(TILE), 0, stream, ix, cut, cut_dev, ws.ka, ws.va,
                      &st->n_left, idx->capacity, (unsigned long long)(n - m));
-  hipLaunchKernelGGL(rebuild_claim_kernel, dim3(n_tiles < MAX_GRID ? n_tiles : MAX_GRID), dim3(TB), 0, stream, ix,
+  hipLaunchKernelGGL(rebuild_claim_kernel, dim3(n_tiles < CLAIM_WG ? n_tiles : CLAIM_WG), dim3(TB), 0, stream, ix,
                      ws.ka, ws.va, &st->n_left, ws.ea, &st->n_trig, ws.ia, &st->n_def, idx->capacity);
   hipLaunchKernelGGL(spill_kernel, dim3(64), dim3(TB), 0, stream, ix, ws.ea, &st->n_trig, nullptr, ws.ka, nullptr,
                      nullptr);
