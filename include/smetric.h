@@ -350,7 +350,7 @@ int smetric_imbalance(const int32_t *inst, const int64_t *t0, const int64_t *t1,
  *   turn           int32[n_req]    turn number within its session (>= 0)
  *   parent         int32[n_req] (out)  parent request, or -1
  *   session        int32[n_req] (out)  index of the chain's first request; may be the memory of
- *                  another array of the call (written after the last read of them)
+ *                  keys, blk_off, user, turn or parent (written after the last read of them)
  *   status         int32 (device, optional: NULL) set to EINVAL if some request has a bad
  *                  key range or a negative turn; such a request gets parent -1, session -1
  *                  and is nobody's parent
